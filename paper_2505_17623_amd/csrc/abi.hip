@@ -1455,9 +1455,8 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     launch_merkle_root(ma, (uint32_t *)(ws + L.o_dig0), (uint32_t *)(ws + L.o_dig1), root, s);
     FsHeader hd{};
     const uint32_t hw[8] = {n, m, k, io->s, (uint32_t)relu, io->round_mode, (uint32_t)t, (uint32_t)P};
-    for (int i = 0; i < 8; i++)
-        for (int j = 0; j < 4; j++) hd.bytes[4 * i + j] = (uint8_t)(hw[i] >> (8 * j));
-    std::memcpy(hd.bytes + 32, pub_digest, 32);
+    std::memcpy(hd.words, hw, 32);  // little-endian host, as the transcript's LE32
+    std::memcpy(hd.words + 8, pub_digest, 32);
     // the layer's challenges (pairs), in the protocol's order
     uint64_t *r1 = fsch, *r2 = r1 + 2 * ln, *rho = r2 + 2 * lk, *lam = rho + 2 * lm, *tau = lam + 8;
     uint64_t *sig = tau + 2 * lP, *rho2 = sig + 2 * (lP + lN);

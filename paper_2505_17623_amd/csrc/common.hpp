@@ -370,7 +370,7 @@ uint64_t merkle_leaves(const MerkleArgs &a);
 // dig0, dig1: merkle_leaves() x 8 words each; root: 32 bytes
 void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *root, hipStream_t st);
 struct FsHeader {
-    uint8_t bytes[64];  // LE32 n, m, k, s, relu, round_mode, t, P, then the 32-byte public digest
+    uint32_t words[16];  // n, m, k, s, relu, round_mode, t, P, then the 32-byte public digest
 };
 void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *root, uint64_t *out, int ndraw,
                       uint32_t *err, hipStream_t st);

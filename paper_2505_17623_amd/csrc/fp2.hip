@@ -416,8 +416,7 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
     constexpr int GS = 65;  // row stride of the staged Gram matrix (odd, so rows start in different banks)
     __shared__ uint64_t g_re[64 * GS], g_im[64 * GS];
     __shared__ f2 W[64], cpre[32], contrib[4][32], tau[8], sig[8], lam[4], pre[8], gsh[4];
-    __shared__ uint32_t fsbuf32[kFsLdsBytes / 4];  // the transcript (Fiat-Shamir mode)
-    uint8_t *fsbuf = (uint8_t *)fsbuf32;
+    __shared__ FsLds fsl;  // the transcript (Fiat-Shamir mode)
     const int tid = threadIdx.x, lP = a.lP, P = a.P;
     for (int e = tid; e < P * P; e += blockDim.x) {
         const int p = e >> lP, q = e & (P - 1);
@@ -441,8 +440,8 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
     }
     if (tid == 0) {
         pre[0] = f2of(1);  // pre[i] = prod over i' < i of eq(tau_i', sigma_i'), after round i - 1
-        if (a.fs) fs_pull(a.fs, fsbuf);
     }
+    if (a.fs) fs_pull(fsl, a.fs);
     for (int jj = 0; jj < lP; jj++) {
         __syncthreads();
         if (tid < (1 << jj)) {
@@ -494,17 +493,14 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
             gsh[tid] = g;
         }
         __syncthreads();
+        if (a.fs) {  // the round's values absorbed, sigma_jj drawn
+            if (!fs_absorb(fsl, (const uint32_t *)gsh, 16) && tid == 0) *a.err = 1;
+            fs_draw(fsl);
+            if (jj == lP - 1) fs_push(a.fs, fsl);
+        }
         if (tid == 0) {
-            if (a.fs) {  // the round's values absorbed, sigma_jj drawn
-                uint64_t w[8], c[2];
-                for (int q = 0; q < 4; q++) {
-                    w[2 * q] = gsh[q].re;
-                    w[2 * q + 1] = gsh[q].im;
-                }
-                if (!fs_absorb_words_lds(fsbuf, w, 8)) *a.err = 1;
-                fs_draw_lds(fsbuf, c);
-                if (jj == lP - 1) fs_push(a.fs, fsbuf);
-                sig[jj] = f2{c[0], c[1]};
+            if (a.fs) {
+                sig[jj] = f2{fsl.out[0], fsl.out[1]};
                 stp(a.sig_out + 2 * jj, sig[jj]);
             }
             pre[jj + 1] = f2mul(pre[jj], eq1z(tau[jj], sig[jj]));

@@ -1,6 +1,6 @@
 // fs.hip -- the non-interactive layer proof (Fiat-Shamir over F_{p^2}) on
 // the device: the Merkle root of the witness tables, the transcript (absorb
-// and draw, one thread: the hash chain is sequential), and the sum-check
+// and draw, one workgroup: the hash chain is sequential), and the sum-check
 // rounds reordered for challenges that exist only after a round's values are
 // hashed.
 //
@@ -143,35 +143,44 @@ void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *r
 }
 
 // ---------------------------------------------------------------------------
-// Transcript kernels: one thread hashes, from LDS (fs_device.hpp); a failed
-// absorb sets *err.
+// Transcript kernels (fs_device.hpp): one workgroup; a failed absorb sets *err.
 // ---------------------------------------------------------------------------
-__global__ void k_fs_header(sha::Transcript *fs, FsHeader h, const uint8_t *__restrict__ root, uint64_t *out,
-                            int ndraw, uint32_t *err)
+constexpr int kFsThreads = 128;  // one wave runs the rounds, one the message schedules
+
+// ndraw challenges in a row to out.
+__device__ __forceinline__ void fs_draws(FsLds &f, uint64_t *out, int ndraw)
 {
-    __shared__ uint32_t buf32[kFsLdsBytes / 4];
-    uint8_t *buf = (uint8_t *)buf32;
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    fs_pull(fs, buf);
-    uint8_t r[32];
-    for (int i = 0; i < 32; i++) r[i] = root[i];
-    if (!fs_absorb_bytes_lds(buf, h.bytes, 64) || !fs_absorb_bytes_lds(buf, r, 32)) *err = 1;
-    for (int i = 0; i < ndraw; i++) fs_draw_lds(buf, out + 2 * i);
-    fs_push(fs, buf);
+    for (int i = 0; i < ndraw; i++) {
+        fs_draw(f);
+        if (threadIdx.x < 2) out[2 * i + threadIdx.x] = f.out[threadIdx.x];
+    }
 }
 
-__global__ void k_fs_absorb_draw(sha::Transcript *fs, const uint64_t *__restrict__ w, int nw, uint64_t *out,
-                                 int ndraw, uint32_t *err)
+__global__ __launch_bounds__(kFsThreads) void k_fs_header(sha::Transcript *fs, FsHeader h,
+                                                          const uint8_t *__restrict__ root, uint64_t *out, int ndraw,
+                                                          uint32_t *err)
 {
-    __shared__ uint32_t buf32[kFsLdsBytes / 4];
-    uint8_t *buf = (uint8_t *)buf32;
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    fs_pull(fs, buf);
-    uint64_t v[16];
-    for (int i = 0; i < nw && i < 16; i++) v[i] = w[i];
-    if (nw > 16 || (nw && !fs_absorb_words_lds(buf, v, (uint32_t)nw))) *err = 1;
-    for (int i = 0; i < ndraw; i++) fs_draw_lds(buf, out + 2 * i);
-    fs_push(fs, buf);
+    __shared__ FsLds f;
+    __shared__ uint32_t msg[24];  // the header, then the root
+    const int tid = threadIdx.x;
+    fs_pull(f, fs);
+    if (tid < 16) msg[tid] = h.words[tid];
+    else if (tid < 24) msg[tid] = ((const uint32_t *)root)[tid - 16];
+    if (!fs_absorb(f, msg, 24) && tid == 0) *err = 1;
+    fs_draws(f, out, ndraw);
+    __syncthreads();
+    fs_push(fs, f);
+}
+
+__global__ __launch_bounds__(kFsThreads) void k_fs_absorb_draw(sha::Transcript *fs, const uint64_t *__restrict__ w,
+                                                               int nw, uint64_t *out, int ndraw, uint32_t *err)
+{
+    __shared__ FsLds f;
+    fs_pull(f, fs);
+    if (!fs_absorb(f, (const uint32_t *)w, 2 * nw) && threadIdx.x == 0) *err = 1;
+    fs_draws(f, out, ndraw);
+    __syncthreads();
+    fs_push(fs, f);
 }
 
 // A round's values from its blocks' partials (eight words per block, the
@@ -181,31 +190,30 @@ __global__ __launch_bounds__(256) void k_fs_round(const uint64_t *__restrict__ p
                                                   uint32_t *err)
 {
     __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    __shared__ uint32_t buf32[kFsLdsBytes / 4];
-    uint8_t *buf = (uint8_t *)buf32;
-    if (threadIdx.x == 0) fs_pull(fs, buf);  // overlaps the sum below
+    __shared__ FsLds f;
+    const int tid = threadIdx.x;
+    fs_pull(f, fs);
     uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nb; b += blockDim.x)
+    for (int b = tid; b < nb; b += blockDim.x)
 #pragma unroll
         for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], part[8 * (size_t)b + q]);
-    m61::block_sum<8>(v, red);
-    if (threadIdx.x != 0) return;
-    for (int q = 0; q < nw; q++) ev[q] = v[q];
-    if (!fs_absorb_words_lds(buf, v, (uint32_t)nw)) *err = 1;
-    fs_draw_lds(buf, out);
-    fs_push(fs, buf);
+    const uint64_t *tot = m61::block_sum_lds<8>(v, red);
+    if (tid < nw) ev[tid] = tot[tid];
+    if (!fs_absorb(f, (const uint32_t *)tot, 2 * nw) && tid == 0) *err = 1;
+    fs_draws(f, out, 1);
+    fs_push(fs, f);
 }
 
 void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *root, uint64_t *out, int ndraw,
                       uint32_t *err, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fs_header, dim3(1), dim3(64), 0, st, fs, h, root, out, ndraw, err);
+    hipLaunchKernelGGL(k_fs_header, dim3(1), dim3(kFsThreads), 0, st, fs, h, root, out, ndraw, err);
 }
 
 void launch_fs_absorb_draw(sha::Transcript *fs, const uint64_t *w, int nw, uint64_t *out, int ndraw, uint32_t *err,
                            hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fs_absorb_draw, dim3(1), dim3(64), 0, st, fs, w, nw, out, ndraw, err);
+    hipLaunchKernelGGL(k_fs_absorb_draw, dim3(1), dim3(kFsThreads), 0, st, fs, w, nw, out, ndraw, err);
 }
 
 void launch_fs_round(const uint64_t *part, int nb, int nw, uint64_t *ev, sha::Transcript *fs, uint64_t *out,
