@@ -1222,9 +1222,8 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     const int gt = plane_gram_tiles(lP, pused), gb = plane_gram_blocks(N, lP);
     uint64_t *gp0 = (uint64_t *)(ws + L.o_gp0), *gp1 = (uint64_t *)(ws + L.o_gp1);
     launch_plane_gram(lP, d_bits, N, 0, EQ.re, ONE.re, sig, Bx.re, gp0, nullptr, s, SIG.re, pused);
-    launch_f2_gram_sum(gp0, gb, gt, Gre, s);
     launch_plane_gram(lP, d_bits, N, 0, EQ.im, ONE.re, sig, Bx.im, gp1, nullptr, s, SIG.im, pused);
-    launch_f2_gram_sum(gp1, gb, gt, Gim, s);
+    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, s);
     {
         F2PlaneArgs pa{};
         pa.G_re = Gre;
@@ -1509,9 +1508,8 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     const int gt = plane_gram_tiles(lP, pused), gb = plane_gram_blocks(N, lP);
     uint64_t *gp0 = (uint64_t *)(ws + L.o_gp0), *gp1 = (uint64_t *)(ws + L.o_gp1);
     launch_plane_gram(lP, d_bits, N, 0, EQ.re, ONE.re, SIG.re, Bx.re, gp0, nullptr, s, SIG.re, pused);
-    launch_f2_gram_sum(gp0, gb, gt, Gre, s);
     launch_plane_gram(lP, d_bits, N, 0, EQ.im, ONE.re, SIG.re, Bx.im, gp1, nullptr, s, SIG.re, pused);
-    launch_f2_gram_sum(gp1, gb, gt, Gim, s);
+    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, s);
     {
         F2PlaneArgs pa{};
         pa.G_re = Gre;
@@ -1530,10 +1528,10 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
         pa.range_sum = tr + 14;
         pa.fs = c->d_fs;
         pa.sig_out = sig;
+        pa.sig_tab = SIG;
         pa.err = err;
         launch_f2_planes(pa, s);
     }
-    launch_f2_eq(sig, lP, SIG, s);
     launch_f2_bx(d_bits, N, SIG, P, Bx, s);
     // rounds over x of the range instance, then the ReLU zero-check
     for (int j = 0; j < lN; j++) {

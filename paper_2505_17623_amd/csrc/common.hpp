@@ -344,6 +344,7 @@ struct F2PlaneArgs {
     // transcript (after each round's values) into sig_out instead of read
     sha::Transcript *fs = nullptr;
     uint64_t *sig_out = nullptr;
+    F2Tab sig_tab{nullptr, nullptr};  // optional, out: eq(sigma_p, .), zero past P (64 entries)
     uint32_t *err = nullptr;
 };
 void launch_f2_eq(const uint64_t *z, int v, F2Tab out, hipStream_t st);
@@ -354,7 +355,8 @@ void launch_f2_sum8(const uint64_t *part, int nb, uint64_t *out, hipStream_t st)
 void launch_f2_round(const F2RoundArgs &a, hipStream_t st);
 void launch_f2_finish(const F2FinishArgs &a, hipStream_t st);
 void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st);
-void launch_f2_gram_sum(const uint64_t *gpart, int nblk, int TP, uint64_t *G, hipStream_t st);
+void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
+                        uint64_t *G_im, hipStream_t st);
 
 // ---- the non-interactive layer proof (fs.hip) ----
 struct MerkleSeg {

@@ -19,48 +19,12 @@
 // large, and the last rounds of an instance in one workgroup over LDS; this
 // is slower than the F_p path's fused passes.
 #include "common.hpp"
-#include "m61.hpp"
+#include "f2.hpp"
 #include "gram_reduce.hpp"
 #include "fs_device.hpp"
 #include "sha256.hpp"
 
 namespace ra {
-
-struct f2 {
-    uint64_t re, im;
-};
-
-__device__ __forceinline__ f2 f2of(uint64_t a) { return f2{a, 0}; }
-__device__ __forceinline__ f2 f2add(f2 a, f2 b) { return f2{m61::add(a.re, b.re), m61::add(a.im, b.im)}; }
-__device__ __forceinline__ f2 f2sub(f2 a, f2 b) { return f2{m61::sub(a.re, b.re), m61::sub(a.im, b.im)}; }
-// (a0 + a1 i)(b0 + b1 i) = (a0 b0 - a1 b1) + ((a0 + a1)(b0 + b1) - a0 b0 - a1 b1) i:
-// three products of F_p instead of four
-__device__ __forceinline__ f2 f2mul(f2 a, f2 b)
-{
-    const uint64_t p0 = m61::mul(a.re, b.re), p1 = m61::mul(a.im, b.im);
-    const uint64_t p2 = m61::mul(m61::add(a.re, a.im), m61::add(b.re, b.im));
-    return f2{m61::sub(p0, p1), m61::sub(m61::sub(p2, p0), p1)};
-}
-// a c for a small integer c (|c| < 2^31)
-__device__ __forceinline__ f2 f2small(f2 a, int32_t c) { return f2{m61::mul_small(a.re, c), m61::mul_small(a.im, c)}; }
-// a c for an F_p element c
-__device__ __forceinline__ f2 f2scale(f2 a, uint64_t c) { return f2{m61::mul(a.re, c), m61::mul(a.im, c)}; }
-__device__ __forceinline__ f2 ldp(const uint64_t *p) { return f2{p[0], p[1]}; }  // a challenge (re, im)
-__device__ __forceinline__ void stp(uint64_t *p, f2 v)
-{
-    p[0] = v.re;
-    p[1] = v.im;
-}
-__device__ __forceinline__ f2 ldt(const F2Tab &t, uint64_t i) { return f2{t.re[i], t.im[i]}; }
-__device__ __forceinline__ void stt(const F2Tab &t, uint64_t i, f2 v)
-{
-    t.re[i] = v.re;
-    t.im[i] = v.im;
-}
-// eq(z, b) for one variable and a bit b
-__device__ __forceinline__ f2 eq1b(f2 z, int b) { return b ? z : f2sub(f2of(1), z); }
-// eq(z, X) = (1 - X) + z (2 X - 1) for a small integer X
-__device__ __forceinline__ f2 eq1x(f2 z, int X) { return f2add(f2of(m61::from_i64(1 - X)), f2small(z, 2 * X - 1)); }
 
 // Block sum of the eight words of four F_{p^2} values; thread 0 writes them.
 __device__ __forceinline__ void f2_block_out(const f2 (&acc)[4], uint64_t *red, uint64_t *out)
@@ -386,36 +350,45 @@ void launch_f2_finish(const F2FinishArgs &a, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------
-// The plane rounds of the range instance from the Gram matrix (one
-// workgroup).  With the plane variables q_1 .. q_{j-1} bound to sigma and q_j
-// = X, the table is b(sigma_<j, X, q', x) = sum_{y, z} c_X(y, z)
-// bit_{(y, z, q')}(x) with c_X(y, z) = eq(sigma_<j, y) eq(X, z), so
-//   g_j(X) = sum_{q'} E(X, q') (Q - L) + mu Wt(X, q') L,
-//   Q = c^T G c, L = sum c G_diag (a bit squared is itself),
-//   E(X, q') = eq(tau_p, (sigma_<j, X, q')), Wt(X, q') = W~(sigma_<j, X, q'),
-// where the sums run over the planes (y, z, q') and G[p][p'] = sum_x EQ(x)
-// bit_p(x) bit_p'(x).  Also writes the x rounds' constants c_eq =
-// eq(tau_p, sigma_p), c_w = mu W~(sigma_p) and the claimed sum
-// mu (l1 Rm~ + l2 (R~ + 2^(t+1)) + l3 Y~).  G and the challenges are staged
-// in LDS.  Round j has 4 P / 2^(j+1) items (X, q') of 2^(j+1) rows each, so
-// 4 P <= 256 threads take one (item, row) pair each; an item's rows are
-// adjacent lanes and are summed by a butterfly inside their lane group.
+// The plane rounds of the range instance from the Gram matrix G[p][p'] =
+// sum_x EQ(x) bit_p(x) bit_p'(x) (one workgroup).  A bit squared is itself, so
+// with the diagonal g = diag(G) and the plane weights W the summand's sums
+// over x are
+//   g_j(X) = K_j eq(tau_j, X) sum_q es(q) (Q - L) + mu sum_q w L
+// where q runs over the planes after the free one, es = eq(tau_{>j}, .), and
+// Q, L, w are G, g and W bound at (sigma_<j, X): Q quadratic in X from G's
+// entries (q, q), (q, q + h), (q + h, q + h), L and w linear from entries q
+// and q + h.  So a round needs eight sums over at most 32 planes (five with
+// es, three of W with g), one per group of 32 lanes; then g and W are folded at
+// sigma_j, and G on both sides (its upper triangle, h (h + 1) / 2 entries).
+// Keeping G unfolded and forming c^T G c anew each round took 106 us (118 us
+// with the challenges hashed, MI355X, 64 planes); this takes 37 and 61.
+//
+// Also writes the x rounds' constants c_eq = eq(tau_p, sigma_p), c_w =
+// mu W~(sigma_p), the claimed sum mu (l1 Rm~ + l2 (R~ + 2^(t+1)) + l3 Y~) and,
+// where wanted, the table eq(sigma_p, .).
 // ---------------------------------------------------------------------------
-// eq(a, b) for one variable, both points in F_{p^2}: a b + (1 - a)(1 - b)
-__device__ __forceinline__ f2 eq1z(f2 a, f2 b) { return f2add(f2mul(a, b), f2mul(f2sub(f2of(1), a), f2sub(f2of(1), b))); }
-
-__device__ __forceinline__ f2 group_sum(f2 v, int width)
+__device__ __forceinline__ f2 group32_sum(f2 v)
 {
-    for (int off = 1; off < width; off <<= 1)
-        v = f2{m61::add(v.re, __shfl_xor(v.re, off, 64)), m61::add(v.im, __shfl_xor(v.im, off, 64))};
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1)
+        v = f2{m61::fold(v.re + __shfl_xor(v.re, off, 64)), m61::fold(v.im + __shfl_xor(v.im, off, 64))};
     return v;
+}
+
+// eq(z, .) of k variables at index i (first variable most significant)
+__device__ __forceinline__ f2 eq_entry(const f2 *z, int k, int i)
+{
+    f2 e = f2of(1);
+    for (int j = 0; j < k; j++) e = l2mul(e, eq1b(z[j], (i >> (k - 1 - j)) & 1));
+    return e;
 }
 
 __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
 {
     constexpr int GS = 65;  // row stride of the staged Gram matrix (odd, so rows start in different banks)
     __shared__ uint64_t g_re[64 * GS], g_im[64 * GS];
-    __shared__ f2 W[64], cpre[32], contrib[4][32], tau[8], sig[8], lam[4], pre[8], gsh[4];
+    __shared__ f2 W[64], dv[64], es[64], tau[8], sig[8], lam[4], pre[8], tot[8], gsh[4];
     __shared__ FsLds fsl;  // the transcript (Fiat-Shamir mode)
     const int tid = threadIdx.x, lP = a.lP, P = a.P;
     for (int e = tid; e < P * P; e += blockDim.x) {
@@ -428,6 +401,7 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
         if (!a.fs) sig[tid] = ldp(a.sig + 2 * tid);  // else drawn after each round
     }
     if (tid < 4) lam[tid] = ldp(a.lam + 2 * tid);
+    if (a.fs) fs_pull(fsl, a.fs);
     __syncthreads();
     const f2 mu = lam[3];
     if (tid < 64) {
@@ -437,58 +411,54 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
         else if (tid < s + t + 2) w = f2scale(lam[1], 1ull << (tid - s));
         else if (a.relu && tid < s + 2 * t + 4) w = f2scale(lam[2], 1ull << (tid - s - t - 2));
         W[tid] = tid < P ? w : f2of(0);
-    }
-    if (tid == 0) {
+        if (tid < P) dv[tid] = f2{g_re[tid * GS + tid], g_im[tid * GS + tid]};
+    } else if (tid < 128) {  // the suffix eq tables as a heap: 2^k entries from index 2^k, over the last k variables
+        const int i = tid - 64;
+        if (i >= 1 && i < P) {
+            const int k = 31 - __builtin_clz(i);
+            es[i] = eq_entry(tau + lP - k, k, i - (1 << k));
+        }
+    } else if (tid == 128) {
         pre[0] = f2of(1);  // pre[i] = prod over i' < i of eq(tau_i', sigma_i'), after round i - 1
     }
-    if (a.fs) fs_pull(fsl, a.fs);
+    __syncthreads();
     for (int jj = 0; jj < lP; jj++) {
-        __syncthreads();
-        if (tid < (1 << jj)) {
-            f2 c = f2of(1);
-            for (int i = 0; i < jj; i++) c = f2mul(c, eq1b(sig[i], (tid >> (jj - 1 - i)) & 1));
-            cpre[tid] = c;
-        }
-        __syncthreads();
-        const int sh = lP - jj - 1, nq = 1 << sh, nrows = 2 << jj;
-        const int item = tid >> (jj + 1), r = tid & (nrows - 1);
-        const int X = item >> sh, qp = item & (nq - 1);
-        const bool on = tid < 4 * P;
-        auto coef = [&](int row) {
-            const f2 c = cpre[row >> 1];
-            return (row & 1) ? f2small(c, X) : f2small(c, 1 - X);
-        };
-        f2 Q = f2of(0), L = f2of(0), Ws = f2of(0);
-        if (on) {
-            const int pr = (r << sh) | qp;
-            const uint64_t *gr = g_re + pr * GS + qp, *gi = g_im + pr * GS + qp;
-            // four independent partial sums, so the products of four rows are
-            // in flight together (the sum is exact in any order)
-            f2 r4[4] = {f2of(0), f2of(0), f2of(0), f2of(0)};
-            int c = 0;
-            for (; c + 3 < nrows; c += 4)
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    r4[u] = f2add(r4[u], f2mul(coef(c + u), f2{gr[(c + u) << sh], gi[(c + u) << sh]}));
-            for (; c < nrows; c++) r4[0] = f2add(r4[0], f2mul(coef(c), f2{gr[c << sh], gi[c << sh]}));
-            const f2 row = f2add(f2add(r4[0], r4[1]), f2add(r4[2], r4[3]));
-            const f2 cr = coef(r);
-            Q = f2mul(cr, row);
-            L = f2mul(cr, f2{g_re[pr * GS + pr], g_im[pr * GS + pr]});
-            Ws = f2mul(cr, W[pr]);
-        }
-        Q = group_sum(Q, nrows);
-        L = group_sum(L, nrows);
-        Ws = group_sum(Ws, nrows);
-        if (on && r == 0) {
-            f2 E = f2mul(pre[jj], eq1x(tau[jj], X));
-            for (int i = jj + 1; i < lP; i++) E = f2mul(E, eq1b(tau[i], (qp >> (lP - 1 - i)) & 1));
-            contrib[X][qp] = f2add(f2mul(E, f2sub(Q, L)), f2mul(mu, f2mul(Ws, L)));
+        const int h = P >> (jj + 1);
+        {   // the round's eight sums
+            const int T = tid >> 5, q = tid & 31;
+            f2 v = f2of(0);
+            if (q < h) {
+                const int e00 = q * GS + q, e01 = e00 + h, e11 = e00 + h * GS + h;
+                f2 x, y;
+                if (T < 5) {
+                    x = es[h + q];
+                    if (T == 0) y = f2{g_re[e00], g_im[e00]};
+                    else if (T == 1) y = f2{g_re[e01], g_im[e01]};
+                    else if (T == 2) y = f2{g_re[e11], g_im[e11]};
+                    else y = dv[T == 3 ? q : q + h];
+                } else if (T == 5) {
+                    x = W[q];
+                    y = dv[q];
+                } else if (T == 6) {
+                    x = W[q + h];
+                    y = dv[q + h];
+                } else {
+                    x = l2add(W[q], W[q + h]);
+                    y = l2add(dv[q], dv[q + h]);
+                }
+                v = l2mul(x, y);
+            }
+            v = group32_sum(v);
+            if (q == 0) tot[T] = l2canon(v);
         }
         __syncthreads();
         if (tid < 4) {
-            f2 g = f2of(0);
-            for (int q = 0; q < nq; q++) g = f2add(g, contrib[tid][q]);
+            const int X = tid, u = 1 - X;
+            const f2 cross = f2sub(f2sub(tot[7], tot[5]), tot[6]);
+            f2 A = f2add(f2add(f2small(tot[0], u * u), f2small(tot[1], 2 * X * u)), f2small(tot[2], X * X));
+            A = f2sub(f2sub(A, f2small(tot[3], u)), f2small(tot[4], X));
+            const f2 B = f2add(f2add(f2small(tot[5], u * u), f2small(cross, X * u)), f2small(tot[6], X * X));
+            const f2 g = f2add(f2mul(f2mul(pre[jj], eq1x(tau[jj], X)), A), f2mul(mu, B));
             stp(a.ev + 8 * jj + 2 * tid, g);
             gsh[tid] = g;
         }
@@ -497,33 +467,41 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
             if (!fs_absorb(fsl, (const uint32_t *)gsh, 16) && tid == 0) *a.err = 1;
             fs_draw(fsl);
             if (jj == lP - 1) fs_push(a.fs, fsl);
-        }
-        if (tid == 0) {
-            if (a.fs) {
+            if (tid == 0) {
                 sig[jj] = f2{fsl.out[0], fsl.out[1]};
                 stp(a.sig_out + 2 * jj, sig[jj]);
             }
-            pre[jj + 1] = f2mul(pre[jj], eq1z(tau[jj], sig[jj]));
+            __syncthreads();
         }
+        const f2 sg = sig[jj];
+        if (tid == 255) pre[jj + 1] = f2mul(pre[jj], eq1z(tau[jj], sg));
+        // the folds; an entry's four sources are read by its own thread only
+        if (tid < h) dv[tid] = l2fold(dv[tid], dv[tid + h], sg);
+        else if (tid >= 64 && tid < 64 + h) W[tid - 64] = l2fold(W[tid - 64], W[tid - 64 + h], sg);
+        if (h > 1)
+            for (int e = tid; e < (h / 2) * (h + 1); e += blockDim.x) {
+                // the upper triangle, rows r and h - 1 - r side by side (h + 1 entries)
+                const int r = e / (h + 1), c = e - r * (h + 1), first = h - r;
+                const int i = c < first ? r : h - 1 - r, k = c < first ? r + c : i + c - first;
+                // (i, k), (i, k + h), (i + h, k) = (k, i + h) by symmetry, (i + h, k + h)
+                const int e00 = i * GS + k, e01 = e00 + h, e10 = k * GS + i + h, e11 = e00 + h * GS + h;
+                const f2 lo = l2fold(f2{g_re[e00], g_im[e00]}, f2{g_re[e10], g_im[e10]}, sg);
+                const f2 hi = l2fold(f2{g_re[e01], g_im[e01]}, f2{g_re[e11], g_im[e11]}, sg);
+                const f2 o = l2fold(lo, hi, sg);
+                g_re[e00] = o.re;
+                g_im[e00] = o.im;
+            }
+        __syncthreads();
     }
-    __syncthreads();
-    // x rounds' constants and the claimed sum
-    if (tid < 64) {
-        f2 term = f2of(0);
-        if (tid < P) {
-            f2 e = f2of(1);
-            for (int i = 0; i < lP; i++) e = f2mul(e, eq1b(sig[i], (tid >> (lP - 1 - i)) & 1));
-            term = f2mul(e, W[tid]);
-        }
-        const f2 wsig = f2{m61::wave_sum(term.re), m61::wave_sum(term.im)};
-        if (tid == 0) {
-            stp(a.cst, pre[lP]);
-            stp(a.cst + 2, f2mul(mu, wsig));
-            const f2 r = ldp(a.claims), rm = ldp(a.claims + 2), y = ldp(a.claims + 4);
-            f2 H = f2add(f2mul(lam[0], rm), f2mul(lam[1], f2add(r, f2of(1ull << (a.t + 1)))));
-            if (a.relu) H = f2add(H, f2mul(lam[2], y));
-            stp(a.range_sum, f2mul(mu, H));
-        }
+    if (tid < 64 && a.sig_tab.re) stt(a.sig_tab, tid, tid < P ? l2canon(eq_entry(sig, lP, tid)) : f2of(0));
+    if (tid == 64) {  // x rounds' constants
+        stp(a.cst, pre[lP]);
+        stp(a.cst + 2, f2mul(mu, l2canon(W[0])));
+    } else if (tid == 128) {  // the claimed sum
+        const f2 r = ldp(a.claims), rm = ldp(a.claims + 2), y = ldp(a.claims + 4);
+        f2 H = f2add(f2mul(lam[0], rm), f2mul(lam[1], f2add(r, f2of(1ull << (a.t + 1)))));
+        if (a.relu) H = f2add(H, f2mul(lam[2], y));
+        stp(a.range_sum, f2mul(mu, H));
     }
 }
 
@@ -532,17 +510,20 @@ void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st)
     hipLaunchKernelGGL(k_f2_planes, dim3(1), dim3(kThreads), 0, st, a);
 }
 
-// The Gram matrix from the partial tiles of one Gram pass.
-__global__ __launch_bounds__(256) void k_f2_gram_sum(const uint64_t *__restrict__ gpart, int nblk, int tiles,
-                                                     uint64_t *__restrict__ G)
+// The Gram matrix's two parts from the partial tiles of their passes.
+__global__ __launch_bounds__(256) void k_f2_gram_sum(const uint64_t *__restrict__ gp_re,
+                                                     const uint64_t *__restrict__ gp_im, int nblk, int tiles,
+                                                     uint64_t *__restrict__ G_re, uint64_t *__restrict__ G_im)
 {
     __shared__ uint64_t red[kGramReduceLdsWords];
-    gram_reduce_block(gpart, nblk, tiles, G, blockIdx.x, red);
+    gram_reduce_block(blockIdx.y ? gp_im : gp_re, nblk, tiles, blockIdx.y ? G_im : G_re, blockIdx.x, red);
 }
 
-void launch_f2_gram_sum(const uint64_t *gpart, int nblk, int tiles, uint64_t *G, hipStream_t st)
+void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
+                        uint64_t *G_im, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f2_gram_sum, dim3(gram_reduce_groups(tiles)), dim3(kThreads), 0, st, gpart, nblk, tiles, G);
+    hipLaunchKernelGGL(k_f2_gram_sum, dim3(gram_reduce_groups(tiles), 2), dim3(kThreads), 0, st, gp_re, gp_im, nblk,
+                       tiles, G_re, G_im);
 }
 
 }  // namespace ra
