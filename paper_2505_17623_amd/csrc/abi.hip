@@ -452,7 +452,7 @@ RangeLayout range_layout(uint64_t N, int lP, int relu)
 constexpr int kF2TrFixed = 22;
 struct Fp2Layout {
     size_t o_gemm, o_e1, o_e2, o_scr, o_a, o_b, o_eq, o_eqr, o_eqz, o_bx, o_d, o_s, o_sig, o_one, o_gp0, o_gp1, o_g,
-        o_part, o_cpart, o_cst, o_tr, tr_words, o_fsch, o_dig0, o_dig1, o_root, o_err, bytes;
+        o_part, o_cpart, o_cst, o_tr, tr_words, o_hs, o_ls, o_fsch, o_fsk, o_fst, o_dig0, o_dig1, o_root, o_err, bytes;
 };
 // leaves of the witness tables' Merkle tree (R, Rm, Y, Z int32 / uint16, the bit words)
 uint64_t witness_leaves(uint64_t N)
@@ -489,8 +489,14 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_cst = cv.take<uint64_t>(8);
     l.tr_words = kF2TrFixed + 6 * (size_t)lm + 8 * (size_t)(kMaxPlaneLog + lN) + 8 * (size_t)lN;
     l.o_tr = cv.take<uint64_t>(l.tr_words);
-    // Fiat-Shamir: the layer's drawn challenges (pairs), the Merkle digests, the root, a status word
-    l.o_fsch = cv.take<uint64_t>(2 * ((size_t)log2u(n) + log2u(k) + lm + 4 + 2 * kMaxPlaneLog + 2 * (size_t)lN));
+    const int low = std::min(lN, kF2Low);
+    l.o_hs = cv.take<uint64_t>(4ull << (lN - low));
+    l.o_ls = cv.take<uint64_t>(4ull << low);
+    // Fiat-Shamir: the layer's drawn challenges (pairs; those of the rounds over tables are not kept), two
+    // running products, the transcript's second copy, the Merkle digests, the root, a status word
+    l.o_fsch = cv.take<uint64_t>(2 * ((size_t)lN + 4 + 2 * kMaxPlaneLog));
+    l.o_fsk = cv.take<uint64_t>(4);
+    l.o_fst = cv.take<sha::Transcript>(1);
     l.o_dig0 = cv.take<uint32_t>(8 * witness_leaves(N));
     l.o_dig1 = cv.take<uint32_t>(8 * ((witness_leaves(N) + 3) / 4));
     l.o_root = cv.take<uint8_t>(32);
@@ -1401,7 +1407,7 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     };
     const uint64_t H = N > 1 ? N / 2 : 1;
     const F2Tab E1 = tab(L.o_e1, n), E2 = tab(L.o_e2, k), Ta = tab(L.o_a, m), Tb = tab(L.o_b, m);
-    const F2Tab EQ = tab(L.o_eq, N), EQr = tab(L.o_eqr, H), EQz = tab(L.o_eqz, H), Bx = tab(L.o_bx, N);
+    const F2Tab EQ = tab(L.o_eq, N), Bx = tab(L.o_bx, N);
     const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64), ONE = tab(L.o_one, 1);
     uint64_t *scr = (uint64_t *)(ws + L.o_scr), *part = (uint64_t *)(ws + L.o_part);
     uint64_t *cpart = (uint64_t *)(ws + L.o_cpart), *cst = (uint64_t *)(ws + L.o_cst);
@@ -1457,51 +1463,92 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     std::memcpy(hd.words, hw, 32);  // little-endian host, as the transcript's LE32
     std::memcpy(hd.words + 8, pub_digest, 32);
     // the layer's challenges (pairs), in the protocol's order
-    uint64_t *r1 = fsch, *r2 = r1 + 2 * ln, *rho = r2 + 2 * lk, *lam = rho + 2 * lm, *tau = lam + 8;
-    uint64_t *sig = tau + 2 * lP, *rho2 = sig + 2 * (lP + lN);
-    launch_fs_header(c->d_fs, hd, root, r1, ln + lk, err, s);
-    launch_f2_eq(r1, ln, E1, s);
-    launch_f2_eq(r2, lk, E2, s);
+    uint64_t *r1 = fsch, *lam = r1 + 2 * lN, *tau = lam + 8, *sig = tau + 2 * lP;
+    launch_fs_header(c->d_fs, hd, root, r1, lN, err, s);
+    f2 *HS = (f2 *)(ws + L.o_hs), *LS = (f2 *)(ws + L.o_ls);
+    launch_f2_eqs(r1, ln, lk, E1, E2, HS, LS, s);
 
-    // matrix instance: each round folds the previous round's variable, then
-    // evaluates; its values are hashed into the next challenge
+    // An instance: one launch per round while its tables hold more than
+    // 2^kFsTailLog entries, each finishing the round before it, then the rest
+    // in one workgroup.  The transcript, the running product of the eq
+    // factors and the partials alternate between two copies.
+    sha::Transcript *fst[2] = {c->d_fs, (sha::Transcript *)(ws + L.o_fst)};
+    uint64_t *fsk = (uint64_t *)(ws + L.o_fsk);
+    const int tabs = ((int)io->s + (t + 2) * (relu ? 2 : 1) + 7) / 8;  // bytes of a bit word the witness writes
+    auto instance = [&](int kind, int v, F2Tab s0, F2Tab s1, F2Tab d0, F2Tab d1, uint64_t *ev, uint64_t *fin) {
+        const int width = kind == F2_MATMUL ? 6 : 8;
+        FsFinArgs fn{};
+        fn.cst = cst;
+        fn.fs_in = fst[0];
+        fn.err = err;
+        int j = 0;
+        for (; v - j > kFsTailLog; j++) {
+            FsPassArgs pa{};
+            pa.kind = kind;
+            pa.h = 1ull << (v - 1 - j);
+            pa.src[0] = j <= 1 ? s0 : d0;
+            pa.src[1] = j <= 1 ? s1 : d1;
+            pa.dst[0] = d0;
+            pa.dst[1] = d1;
+            if (kind == F2_RELU && j <= 1) {
+                pa.R = d_R;
+                pa.Y = d_Y;
+            }
+            pa.bits = d_bits;
+            pa.sig = SIG;
+            pa.tabs = tabs;
+            pa.HS = HS;
+            pa.LS = LS;
+            pa.part = part + (size_t)(j & 1) * 10 * kF2MaxBlocks;
+            pa.fin = fn;
+            launch_fs_pass(pa, s);
+            if (j > 0) fn.fs_in = fn.fs_out;
+            fn.nb = f2_blocks(pa.h);
+            fn.part = pa.part;
+            fn.r = r1 + 2 * j;
+            fn.ev = ev + width * j;
+            fn.fs_out = fn.fs_in == fst[0] ? fst[1] : fst[0];
+            fn.K_in = j > 0 ? fsk + 2 * (j & 1) : nullptr;
+            fn.K_out = fsk + 2 * ((j + 1) & 1);
+        }
+        FsTailArgs ta{};
+        ta.kind = kind;
+        ta.v = v - j;
+        ta.j0 = j;
+        ta.src[0] = j <= 1 ? s0 : d0;
+        ta.src[1] = j <= 1 ? s1 : d1;
+        if (kind == F2_RELU && j <= 1) {
+            ta.R = d_R;
+            ta.Y = d_Y;
+        }
+        ta.bits = d_bits;
+        ta.sig = SIG;
+        ta.tabs = tabs;
+        ta.LS = LS;
+        ta.r = r1;
+        ta.cst = cst;
+        ta.ev = ev;
+        ta.out = fin;
+        ta.fin = fn;
+        ta.fs_out = fst[0];
+        ta.err = err;
+        launch_fs_tail(ta, s);
+    };
+
+    // matrix instance: A's rows bound at r1, B's columns at r2; a*, b* absorbed at its end
     launch_bind_rows(d_A, a_dtype, n, m, E1.re, scr, Ta.re, s);
     launch_bind_rows(d_A, a_dtype, n, m, E1.im, scr, Ta.im, s);
     launch_bind_cols(d_B, RA_I16, m, k, E2.re, Tb.re, s);
     launch_bind_cols(d_B, RA_I16, m, k, E2.im, Tb.im, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
-    for (int j = 0; j < lm; j++) {
-        F2FsRoundArgs ra{};
-        ra.kind = F2_MATMUL;
-        ra.fold = j > 0;
-        ra.h = (uint64_t)m >> (j + 1);
-        ra.src[0] = ra.dst[0] = Ta;
-        ra.src[1] = ra.dst[1] = Tb;
-        ra.rho_prev = j > 0 ? rho + 2 * (j - 1) : nullptr;
-        ra.part = part;
-        launch_f2_round_fs(ra, s);
-        launch_fs_round(part, f2_blocks(ra.h), 6, ev_mm + 6 * j, c->d_fs, rho + 2 * j, err, s);
-    }
-    {
-        F2FsFinalArgs fa{};
-        fa.kind = F2_MATMUL;
-        fa.rounds = lm;
-        fa.t[0] = Ta;
-        fa.t[1] = Tb;
-        fa.rho = lm ? rho + 2 * (lm - 1) : nullptr;
-        fa.ev0 = ev_mm;
-        fa.fin = tr;
-        launch_f2_final_fs(fa, s);
-    }
-    // the claims at (r1, r2), then a*, b* and the claims absorbed; lambda,
-    // mu, tau_p drawn
+    instance(F2_MATMUL, lm, Ta, Tb, Ta, Tb, ev_mm, tr);
+    // the claims at (r1, r2) absorbed; lambda, mu, tau_p drawn
     launch_f2_outer(E1, E2, lk, N, EQ, s);
     launch_f2_claims(EQ, d_R, d_Rm, d_Y, d_Z, N, cpart, s);
-    launch_f2_sum8(cpart, f2_blocks(N), tr + 6, s);
-    launch_fs_absorb_draw(c->d_fs, tr + 2, 12, lam, 4 + lP, err, s);
+    launch_fs_claims(cpart, f2_blocks(N), tr + 6, c->d_fs, lam, 4 + lP, err, s);
     // plane rounds: the Gram matrix's two parts (their pass's plane-bound
     // output is not used: sigma_p does not exist yet), then the rounds, which
-    // draw sigma_p as they go, then Bx with eq(sigma_p, .)
+    // draw sigma_p as they go
     launch_fill0(SIG.re, 64, s);
     launch_f2_eq(lam, 0, ONE, s);
     const int pused = (int)io->s + (t + 2) * (relu ? 2 : 1);  // planes the witness writes
@@ -1532,65 +1579,10 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
         pa.err = err;
         launch_f2_planes(pa, s);
     }
-    launch_f2_bx(d_bits, N, SIG, P, Bx, s);
-    // rounds over x of the range instance, then the ReLU zero-check
-    for (int j = 0; j < lN; j++) {
-        F2FsRoundArgs ra{};
-        ra.kind = F2_RANGE;
-        ra.fold = j > 0;
-        ra.h = N >> (j + 1);
-        ra.src[0] = j <= 1 ? EQ : EQr;
-        ra.dst[0] = EQr;
-        ra.src[1] = ra.dst[1] = Bx;
-        ra.rho_prev = j > 0 ? sig + 2 * (lP + j - 1) : nullptr;
-        ra.cst = cst;
-        ra.part = part;
-        launch_f2_round_fs(ra, s);
-        launch_fs_round(part, f2_blocks(ra.h), 8, ev_rs + 8 * (size_t)(lP + j), c->d_fs, sig + 2 * (lP + j), err, s);
-    }
-    {
-        F2FsFinalArgs fa{};
-        fa.kind = F2_RANGE;
-        fa.rounds = lN;
-        fa.t[0] = lN >= 2 ? EQr : EQ;
-        fa.t[1] = Bx;
-        fa.rho = lN ? sig + 2 * (lP + lN - 1) : nullptr;
-        fa.fin = tr + 16;
-        launch_f2_final_fs(fa, s);
-    }
-    launch_fs_absorb_draw(c->d_fs, tr + 16, 2, nullptr, 0, err, s);
-    if (relu) {
-        for (int j = 0; j < lN; j++) {
-            F2FsRoundArgs ra{};
-            ra.kind = F2_RELU;
-            ra.fold = j > 0;
-            ra.ints = j <= 1;
-            ra.h = N >> (j + 1);
-            ra.src[0] = j <= 1 ? EQ : EQz;
-            ra.dst[0] = EQz;
-            ra.src[1] = ra.dst[1] = Dt;
-            ra.src[2] = ra.dst[2] = St;
-            ra.R = d_R;
-            ra.Y = d_Y;
-            ra.rho_prev = j > 0 ? rho2 + 2 * (j - 1) : nullptr;
-            ra.part = part;
-            launch_f2_round_fs(ra, s);
-            launch_fs_round(part, f2_blocks(ra.h), 8, ev_zc + 8 * (size_t)j, c->d_fs, rho2 + 2 * j, err, s);
-        }
-        F2FsFinalArgs fa{};
-        fa.kind = F2_RELU;
-        fa.rounds = lN;
-        fa.ints = lN <= 1;
-        fa.t[0] = lN >= 2 ? EQz : EQ;
-        fa.t[1] = Dt;
-        fa.t[2] = St;
-        fa.R = d_R;
-        fa.Y = d_Y;
-        fa.rho = lN ? rho2 + 2 * (lN - 1) : nullptr;
-        fa.fin = tr + 18;
-        launch_f2_final_fs(fa, s);
-        launch_fs_absorb_draw(c->d_fs, tr + 18, 4, nullptr, 0, err, s);
-    }
+    // rounds over x of the range instance (Bx formed from the bit words as it
+    // goes), then the ReLU zero-check; their final values absorbed
+    instance(F2_RANGE, lN, Bx, Bx, Bx, Bx, ev_rs + 8 * (size_t)lP, tr + 16);
+    if (relu) instance(F2_RELU, lN, Dt, St, Dt, St, ev_zc, tr + 18);
     RA_HIP(hipGetLastError());
     // the transcript, the witness status, the transcript status and the root
     // into the context's pinned area (nothing else is pending there)

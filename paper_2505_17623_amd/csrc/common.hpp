@@ -292,6 +292,7 @@ struct F2Tab {
 };
 enum { F2_MATMUL = 0, F2_RANGE = 1, F2_RELU = 2 };
 constexpr int kF2MaxBlocks = 512;  // blocks of a round launch (partials per round)
+constexpr int kF2Low = 11;         // variables in the low part of the suffix eq tables (f2.hpp)
 // blocks of a pass over h pairs (256 threads each, grid-stride beyond kF2MaxBlocks)
 __host__ __device__ inline int f2_blocks(uint64_t h)
 {
@@ -378,30 +379,57 @@ void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *roo
                       uint32_t *err, hipStream_t st);
 void launch_fs_absorb_draw(sha::Transcript *fs, const uint64_t *w, int nw, uint64_t *out, int ndraw, uint32_t *err,
                            hipStream_t st);
-void launch_fs_round(const uint64_t *part, int nb, int nw, uint64_t *ev, sha::Transcript *fs, uint64_t *out,
-                     uint32_t *err, hipStream_t st);
-// A round whose pass first binds the previous round's variable (fold, tables
-// of 4h entries at src to 2h at dst) and then evaluates on h pairs.
-struct F2FsRoundArgs {
-    int kind, fold, ints;      // ints: the ReLU tables D, S are read from R, Y
-    uint64_t h;
-    F2Tab src[3], dst[3];
-    const int32_t *R, *Y;
-    const uint64_t *rho_prev;  // pair
-    const uint64_t *cst;       // range: c_eq, c_w
-    uint64_t *part;            // f2_blocks(h) x 8 words
+void launch_fs_claims(const uint64_t *part, int nb, uint64_t *out8, sha::Transcript *fs, uint64_t *out, int ndraw,
+                      uint32_t *err, hipStream_t st);
+constexpr int kFsTailLog = 11;       // the last rounds, over at most 2^11 entries, run in one workgroup
+constexpr int kFsTailThreads = 512;
+// What the next launch needs to finish a round whose partials a pass left
+// (nb = 0: there is none).
+struct FsFinArgs {
+    int nb;                        // blocks of that pass
+    const uint64_t *part;          // word q of block b at q kF2MaxBlocks + b
+    const uint64_t *r;             // that round's variable of (r1, r2) (pair; not for the matrix instance)
+    const uint64_t *cst;           // range: c_eq, c_w
+    const uint64_t *K_in;          // the product of eq(r_i, rho_i) over the rounds before it (null: 1)
+    uint64_t *K_out;               // the same with that round's factor
+    uint64_t *ev;                  // out: its values
+    const sha::Transcript *fs_in;
+    sha::Transcript *fs_out;       // another copy (other workgroups may still read fs_in)
+    uint32_t *err;
 };
-void launch_f2_round_fs(const F2FsRoundArgs &a, hipStream_t st);
-struct F2FsFinalArgs {
-    int kind, rounds, ints;
-    F2Tab t[3];
-    const int32_t *R, *Y;
-    const uint64_t *rho;  // the last challenge (rounds > 0)
-    const uint64_t *ev0;  // the first round's values (matrix c0)
-    uint64_t *fin;
+struct FsPassArgs {
+    int kind;
+    uint64_t h;                // pairs; at least 2^kFsTailLog
+    F2Tab src[2], dst[2];      // 4h entries (2h without a round to finish) to 2h: B; D, S; a, b
+    const int32_t *R, *Y;      // ReLU: D, S are read from these instead (null: from src)
+    const uint64_t *bits;      // range, first pass: the bit words, with eq(sigma_p, .) (64 entries)
+    F2Tab sig;
+    int tabs;                  // bytes of a bit word that can hold set bits
+    const struct f2 *HS, *LS;  // suffix eq tables (f2.hpp)
+    uint64_t *part;
+    FsFinArgs fin;
 };
-void launch_f2_final_fs(const F2FsFinalArgs &a, hipStream_t st);
-void launch_f2_bx(const uint64_t *bits, uint64_t N, F2Tab SIG, int P, F2Tab Bx, hipStream_t st);
+void launch_fs_pass(const FsPassArgs &a, hipStream_t st);
+struct FsTailArgs {
+    int kind, v, j0;           // rounds j0 .. j0 + v - 1
+    F2Tab src[2];
+    const int32_t *R, *Y;      // as FsPassArgs
+    const uint64_t *bits;
+    F2Tab sig;
+    int tabs;
+    const struct f2 *LS;
+    const uint64_t *r;         // (r1, r2), pairs
+    const uint64_t *cst;
+    uint64_t *ev;              // round j's values at ev + 2 (D + 1) j
+    uint64_t *out;             // matrix c0, a*, b*; range b~(sigma); ReLU R~, Y~
+    FsFinArgs fin;             // fin.fs_in also without a round to finish; fin.fs_out unused
+    sha::Transcript *fs_out;   // may be fin.fs_in
+    uint32_t *err;
+};
+void launch_fs_tail(const FsTailArgs &a, hipStream_t st);
+// The eq tables of (r1, r2) = r (lN pairs): E1 (2^ln), E2 (2^lk) and the
+// suffix tables LS (2^(low + 1) entries, low = min(lN, kF2Low)) and HS (2^(lN - low + 1)).
+void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, struct f2 *HS, struct f2 *LS, hipStream_t st);
 void launch_fill0(uint64_t *p, uint64_t n, hipStream_t st);
 
 // ---- the gather link between layers (link.hip) ----

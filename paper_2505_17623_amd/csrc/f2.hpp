@@ -67,4 +67,172 @@ __device__ __forceinline__ f2 l2mul(f2 a, f2 b)
 __device__ __forceinline__ f2 l2fold(f2 lo, f2 hi, f2 r) { return l2add(lo, l2mul(r, l2sub(hi, lo))); }
 __device__ __forceinline__ f2 l2canon(f2 a) { return f2{m61::canon(a.re), m61::canon(a.im)}; }
 
+// A sum of products with its three Karatsuba parts summed apart, combined once.
+struct K3 {
+    uint64_t p0 = 0, p1 = 0, p2 = 0;
+    __device__ __forceinline__ void add(f2 a, f2 b)
+    {
+        p0 = m61::lmacc(p0, a.re, b.re);
+        p1 = m61::lmacc(p1, a.im, b.im);
+        p2 = m61::lmacc(p2, a.re + a.im, b.re + b.im);
+    }
+    __device__ __forceinline__ void add(f2 a, uint64_t b)  // b in F_p
+    {
+        p0 = m61::lmacc(p0, a.re, b);
+        p2 = m61::lmacc(p2, a.re + a.im, b);
+    }
+    __device__ __forceinline__ f2 value() const { return l2comb(p0, p1, p2); }
+};
+
+// ---------------------------------------------------------------------------
+// Sum-check rounds with a factored eq (Sec. II-D).  With x bound to z_{<j},
+// EQ(x) = eq(r, x) is K_j eq(r_j, X) w_i, w_i = eq(r_{>j}, i), so a round's
+// polynomial is K_j eq(r_j, X) s(X) with s quadratic, and no EQ table is read
+// or folded.  Over the pairs (i, i + h), lo at X = 0 and hi at X = 1:
+//   range   EQ B (c_eq (B - 1) + c_w):  P0 = sum w b0, P1 = sum w b1, Q0 = sum w b0^2,
+//           M = sum w b0 b1, Q1 = sum w b1^2;
+//           s = c_eq ((1-X)^2 Q0 + 2 X (1-X) M + X^2 Q1) + (c_w - c_eq) ((1-X) P0 + X P1)
+//   ReLU    EQ D S (D = R - Y, S = R + Y):  T0 = sum w d0 s0, T1 = sum w d1 s1,
+//           U = sum w (d0 + d1)(s0 + s1);  s = (1-X)^2 T0 + X (1-X) (U - T0 - T1) + X^2 T1
+//   matrix  a b: as ReLU without weights, and g = s.
+// A pair costs 5 (range: 15 products of F_p) or 5 (ReLU) products of F_{p^2},
+// where evaluating the summand at X = 0..3 from tables of EQ took 12 and a
+// fold more.
+// ---------------------------------------------------------------------------
+constexpr int f2_sum_words(int kind) { return kind == F2_RANGE ? 10 : 6; }
+
+template <int KIND> struct F2Sums {  // ReLU, matrix
+    K3 t0, t1, u;
+    // d weighted (or, matrix, as it is)
+    __device__ __forceinline__ void add(f2 d0, f2 d1, f2 s0, f2 s1)
+    {
+        t0.add(d0, s0);
+        t1.add(d1, s1);
+        u.add(l2add(d0, d1), l2add(s0, s1));
+    }
+    // weight w, the pair's products in F_p (integer tables)
+    __device__ __forceinline__ void add_int(f2 w, uint64_t d0, uint64_t d1, uint64_t s0, uint64_t s1)
+    {
+        t0.add(w, m61::lmul(d0, s0));
+        t1.add(w, m61::lmul(d1, s1));
+        u.add(w, m61::lmul(m61::fold(d0 + d1), m61::fold(s0 + s1)));
+    }
+    __device__ __forceinline__ void words(uint64_t (&v)[6], bool scaled, f2 w) const
+    {
+        f2 x[3] = {t0.value(), t1.value(), u.value()};
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            if (scaled) x[q] = l2mul(x[q], w);
+            v[2 * q] = x[q].re;
+            v[2 * q + 1] = x[q].im;
+        }
+    }
+};
+template <> struct F2Sums<F2_RANGE> {
+    f2 P0{0, 0}, P1{0, 0};
+    K3 q0, m, q1;
+    // u = w b
+    __device__ __forceinline__ void add(f2 u0, f2 u1, f2 b0, f2 b1)
+    {
+        P0 = l2add(P0, u0);
+        P1 = l2add(P1, u1);
+        q0.add(u0, b0);
+        m.add(u0, b1);
+        q1.add(u1, b1);
+    }
+    __device__ __forceinline__ void words(uint64_t (&v)[10], bool scaled, f2 w) const
+    {
+        f2 x[5] = {P0, P1, q0.value(), m.value(), q1.value()};
+#pragma unroll
+        for (int q = 0; q < 5; q++) {
+            if (scaled) x[q] = l2mul(x[q], w);
+            v[2 * q] = x[q].re;
+            v[2 * q + 1] = x[q].im;
+        }
+    }
+};
+
+// The round's value at X from the sums (canonical, the words of F2Sums), K =
+// K_j, r = r_j, cst = (c_eq, c_w).
+__device__ __forceinline__ f2 f2_round_value(int kind, const uint64_t *t, int X, f2 K, f2 r, const uint64_t *cst)
+{
+    const int u = 1 - X;
+    auto at = [&](int q) { return f2{t[2 * q], t[2 * q + 1]}; };
+    f2 s;
+    if (kind == F2_RANGE) {
+        const f2 lin = f2add(f2small(at(0), u), f2small(at(1), X));
+        const f2 quad = f2add(f2add(f2small(at(2), u * u), f2small(at(3), 2 * X * u)), f2small(at(4), X * X));
+        const f2 ceq = ldp(cst), cw = ldp(cst + 2);
+        s = f2add(f2mul(ceq, quad), f2mul(f2sub(cw, ceq), lin));
+    } else {
+        const f2 cross = f2sub(f2sub(at(2), at(0)), at(1));
+        s = f2add(f2add(f2small(at(0), u * u), f2small(cross, X * u)), f2small(at(1), X * X));
+        if (kind == F2_MATMUL) return s;
+    }
+    return f2mul(f2mul(K, eq1x(r, X)), s);
+}
+
+// Totals of NW words per thread over the block's first nt threads (nt a
+// multiple of 64, the others' words are zero): canonical, in tot (LDS) for
+// every thread.  red: NW nt words.  Barriers on both sides.
+template <int NW>
+__device__ __forceinline__ void f2_totals(const uint64_t (&v)[NW], uint64_t *red, uint64_t *tot, int nt)
+{
+    const int tid = threadIdx.x, seg = nt >> 4;
+    __syncthreads();
+    if (tid < nt)
+#pragma unroll
+        for (int q = 0; q < NW; q++) red[q * nt + tid] = v[q];
+    __syncthreads();
+    for (int task = tid; task < NW * 16; task += blockDim.x) {  // 16 adjacent lanes per word
+        const uint64_t *src = red + (task >> 4) * nt + (task & 15);
+        uint64_t a0 = 0, a1 = 0;
+        for (int e = 0; e < seg; e += 4) {
+            a0 = m61::fold(a0 + src[16 * e] + src[16 * e + 32]);
+            a1 = m61::fold(a1 + src[16 * e + 16] + src[16 * e + 48]);
+        }
+        uint64_t x = m61::fold(a0 + a1);
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) x = m61::fold(x + __shfl_xor(x, off, 64));
+        if ((task & 15) == 0) tot[task >> 4] = m61::canon(x);
+    }
+    __syncthreads();
+}
+
+// D = R - Y and S = R + Y of entry i as elements of F_p
+__device__ __forceinline__ void relu_ints(const int32_t *R, const int32_t *Y, uint64_t i, uint64_t &d, uint64_t &s)
+{
+    const int64_t r = R[i], y = Y[i];
+    d = m61::from_i64(r - y);
+    s = m61::from_i64(r + y);
+}
+
+// The sums of eq(sigma_p, q) over the set bits q of a byte, for each byte of a
+// bit word: tab[t][e], byte t (256 threads; tabs bytes, sig: 64 entries in
+// LDS).  A word's plane-bound value is then one lookup and add per byte.
+__device__ __forceinline__ void f2_byte_tables(const f2 *sig, int tabs, f2 (*tab)[256])
+{
+    for (int e = threadIdx.x; e < 256; e += blockDim.x)
+        for (int t = 0; t < tabs; t++) {
+            f2 s = f2of(0);
+#pragma unroll
+            for (int b = 0; b < 8; b++)
+                if ((e >> b) & 1) s = f2{s.re + sig[8 * t + b].re, s.im + sig[8 * t + b].im};  // at most 8 2^61
+            tab[t][e] = l2canon(s);
+        }
+}
+__device__ __forceinline__ f2 f2_plane_bound(uint64_t w, int tabs, const f2 (*tab)[256])
+{
+    f2 s = f2of(0);
+    for (int t = 0; t < tabs; t++) {
+        const f2 x = tab[t][(w >> (8 * t)) & 255];
+        s = f2{s.re + x.re, s.im + x.im};  // at most 8 canonical terms
+    }
+    return l2canon(s);
+}
+
+// ---- suffix eq tables of the point r = (r1, r2) ----
+// LS: the last kF2Low variables, a heap: entry 2^k + y is eq over the last k
+// variables at y.  HS: the variables before them, in the same form.
+
 }  // namespace ra

@@ -65,6 +65,53 @@ void launch_f2_eq(const uint64_t *z, int v, F2Tab out, hipStream_t st)
     hipLaunchKernelGGL(k_f2_eq, dim3(nb), dim3(kThreads), 0, st, z, v, out);
 }
 
+// The eq tables of a layer in one launch: segments E1, E2 (SoA), LS, HS
+// (f2.hpp; heaps, entry 2^k + y), each entry the product of its variables'
+// factors.
+__global__ __launch_bounds__(256) void k_f2_eqs(const uint64_t *__restrict__ r, int ln, int lk, F2Tab E1, F2Tab E2,
+                                                f2 *__restrict__ HS, f2 *__restrict__ LS)
+{
+    __shared__ f2 z[64];
+    const int lN = ln + lk, low = lN < kF2Low ? lN : kF2Low, hs = lN - low;
+    if ((int)threadIdx.x < lN) z[threadIdx.x] = ldp(r + 2 * threadIdx.x);
+    __syncthreads();
+    const uint64_t n = 1ull << ln, k = 1ull << lk, ls = 2ull << low, nh = 2ull << hs;
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const f2 *v;  // the entry: eq over v[0 .. m) at y
+    int m;
+    uint64_t y;
+    if (i < n + k) {
+        const bool one = i < n;
+        y = one ? i : i - n;
+        v = one ? z : z + ln;
+        m = one ? ln : lk;
+    } else if (i < n + k + ls + nh) {
+        const bool lo = i < n + k + ls;
+        y = lo ? i - n - k : i - n - k - ls;
+        if (!y) return;
+        m = 63 - __builtin_clzll(y);
+        y -= 1ull << m;
+        v = lo ? z + lN - m : z + hs - m;
+    } else {
+        return;
+    }
+    f2 e = f2of(1);
+    for (int j = 0; j < m; j++) e = l2mul(e, eq1b(v[j], (int)((y >> (m - 1 - j)) & 1)));
+    e = l2canon(e);
+    if (i < n) stt(E1, i, e);
+    else if (i < n + k) stt(E2, y, e);
+    else if (i < n + k + ls) LS[i - n - k] = e;
+    else HS[i - n - k - ls] = e;
+}
+
+void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st)
+{
+    const int lN = ln + lk, low = lN < kF2Low ? lN : kF2Low;
+    const uint64_t tot = (1ull << ln) + (1ull << lk) + (2ull << low) + (2ull << (lN - low));
+    hipLaunchKernelGGL(k_f2_eqs, dim3((unsigned)((tot + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, r, ln, lk, E1,
+                       E2, HS, LS);
+}
+
 // EQ(x) = E1[x >> lk] E2[x mod 2^lk] for x < N (the eq table of (r1, r2)).
 __global__ __launch_bounds__(256) void k_f2_outer(F2Tab E1, F2Tab E2, int lk, uint64_t N, F2Tab out)
 {

@@ -3,19 +3,10 @@
 // and draw, one workgroup: the hash chain is sequential), and the sum-check
 // rounds reordered for challenges that exist only after a round's values are
 // hashed.
-//
-// With the challenges fixed in advance (fp2.hip) a round evaluates its
-// polynomial and folds its tables in the same pass.  Here the fold of round
-// j - 1 has to wait for rho_{j-1}, which is the hash of round j - 1's values,
-// so the pass of round j first folds (tables of 4h entries to 2h, with
-// rho_{j-1}) and then evaluates round j on the folded pairs; a final fold
-// after the last challenge gives the instance's final values.  A one-workgroup
-// launch between the passes sums the round's partials, absorbs the values and
-// draws the challenge.
 #include <algorithm>
 
 #include "common.hpp"
-#include "m61.hpp"
+#include "f2.hpp"
 #include "fs_device.hpp"
 #include "sha256.hpp"
 
@@ -183,27 +174,6 @@ __global__ __launch_bounds__(kFsThreads) void k_fs_absorb_draw(sha::Transcript *
     fs_push(fs, f);
 }
 
-// A round's values from its blocks' partials (eight words per block, the
-// first nw used), written to ev; then absorbed and one challenge drawn.
-__global__ __launch_bounds__(256) void k_fs_round(const uint64_t *__restrict__ part, int nb, int nw,
-                                                  uint64_t *__restrict__ ev, sha::Transcript *fs, uint64_t *out,
-                                                  uint32_t *err)
-{
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    __shared__ FsLds f;
-    const int tid = threadIdx.x;
-    fs_pull(f, fs);
-    uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int b = tid; b < nb; b += blockDim.x)
-#pragma unroll
-        for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], part[8 * (size_t)b + q]);
-    const uint64_t *tot = m61::block_sum_lds<8>(v, red);
-    if (tid < nw) ev[tid] = tot[tid];
-    if (!fs_absorb(f, (const uint32_t *)tot, 2 * nw) && tid == 0) *err = 1;
-    fs_draws(f, out, 1);
-    fs_push(fs, f);
-}
-
 void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *root, uint64_t *out, int ndraw,
                       uint32_t *err, hipStream_t st)
 {
@@ -216,189 +186,304 @@ void launch_fs_absorb_draw(sha::Transcript *fs, const uint64_t *w, int nw, uint6
     hipLaunchKernelGGL(k_fs_absorb_draw, dim3(1), dim3(kFsThreads), 0, st, fs, w, nw, out, ndraw, err);
 }
 
-void launch_fs_round(const uint64_t *part, int nb, int nw, uint64_t *ev, sha::Transcript *fs, uint64_t *out,
-                     uint32_t *err, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_fs_round, dim3(1), dim3(256), 0, st, part, nb, nw, ev, fs, out, err);
-}
-
-// ---------------------------------------------------------------------------
-// Rounds with the fold of the previous round first.
-// ---------------------------------------------------------------------------
-struct g2 {
-    uint64_t re, im;
-};
-__device__ __forceinline__ g2 gof(uint64_t a) { return g2{a, 0}; }
-__device__ __forceinline__ g2 gadd(g2 a, g2 b) { return g2{m61::add(a.re, b.re), m61::add(a.im, b.im)}; }
-__device__ __forceinline__ g2 gsub(g2 a, g2 b) { return g2{m61::sub(a.re, b.re), m61::sub(a.im, b.im)}; }
-__device__ __forceinline__ g2 gmul(g2 a, g2 b)
-{
-    const uint64_t p0 = m61::mul(a.re, b.re), p1 = m61::mul(a.im, b.im);
-    const uint64_t p2 = m61::mul(m61::add(a.re, a.im), m61::add(b.re, b.im));
-    return g2{m61::sub(p0, p1), m61::sub(m61::sub(p2, p0), p1)};
-}
-__device__ __forceinline__ g2 gld(const F2Tab &t, uint64_t i) { return g2{t.re[i], t.im[i]}; }
-__device__ __forceinline__ void gst(const F2Tab &t, uint64_t i, g2 v)
-{
-    t.re[i] = v.re;
-    t.im[i] = v.im;
-}
-__device__ __forceinline__ g2 gfold(g2 lo, g2 hi, g2 r) { return gadd(lo, gmul(r, gsub(hi, lo))); }
-
-// value q of the ReLU instance read from the int32 tables: D = R - Y, S = R + Y
-__device__ __forceinline__ g2 relu_int(int q, const int32_t *R, const int32_t *Y, uint64_t i)
-{
-    const int64_t r = R[i], y = Y[i];
-    return gof(m61::from_i64(q == 1 ? r - y : r + y));
-}
-
-template <int KIND>
-__global__ __launch_bounds__(256) void k_f2_round_fs(F2FsRoundArgs a)
+// The claims R~, Rm~, Y~, Z~ from their partials (eight words per block),
+// written to `out` and absorbed; ndraw challenges drawn.
+__global__ __launch_bounds__(256) void k_fs_claims(const uint64_t *__restrict__ part, int nb, uint64_t *out8,
+                                                   sha::Transcript *fs, uint64_t *out, int ndraw, uint32_t *err)
 {
     __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    constexpr int NT = KIND == F2_RELU ? 3 : 2;
-    g2 rho{0, 0}, ceq{0, 0}, cw{0, 0};
-    if (a.fold) rho = g2{a.rho_prev[0], a.rho_prev[1]};
-    if (KIND == F2_RANGE) {
-        ceq = g2{a.cst[0], a.cst[1]};
-        cw = g2{a.cst[2], a.cst[3]};
-    }
-    g2 acc[4] = {gof(0), gof(0), gof(0), gof(0)};
-    const uint64_t h = a.h;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < h; i += (uint64_t)gridDim.x * blockDim.x) {
-        g2 lo[3], hi[3];
+    __shared__ FsLds f;
+    const int tid = threadIdx.x;
+    fs_pull(f, fs);
+    uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int b = tid; b < nb; b += blockDim.x)
 #pragma unroll
-        for (int q = 0; q < NT; q++) {
-            const bool from_int = KIND == F2_RELU && q > 0 && a.ints;
-            if (a.fold) {  // tables of 4h entries, bound at rho_{j-1}
-                const g2 x0 = from_int ? relu_int(q, a.R, a.Y, i) : gld(a.src[q], i);
-                const g2 x1 = from_int ? relu_int(q, a.R, a.Y, i + h) : gld(a.src[q], i + h);
-                const g2 x2 = from_int ? relu_int(q, a.R, a.Y, i + 2 * h) : gld(a.src[q], i + 2 * h);
-                const g2 x3 = from_int ? relu_int(q, a.R, a.Y, i + 3 * h) : gld(a.src[q], i + 3 * h);
-                lo[q] = gfold(x0, x2, rho);
-                hi[q] = gfold(x1, x3, rho);
-                gst(a.dst[q], i, lo[q]);
-                gst(a.dst[q], i + h, hi[q]);
-            } else {
-                lo[q] = from_int ? relu_int(q, a.R, a.Y, i) : gld(a.src[q], i);
-                hi[q] = from_int ? relu_int(q, a.R, a.Y, i + h) : gld(a.src[q], i + h);
-            }
-        }
-        g2 v[3], d[3];
-#pragma unroll
-        for (int q = 0; q < NT; q++) {
-            v[q] = lo[q];
-            d[q] = gsub(hi[q], lo[q]);
-        }
-#pragma unroll
-        for (int X = 0; X < 4; X++) {
-            if (X > 0)
-#pragma unroll
-                for (int q = 0; q < NT; q++) v[q] = gadd(v[q], d[q]);
-            g2 f;
-            if (KIND == F2_MATMUL) {
-                if (X == 3) break;
-                f = gmul(v[0], v[1]);
-            } else if (KIND == F2_RANGE) {
-                f = gmul(gmul(v[0], v[1]), gadd(gmul(ceq, gsub(v[1], gof(1))), cw));
-            } else {
-                f = gmul(gmul(v[0], v[1]), v[2]);
-            }
-            acc[X] = gadd(acc[X], f);
-        }
-    }
-    uint64_t w[8];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        w[2 * q] = acc[q].re;
-        w[2 * q + 1] = acc[q].im;
-    }
-    m61::block_sum<8>(w, red);
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int q = 0; q < 8; q++) a.part[8 * (size_t)blockIdx.x + q] = w[q];
+        for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], part[8 * (size_t)b + q]);
+    const uint64_t *tot = m61::block_sum_lds<8>(v, red);
+    if (tid < 8) out8[tid] = tot[tid];
+    if (!fs_absorb(f, (const uint32_t *)tot, 16) && tid == 0) *err = 1;
+    fs_draws(f, out, ndraw);
+    __syncthreads();
+    fs_push(fs, f);
 }
 
-void launch_f2_round_fs(const F2FsRoundArgs &a, hipStream_t st)
+void launch_fs_claims(const uint64_t *part, int nb, uint64_t *out8, sha::Transcript *fs, uint64_t *out, int ndraw,
+                      uint32_t *err, hipStream_t st)
 {
-    const dim3 grid(f2_blocks(a.h));
-    switch (a.kind) {
-    case F2_MATMUL: hipLaunchKernelGGL(k_f2_round_fs<F2_MATMUL>, grid, dim3(kThreads), 0, st, a); break;
-    case F2_RANGE: hipLaunchKernelGGL(k_f2_round_fs<F2_RANGE>, grid, dim3(kThreads), 0, st, a); break;
-    default: hipLaunchKernelGGL(k_f2_round_fs<F2_RELU>, grid, dim3(kThreads), 0, st, a); break;
-    }
+    hipLaunchKernelGGL(k_fs_claims, dim3(1), dim3(kThreads), 0, st, part, nb, out8, fs, out, ndraw, err);
 }
 
-// The instance's final values after its last challenge (one thread): tables
-// of two entries bound at rho (or, with no rounds, their single entry).
-//   F2_MATMUL  fin: c0 (g_1(0) + g_1(1), or a b with no rounds), a*, b*
-//   F2_RANGE   fin: b~(sigma)
-//   F2_RELU    fin: R~ = (D + S) / 2, Y~ = (S - D) / 2; ints: D, S from R, Y
-__global__ void k_f2_final_fs(F2FsFinalArgs a)
+// ---------------------------------------------------------------------------
+// Rounds whose challenges exist only after their values are hashed.  Pass j
+// (one launch per round while the tables hold more than 2^kFsTailLog
+// entries) first finishes round j - 1: every workgroup sums that round's
+// partials, forms its values, absorbs them and draws rho_{j-1}, so no launch
+// of one workgroup sits between two passes (it took 7.6 us and the gaps of
+// two launches per round); workgroup 0 writes the values and the transcript,
+// to the other of two copies, since the rest still read the first.  Then it
+// folds with rho_{j-1} (4h entries to 2h) and sums round j (f2.hpp).
+// The last rounds run in one workgroup over LDS, hashing as they go.
+// ---------------------------------------------------------------------------
+// Round j - 1 finished in every workgroup: its challenge; f holds the
+// transcript after it.  K: K_j in LDS.
+struct FsFinLds {
+    FsLds f;
+    f2 g[4], K;
+    uint64_t tot[10];
+};
+
+// The values of a round from its sums in l.tot (after a barrier): to l.g, and
+// by the writer to ev; absorbed, the challenge drawn; K advanced.
+template <int KIND>
+__device__ __forceinline__ f2 fs_finish_round(FsFinLds &l, f2 r, const uint64_t *cst, uint64_t *ev, bool writer,
+                                              uint32_t *err)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    constexpr uint64_t inv2 = 1ull << 60;  // 2 2^60 = 2^61 = 1 mod p
-    const int NT = a.kind == F2_RELU ? 3 : 2;
-    g2 f[3];
-    for (int q = 0; q < NT; q++) {
-        const bool from_int = a.kind == F2_RELU && q > 0 && a.ints;
-        const g2 x0 = from_int ? relu_int(q, a.R, a.Y, 0) : gld(a.t[q], 0);
-        if (a.rounds > 0) {
-            const g2 x1 = from_int ? relu_int(q, a.R, a.Y, 1) : gld(a.t[q], 1);
-            f[q] = gfold(x0, x1, g2{a.rho[0], a.rho[1]});
+    constexpr int D1 = KIND == F2_MATMUL ? 3 : 4;
+    const int tid = threadIdx.x;
+    if (tid < D1) {
+        const f2 g = f2_round_value(KIND, l.tot, tid, l.K, r, cst);
+        l.g[tid] = g;
+        if (writer) stp(ev + 2 * tid, g);
+    }
+    if (!fs_absorb(l.f, (const uint32_t *)l.g, 4 * D1) && tid == 0 && writer) *err = 1;
+    fs_draw(l.f);
+    return f2{l.f.out[0], l.f.out[1]};
+}
+
+// As above, with the sums taken from the blocks' partials first and the
+// transcript pulled; K_j-1 read from K_in (null: 1).
+template <int KIND>
+__device__ __forceinline__ f2 fs_finish_prev(FsFinLds &l, const FsFinArgs &a, bool writer)
+{
+    constexpr int NW = f2_sum_words(KIND);
+    const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    fs_pull(l.f, a.fs_in);
+    for (int q = tid >> 6; q < NW; q += nw) {
+        uint64_t v = 0;
+        for (int b = lane; b < a.nb; b += 64) v = m61::fold(v + a.part[(size_t)q * kF2MaxBlocks + b]);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) v = m61::fold(v + __shfl_xor(v, off, 64));
+        if (lane == 0) l.tot[q] = m61::canon(v);
+    }
+    const f2 r = KIND == F2_MATMUL ? f2of(0) : ldp(a.r);
+    if (tid == 0) l.K = KIND != F2_MATMUL && a.K_in ? ldp(a.K_in) : f2of(1);
+    __syncthreads();
+    const f2 rho = fs_finish_round<KIND>(l, r, a.cst, a.ev, writer, a.err);
+    if (KIND != F2_MATMUL) {
+        if (tid == 64) {
+            const f2 K = f2mul(l.K, eq1z(r, rho));
+            l.K = K;
+            if (writer && a.K_out) stp(a.K_out, K);
+        }
+        __syncthreads();
+    }
+    return rho;
+}
+
+// Sources of a pass: field tables, the integer tables R, Y (ReLU), the bit
+// words (range: Bx formed from them and written).
+enum { FS_FIELD = 0, FS_INTS = 1, FS_BITS = 2 };
+
+// lo + r (hi - lo) for lo, hi in F_p
+__device__ __forceinline__ f2 fold_real(uint64_t lo, uint64_t hi, f2 r)
+{
+    const uint64_t d = m61::lsub(hi, lo);
+    return f2{m61::lmacc(lo, r.re, d), m61::lmul(r.im, d)};
+}
+
+template <int KIND, int SRC, bool FOLD>
+__global__ __launch_bounds__(256) void k_fs_pass(FsPassArgs a)
+{
+    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2;
+    __shared__ FsFinLds l;
+    __shared__ uint64_t red[NW * 256];
+    __shared__ f2 tab[SRC == FS_BITS ? 8 : 1][256], sig[SRC == FS_BITS ? 64 : 1];
+    const int tid = threadIdx.x;
+    f2 rho{0, 0};
+    if (FOLD) {
+        rho = fs_finish_prev<KIND>(l, a.fin, blockIdx.x == 0);
+        if (blockIdx.x == 0) fs_push(a.fin.fs_out, l.f);
+    }
+    if (SRC == FS_BITS) {
+        if (tid < 64) sig[tid] = ldt(a.sig, tid);
+        __syncthreads();
+        f2_byte_tables(sig, a.tabs, tab);
+        __syncthreads();
+    }
+    F2Sums<KIND> acc;
+    const uint64_t h = a.h, first = (uint64_t)blockIdx.x * blockDim.x + tid;
+    for (uint64_t i = first; i < h; i += (uint64_t)gridDim.x * blockDim.x) {
+        f2 lo[2], hi[2];
+        // weights: the high variables here (the same for the whole workgroup), the low ones at the end
+        f2 w = f2of(1);
+        if (KIND != F2_MATMUL) w = a.HS[(h >> kF2Low) + (i >> kF2Low)];
+        if (SRC == FS_INTS) {
+            uint64_t d[4], s[4];
+#pragma unroll
+            for (int q = 0; q < (FOLD ? 4 : 2); q++) relu_ints(a.R, a.Y, i + q * h, d[q], s[q]);
+            if (!FOLD) {
+                if constexpr (KIND == F2_RELU) acc.add_int(w, d[0], d[1], s[0], s[1]);
+                continue;
+            }
+            lo[0] = fold_real(d[0], d[2], rho);
+            hi[0] = fold_real(d[1], d[3], rho);
+            lo[1] = fold_real(s[0], s[2], rho);
+            hi[1] = fold_real(s[1], s[3], rho);
+        } else if (SRC == FS_BITS) {
+            lo[0] = f2_plane_bound(a.bits[i], a.tabs, tab);
+            hi[0] = f2_plane_bound(a.bits[i + h], a.tabs, tab);
         } else {
-            f[q] = x0;
+#pragma unroll
+            for (int q = 0; q < NT; q++) {
+                lo[q] = ldt(a.src[q], i);
+                hi[q] = ldt(a.src[q], i + h);
+                if (FOLD) {
+                    lo[q] = l2fold(lo[q], ldt(a.src[q], i + 2 * h), rho);
+                    hi[q] = l2fold(hi[q], ldt(a.src[q], i + 3 * h), rho);
+                }
+            }
         }
+        if (FOLD || SRC == FS_BITS)
+#pragma unroll
+            for (int q = 0; q < NT; q++) {
+                stt(a.dst[q], i, lo[q]);
+                stt(a.dst[q], i + h, hi[q]);
+            }
+        if constexpr (KIND == F2_MATMUL) acc.add(lo[0], hi[0], lo[1], hi[1]);
+        else if constexpr (KIND == F2_RANGE) acc.add(l2mul(w, lo[0]), l2mul(w, hi[0]), lo[0], hi[0]);
+        else acc.add(l2mul(w, lo[0]), l2mul(w, hi[0]), lo[1], hi[1]);
     }
-    auto put = [&](uint64_t *p, g2 v) {
-        p[0] = v.re;
-        p[1] = v.im;
-    };
+    uint64_t v[NW];
+    acc.words(v, KIND != F2_MATMUL,
+              KIND != F2_MATMUL ? a.LS[(1u << kF2Low) + (uint32_t)(first & ((1u << kF2Low) - 1))] : f2of(1));
+    f2_totals<NW>(v, red, l.tot, blockDim.x);
+    if (tid < NW) a.part[(size_t)tid * kF2MaxBlocks + blockIdx.x] = l.tot[tid];
+}
+
+void launch_fs_pass(const FsPassArgs &a, hipStream_t st)
+{
+    const dim3 grid(f2_blocks(a.h)), blk(kThreads);
+    const bool fold = a.fin.nb > 0;
     if (a.kind == F2_MATMUL) {
-        put(a.fin, a.rounds > 0 ? gadd(g2{a.ev0[0], a.ev0[1]}, g2{a.ev0[2], a.ev0[3]}) : gmul(f[0], f[1]));
-        put(a.fin + 2, f[0]);
-        put(a.fin + 4, f[1]);
+        if (fold) hipLaunchKernelGGL((k_fs_pass<F2_MATMUL, FS_FIELD, true>), grid, blk, 0, st, a);
+        else hipLaunchKernelGGL((k_fs_pass<F2_MATMUL, FS_FIELD, false>), grid, blk, 0, st, a);
     } else if (a.kind == F2_RANGE) {
-        put(a.fin, f[1]);
+        if (fold) hipLaunchKernelGGL((k_fs_pass<F2_RANGE, FS_FIELD, true>), grid, blk, 0, st, a);
+        else hipLaunchKernelGGL((k_fs_pass<F2_RANGE, FS_BITS, false>), grid, blk, 0, st, a);
+    } else if (!a.R) {
+        hipLaunchKernelGGL((k_fs_pass<F2_RELU, FS_FIELD, true>), grid, blk, 0, st, a);
+    } else if (fold) {
+        hipLaunchKernelGGL((k_fs_pass<F2_RELU, FS_INTS, true>), grid, blk, 0, st, a);
     } else {
-        const g2 D = f[1], S = f[2];
-        put(a.fin, g2{m61::mul(m61::add(D.re, S.re), inv2), m61::mul(m61::add(D.im, S.im), inv2)});
-        put(a.fin + 2, g2{m61::mul(m61::sub(S.re, D.re), inv2), m61::mul(m61::sub(S.im, D.im), inv2)});
+        hipLaunchKernelGGL((k_fs_pass<F2_RELU, FS_INTS, false>), grid, blk, 0, st, a);
     }
 }
 
-void launch_f2_final_fs(const F2FsFinalArgs &a, hipStream_t st)
+// The last v rounds (tables of 2^v <= 2^kFsTailLog entries once the previous
+// pass's round is finished and folded), the instance's final values, and
+// their absorption.
+template <int KIND>
+__global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
 {
-    hipLaunchKernelGGL(k_f2_final_fs, dim3(1), dim3(64), 0, st, a);
-}
-
-// Bx(x) = sum over the set bits q of word x of eq(sigma_p, q): the bit table
-// bound at the plane challenges (both parts), eq(sigma_p, .) staged in LDS.
-__global__ __launch_bounds__(256) void k_f2_bx(const uint64_t *__restrict__ bits, uint64_t N, F2Tab SIG, int P,
-                                               F2Tab Bx)
-{
-    __shared__ uint64_t sre[64], sim[64];
-    if (threadIdx.x < 64) {
-        sre[threadIdx.x] = (int)threadIdx.x < P ? SIG.re[threadIdx.x] : 0;
-        sim[threadIdx.x] = (int)threadIdx.x < P ? SIG.im[threadIdx.x] : 0;
+    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2, S = 1 << kFsTailLog;
+    constexpr int D1 = KIND == F2_MATMUL ? 3 : 4;
+    // red: also the byte tables while Bx is formed
+    constexpr int RED = NW * kFsTailThreads > 8 * 512 ? NW * kFsTailThreads : 8 * 512;
+    __shared__ f2 T[NT][S], LS[KIND == F2_MATMUL ? 1 : S];
+    __shared__ uint64_t red[RED];
+    __shared__ FsFinLds l;
+    __shared__ f2 sig[KIND == F2_RANGE ? 64 : 1], fin[3];
+    const int tid = threadIdx.x, n0 = 1 << a.v;
+    f2 rho{0, 0};
+    if (KIND != F2_MATMUL)
+        for (int i = tid; i < n0; i += blockDim.x) LS[i] = a.LS[i];  // entries 2^k + y, k < v
+    const bool prev = a.fin.nb > 0;
+    if (prev) {
+        rho = fs_finish_prev<KIND>(l, a.fin, true);
+    } else {
+        fs_pull(l.f, a.fin.fs_in);
+        if (tid == 0) l.K = f2of(1);
+    }
+    if (KIND == F2_RANGE && !prev) {
+        f2(*tab)[256] = (f2(*)[256])red;
+        if (tid < 64) sig[tid] = ldt(a.sig, tid);
+        __syncthreads();
+        f2_byte_tables(sig, a.tabs, tab);
+        __syncthreads();
+        for (int i = tid; i < n0; i += blockDim.x) T[0][i] = f2_plane_bound(a.bits[i], a.tabs, tab);
+    } else if (KIND == F2_RELU && a.R) {
+        for (int i = tid; i < n0; i += blockDim.x) {
+            uint64_t d0, s0, d1, s1;
+            relu_ints(a.R, a.Y, i, d0, s0);
+            if (prev) {
+                relu_ints(a.R, a.Y, i + n0, d1, s1);
+                T[0][i] = fold_real(d0, d1, rho);
+                T[NT - 1][i] = fold_real(s0, s1, rho);
+            } else {
+                T[0][i] = f2of(d0);
+                T[NT - 1][i] = f2of(s0);
+            }
+        }
+    } else {
+        for (int i = tid; i < n0; i += blockDim.x)
+#pragma unroll
+            for (int q = 0; q < NT; q++) {
+                const f2 x = ldt(a.src[q], i);
+                T[q][i] = prev ? l2fold(x, ldt(a.src[q], i + n0), rho) : x;
+            }
     }
     __syncthreads();
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N; x += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t w = bits[x], re = 0, im = 0;
-        while (w) {
-            const int q = __builtin_ctzll(w);
-            w &= w - 1;
-            re = m61::add(re, sre[q]);
-            im = m61::add(im, sim[q]);
+    for (int c = 0; c < a.v; c++) {
+        const int h = n0 >> (c + 1);
+        F2Sums<KIND> acc;
+        for (int i = tid; i < h; i += blockDim.x) {
+            f2 lo[2], hi[2];
+#pragma unroll
+            for (int q = 0; q < NT; q++) {
+                lo[q] = T[q][i];
+                hi[q] = T[q][i + h];
+            }
+            if constexpr (KIND == F2_MATMUL) {
+                acc.add(lo[0], hi[0], lo[1], hi[1]);
+            } else {
+                const f2 w = LS[h + i], u0 = l2mul(w, lo[0]), u1 = l2mul(w, hi[0]);
+                if constexpr (KIND == F2_RANGE) acc.add(u0, u1, lo[0], hi[0]);
+                else acc.add(u0, u1, lo[1], hi[1]);
+            }
         }
-        Bx.re[x] = re;
-        Bx.im[x] = im;
+        uint64_t v[NW];
+        acc.words(v, false, f2of(1));
+        f2_totals<NW>(v, red, l.tot, h < 64 ? 64 : (h < kFsTailThreads ? h : kFsTailThreads));
+        const f2 r = KIND == F2_MATMUL ? f2of(0) : ldp(a.r + 2 * (a.j0 + c));
+        rho = fs_finish_round<KIND>(l, r, a.cst, a.ev + 2 * D1 * (a.j0 + c), true, a.err);
+        if (KIND != F2_MATMUL && tid == blockDim.x - 1) l.K = f2mul(l.K, eq1z(r, rho));
+        for (int i = tid; i < h; i += blockDim.x)
+#pragma unroll
+            for (int q = 0; q < NT; q++) T[q][i] = l2fold(T[q][i], T[q][i + h], rho);
+        __syncthreads();
     }
+    constexpr uint64_t inv2 = 1ull << 60;  // 2 2^60 = 2^61 = 1 mod p
+    constexpr int nfin = KIND == F2_MATMUL ? 2 : (KIND == F2_RANGE ? 1 : 2);
+    if (tid == 0) {  // a*, b*; b~(sigma); R~ = (D + S) / 2, Y~ = (S - D) / 2
+        const f2 x = l2canon(T[0][0]), y = l2canon(T[NT - 1][0]);
+        fin[0] = KIND == F2_RELU ? f2scale(f2add(x, y), inv2) : x;
+        fin[1] = KIND == F2_RELU ? f2scale(f2sub(y, x), inv2) : y;
+        if (KIND == F2_MATMUL) {  // c0 = g_1(0) + g_1(1), or a b with no rounds
+            const bool any = a.j0 + a.v > 0;
+            stp(a.out, any ? f2add(ldp(a.ev), ldp(a.ev + 2)) : f2mul(x, y));
+        }
+        for (int q = 0; q < nfin; q++) stp(a.out + (KIND == F2_MATMUL ? 2 : 0) + 2 * q, fin[q]);
+    }
+    if (!fs_absorb(l.f, (const uint32_t *)fin, 4 * nfin) && tid == 0) *a.err = 1;
+    fs_push(a.fs_out, l.f);
 }
 
-void launch_f2_bx(const uint64_t *bits, uint64_t N, F2Tab SIG, int P, F2Tab Bx, hipStream_t st)
+void launch_fs_tail(const FsTailArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f2_bx, dim3(f2_blocks(N)), dim3(kThreads), 0, st, bits, N, SIG, P, Bx);
+    const dim3 blk(kFsTailThreads);
+    if (a.kind == F2_MATMUL) hipLaunchKernelGGL(k_fs_tail<F2_MATMUL>, dim3(1), blk, 0, st, a);
+    else if (a.kind == F2_RANGE) hipLaunchKernelGGL(k_fs_tail<F2_RANGE>, dim3(1), blk, 0, st, a);
+    else hipLaunchKernelGGL(k_fs_tail<F2_RELU>, dim3(1), blk, 0, st, a);
 }
 
 __global__ __launch_bounds__(256) void k_fill0(uint64_t *__restrict__ p, uint64_t n)

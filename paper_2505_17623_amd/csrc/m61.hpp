@@ -102,11 +102,11 @@ __device__ __forceinline__ uint64_t opaque(uint64_t x)
 }
 __host__ __forceinline__ uint64_t opaque(uint64_t x) { return x; }
 
-// Product of two loose values, folded.  With a1, b1 <= 2^30:
+// Product of two loose values, not yet folded.  With a1, b1 <= 2^30:
 //   a b = hi 2^64 + mid 2^32 + lo,  hi = a1 b1 <= 2^60, mid < 2^63, lo < 2^64;
 //   2^64 = 8, mid 2^32 = (mid >> 29) + (mid mod 2^29) 2^32, lo = (lo >> 61) + (lo mod 2^61),
 // and the five terms sum below 2^63 + 2^62 + 2^34 < 2^64.
-__host__ __device__ __forceinline__ uint64_t lmul(uint64_t a, uint64_t b)
+__host__ __device__ __forceinline__ uint64_t lmul_wide(uint64_t a, uint64_t b)
 {
     const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
     const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
@@ -118,9 +118,11 @@ __host__ __device__ __forceinline__ uint64_t lmul(uint64_t a, uint64_t b)
     uint64_t t = (uint64_t)(lh >> 29) | ((uint64_t)((uint32_t)mid & 0x1FFFFFFFu) << 32);
     hi = opaque(hi);  // hi 8 stays one multiply and a shifted add
     t = opaque(t);    // t stays one word
-    const uint64_t s = (hi << 3) + (mid >> 29) + ((uint64_t)(uint32_t)lo | ((uint64_t)(lh & 0x1FFFFFFFu) << 32)) + t;
-    return fold(s);
+    return (hi << 3) + (mid >> 29) + ((uint64_t)(uint32_t)lo | ((uint64_t)(lh & 0x1FFFFFFFu) << 32)) + t;
 }
+// The product folded; acc + the product, folded (acc folded: the sum stays below 2^64).
+__host__ __device__ __forceinline__ uint64_t lmul(uint64_t a, uint64_t b) { return fold(lmul_wide(a, b)); }
+__host__ __device__ __forceinline__ uint64_t lmacc(uint64_t acc, uint64_t a, uint64_t b) { return fold(acc + lmul_wide(a, b)); }
 
 // a - b for loose a, b, folded: a + 4p - b lies in (0, 2^64).
 __host__ __device__ __forceinline__ uint64_t lsub(uint64_t a, uint64_t b) { return fold(a + (4 * P - b)); }

@@ -85,6 +85,23 @@ def test_fs_layer_shapes(ra, n, m, k, s, relu, mode):
     compare(ra, g, o, f"{n}x{m}x{k}")
 
 
+# the rounds' launches: every round in one workgroup (2^11 entries), one pass
+# before it, the passes that read a pass's fold (2^13 and more), and the
+# matrix instance's (m = 4096, 8192, 16384); a table one entry long beside it
+@pytest.mark.parametrize("n,m,k,relu", [(32, 4, 64, True), (64, 4, 64, True), (64, 2, 128, True), (128, 2, 128, True),
+                                        (1, 2, 4096, False), (2, 4096, 4, True), (1, 8192, 2, True),
+                                        (1, 16384, 1, True)])
+def test_fs_round_passes(ra, n, m, k, relu):
+    rng = np.random.default_rng(n + 3 * m + 5 * k)
+    A = rng.integers(-300, 300, size=(n, m)).astype(np.int16)
+    B = rng.integers(-300, 300, size=(m, k)).astype(np.int16)
+    domain, pub = hashlib.sha256(f"passes {n} {m} {k}".encode()).digest(), bytes(range(32))
+    o = orc.prove_layer_fs(A, B, 7, relu, 0, orc.fs_init(domain), pub)
+    g = ra.prove_layer_fp2(ra.Context(fs_domain=domain), torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(),
+                           7, relu, 0, pub=pub)
+    compare(ra, g, o, f"{n}x{m}x{k}")
+
+
 def test_fs_given_t_and_int32(ra):
     rng = np.random.default_rng(3)
     A = rng.integers(-(2 ** 16), 2 ** 16, size=(32, 64)).astype(np.int32)
