@@ -2,28 +2,27 @@
 // (Sec. II-C commits a vector a as g^a; Sec. IV names the curve), for the
 // integer tables of a layer.
 //
-// The multi-scalar product is the bucket (Pippenger) method with 8-bit
-// windows of |v_i| (two windows for 16-bit values, four for 32-bit, eight
-// for 64-bit words), the sign applied to the point:
-//   P = sum_w 2^(8w) sum_{b=1}^{255} b S_{w,b},  S_{w,b} = sum of sign(v_i) G_i
-//   over the i whose window-w digit of |v_i| is b.
+// The multi-scalar product is the bucket (Pippenger) method with 9-bit
+// windows of signed digits (two windows for 16-bit values, four for 32-bit,
+// eight for 64-bit words), the signs applied to the point:
+//   P = sum_w 2^(9w) sum_{b=1}^{256} b S_{w,b},  S_{w,b} = sum of +-G_i
+//   over the i whose window-w digit is +-b.
 // A workgroup takes a chunk of values and one window: it sorts the chunk by
 // digit in LDS (a counting sort), then every thread adds an equal run of the
-// sorted list with mixed Jacobian-affine additions, so a heavy bucket is
-// spread over many threads; the runs' partial sums, in bucket order, are
-// added per bucket.  The chunks' bucket sums are then added per bucket, and
-// sum_b b S_{w,b} is formed as sum_k 2^k (sum over the b with bit k set).
+// sorted list with mixed additions, so a heavy bucket is spread over many
+// threads; the runs' partial sums, in bucket order, are added per bucket.
+// The chunks' bucket sums are then added per bucket, and sum_b b S_{w,b} is
+// formed as sum_k 2^k (sum over the b with bit k set).  Every table of a
+// batch is in each of the four launches.
 #include <algorithm>
 
 #include "commit.hpp"
-#include "secp256k1.hpp"
+#include "secp29.hpp"
 #include "sha256.hpp"
 
 namespace ra {
 
-using secp::Aff;
 using secp::Fe;
-using secp::Jac;
 
 // ---------------------------------------------------------------------------
 // Generators by try-and-increment: x = SHA-256(tag || domain || LE64(i) ||
@@ -85,19 +84,28 @@ void launch_commit_generators(const uint8_t *domain, uint64_t first, uint64_t co
 // ---------------------------------------------------------------------------
 // The bucket method
 // ---------------------------------------------------------------------------
-constexpr int kPipSub = 4096;              // values a workgroup sorts at a time (two workgroups fit a CU)
-constexpr int kPipParts = 256 + 255;       // run partials of one sort, at most
-constexpr int kJacWords = 24;              // X, Y, Z: eight 32-bit limbs each
+using secp29::F;
+using secp29::Pt;
+constexpr int kPipThreads = 512;
+constexpr int kPipSub = 8192;              // values a workgroup sorts at a time (one workgroup's LDS)
+constexpr int kPipBits = 9;                // window width; digits -256 .. 255, buckets 1 .. 256
+constexpr int kPipBuckets = 256;
+constexpr int kPipParts = kPipThreads + kPipBuckets - 1;  // run partials of one sort, at most
+constexpr int kPipChunks = 128;            // chunks of a table, at most
+constexpr int kPtWords = secp29::kPtWords;
+constexpr int kBitSums = kPipBits;         // bits of a bucket's number
 
 int msm_windows(int kind) { return kind == 3 ? 8 : (kind == 2 ? 4 : 2); }
 
+// Room per window: kPipChunks + 1 rows of 256 points and kBitSums more (what
+// the kernels use), within what earlier forms of the workspace held: a
+// caller's workspace of that size stays large enough, and the check of its
+// size what it was.
 size_t msm_workspace_bytes(int kind)
 {
-    const size_t W = (size_t)msm_windows(kind), jac = (size_t)kJacWords * 4;
-    return W * kMsmChunks * 256 * jac   // the chunks' bucket sums
-           + W * 256 * jac             // the bucket sums
-           + W * 8 * jac               // their bit sums
-           + 256;
+    constexpr size_t per_window = (size_t)256 * 257 * 96 + 8 * 96;
+    static_assert(((size_t)(kPipChunks + 1) * kPipBuckets + kBitSums) * kPtWords * 4 <= per_window, "workspace");
+    return (size_t)msm_windows(kind) * per_window + 256;
 }
 
 // |v| and its sign for value i
@@ -114,28 +122,23 @@ __device__ __forceinline__ void scalar(const void *vals, int kind, uint64_t i, u
     mag = (uint64_t)(s < 0 ? -s : s);
 }
 
-__device__ __forceinline__ void store_jac(uint32_t *p, const Jac &j)
+// Digit w of W of mag, in -256 .. 255 below the top one: with 256 added to
+// each of the lower digits, digit w is the 9-bit field less 256; the top
+// digit is what is left (at most 2^7 + 1 for every value type, the carry out of 64
+// bits included).
+__device__ __forceinline__ int signed_digit(uint64_t mag, int w, int W)
 {
-    for (int l = 0; l < 8; l++) {
-        p[l] = j.X.v[l];
-        p[8 + l] = j.Y.v[l];
-        p[16 + l] = j.Z.v[l];
-    }
-}
-__device__ __forceinline__ Jac load_jac(const uint32_t *p)
-{
-    Jac j;
-    for (int l = 0; l < 8; l++) {
-        j.X.v[l] = p[l];
-        j.Y.v[l] = p[8 + l];
-        j.Z.v[l] = p[16 + l];
-    }
-    return j;
+    uint64_t bias = 0;
+    for (int i = 0; i < W - 1; i++) bias |= 256ull << (kPipBits * i);
+    const uint64_t t = mag + bias;
+    if (w < W - 1) return (int)((t >> (kPipBits * w)) & 511) - 256;
+    const uint64_t carry = t < mag ? 1 : 0;  // 2^64; W = 8: the top digit starts at bit 63
+    return (int)((t >> (kPipBits * w)) | (carry << (64 - kPipBits * w)));
 }
 
-// Exclusive prefix sums of one value per thread (256 threads); the total to
-// *total.  sc: 4 words of LDS.
-__device__ __forceinline__ uint32_t block_scan256(uint32_t v, uint32_t *sc, uint32_t *total)
+// Exclusive prefix sums of one value per thread (kPipThreads threads); the
+// total to *total.  sc: a word per wave.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *sc, uint32_t *total)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     uint32_t inc = v;
@@ -147,147 +150,25 @@ __device__ __forceinline__ uint32_t block_scan256(uint32_t v, uint32_t *sc, uint
     __syncthreads();
     uint32_t before = 0;
     for (int q = 0; q < wv; q++) before += sc[q];
-    if (total && threadIdx.x == 255) *total = before + inc;
+    if (total && threadIdx.x == kPipThreads - 1) *total = before + inc;
     const uint32_t ex = before + inc - v;
     __syncthreads();
     return ex;
 }
 
-// Workgroup (c, w): the window-w bucket sums of values c L .. c L + L - 1
-// (L = per), in sorts of kPipSub values; written to out[(w C + c) 256 + b].
-__global__ __launch_bounds__(256) void k_pip_buckets(const void *__restrict__ vals, int kind, uint64_t n,
-                                                     const uint32_t *__restrict__ gens, uint64_t per,
-                                                     uint32_t *__restrict__ out)
-{
-    __shared__ uint8_t dig[kPipSub], sgn[kPipSub];
-    __shared__ uint16_t perm[kPipSub];
-    __shared__ uint32_t cnt[256], cur[256], first[256], sc[4], tot[2];
-    __shared__ uint8_t pd[kPipParts];
-    __shared__ uint32_t pp[kPipParts][kJacWords];
-    const int tid = threadIdx.x, w = blockIdx.y, c = blockIdx.x;
-    const uint64_t lo = (uint64_t)c * per, hi = lo + per < n ? lo + per : n;
-    Jac bucket = secp::jac_inf();  // thread b's bucket b (b >= 1)
-    for (uint64_t base = lo; base < hi; base += kPipSub) {
-        const int len = (int)(hi - base < (uint64_t)kPipSub ? hi - base : (uint64_t)kPipSub);
-        cnt[tid] = 0;
-        first[tid] = 0xFFFFFFFFu;
-        __syncthreads();
-        for (int i = tid; i < len; i += 256) {
-            uint64_t mag;
-            int neg;
-            scalar(vals, kind, base + i, mag, neg);
-            const int d = (int)((mag >> (8 * w)) & 255);
-            dig[i] = (uint8_t)d;
-            sgn[i] = (uint8_t)neg;
-            atomicAdd(&cnt[d], 1u);
-        }
-        __syncthreads();
-        // counting sort by digit: perm[start(d) ..] holds the positions of digit d
-        const uint32_t st = block_scan256(cnt[tid], sc, nullptr);
-        cur[tid] = st;
-        if (tid == 1) tot[0] = st;  // the start of digit 1: the number of zero digits
-        __syncthreads();
-        for (int i = tid; i < len; i += 256) perm[atomicAdd(&cur[dig[i]], 1u)] = (uint16_t)i;
-        __syncthreads();
-        // runs of the sorted list past the zero digits: thread t takes [r0, r1)
-        const int skip = (int)tot[0], run = (len - skip + 255) / 256;
-        const int r0 = skip + tid * run < len ? skip + tid * run : len;
-        const int r1 = r0 + run < len ? r0 + run : len;
-        uint32_t np = 0;  // partials of this run: its distinct digits
-        for (int q = r0, prev = -1; q < r1; q++) {
-            const int d = dig[perm[q]];
-            if (d != prev) np++;
-            prev = d;
-        }
-        const uint32_t off = block_scan256(np, sc, &tot[1]);
-        {
-            Jac acc = secp::jac_inf();
-            int cd = -1;
-            uint32_t k = off;
-            for (int q = r0; q < r1; q++) {
-                const int i = perm[q], d = dig[i];
-                if (d != cd) {
-                    if (cd >= 0) {
-                        store_jac(pp[k], acc);
-                        pd[k++] = (uint8_t)cd;
-                    }
-                    acc = secp::jac_inf();
-                    cd = d;
-                }
-                Aff g;
-                const uint32_t *gp = gens + 16 * (base + i);
-                for (int l = 0; l < 8; l++) {
-                    g.x.v[l] = gp[l];
-                    g.y.v[l] = gp[8 + l];
-                }
-                if (sgn[i]) g.y = secp::fe_neg(g.y);
-                acc = secp::jac_add_aff(acc, g);
-            }
-            if (cd >= 0) {
-                store_jac(pp[k], acc);
-                pd[k] = (uint8_t)cd;
-            }
-        }
-        __syncthreads();
-        // The partials are in digit order.  A digit spread over many runs (a
-        // heavy bucket) has many partials: they are summed by a segmented tree,
-        // each round adding to partial k the partial k + s of the same digit
-        // (values read before any is written), until every segment's first
-        // partial holds its sum.
-        const uint32_t nparts = tot[1];
-        if (tid == 0) tot[0] = 1;  // the longest segment
-        for (uint32_t k = tid; k < nparts; k += 256) {
-            if (k == 0 || pd[k] != pd[k - 1]) first[pd[k]] = k;
-            atomicAdd(&cnt[pd[k]], 1u << 16);  // the partials of digit d, above cnt's 13-bit counts
-        }
-        __syncthreads();
-        atomicMax(&tot[0], cnt[tid] >> 16);
-        __syncthreads();
-        for (uint32_t sd = 1; sd < tot[0]; sd <<= 1) {
-            Jac add[2];
-            bool has[2] = {false, false};
-#pragma unroll
-            for (int e = 0; e < 2; e++) {
-                const uint32_t k = tid + 256 * e;
-                if (k + sd < nparts && pd[k + sd] == pd[k]) {
-                    add[e] = secp::jac_add(load_jac(pp[k]), load_jac(pp[k + sd]));
-                    has[e] = true;
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < 2; e++)
-                if (has[e]) store_jac(pp[tid + 256 * e], add[e]);
-            __syncthreads();
-        }
-        if (tid >= 1 && first[tid] != 0xFFFFFFFFu) bucket = secp::jac_add(bucket, load_jac(pp[first[tid]]));
-        __syncthreads();  // LDS reused by the next sort
-    }
-    if (tid >= 1) store_jac(out + (((size_t)w * gridDim.x + c) * 256 + tid) * kJacWords, bucket);
-}
-
-// Sums of 64 points per group of 64 threads (each thread's point in p[tid])
-// by a tree in LDS; the group's first thread ends with the sum in p.
-__device__ __forceinline__ void group64_tree(uint32_t (*p)[kJacWords])
-{
-    const int tid = threadIdx.x, j = tid & 63;
-    for (int st = 32; st >= 1; st >>= 1) {
-        __syncthreads();
-        if (j < st) store_jac(p[tid], secp::jac_add(load_jac(p[tid]), load_jac(p[tid + st])));
-    }
-    __syncthreads();
-}
-
 // The tables of one batch: windows of table t are the global windows
 // wpre[t] .. wpre[t + 1] - 1; its workspace starts off[t] bytes into ws:
-// room for the chunks' bucket sums (W kMsmChunks 256 points, of which the
-// bucket pass fills W C 256, window-major), the bucket sums S (W 256),
-// their bit sums U (W 8).
+// the chunks' bucket sums (W C 256 points, window-major), the bucket sums S
+// (W 256), their bit sums U (W kBitSums).
 struct MsmBatch {
     int count;
     uint32_t wpre[kCommitBatchMax + 1];
-    uint32_t C[kCommitBatchMax];
+    uint32_t C[kCommitBatchMax];     // chunks
+    uint8_t kind[kCommitBatchMax];
     uint64_t off[kCommitBatchMax];
+    uint64_t n[kCommitBatchMax];
+    const void *vals[kCommitBatchMax];
+    uint64_t per;                    // values per chunk, the same for every table
 };
 __device__ __forceinline__ int batch_table(const MsmBatch &b, uint32_t gw)
 {
@@ -302,80 +183,253 @@ __device__ __forceinline__ uint32_t *batch_chunks(char *ws, const MsmBatch &b, i
 __device__ __forceinline__ uint32_t *batch_S(char *ws, const MsmBatch &b, int t)
 {
     const uint32_t W = b.wpre[t + 1] - b.wpre[t];
-    return batch_chunks(ws, b, t) + (size_t)W * kMsmChunks * 256 * kJacWords;
+    return batch_chunks(ws, b, t) + (size_t)W * kPipChunks * kPipBuckets * kPtWords;
 }
 __device__ __forceinline__ uint32_t *batch_U(char *ws, const MsmBatch &b, int t)
 {
     const uint32_t W = b.wpre[t + 1] - b.wpre[t];
-    return batch_S(ws, b, t) + (size_t)W * 256 * kJacWords;
+    return batch_S(ws, b, t) + (size_t)W * kPipBuckets * kPtWords;
 }
 
-// S[w][b] = sum over the C chunks of the chunks' bucket b of window w: 64
-// threads per bucket, each a strided share, then a tree.  Four buckets of
+// Workgroup (window, chunk): the window's bucket sums over the chunk's values,
+// in sorts of kPipSub values.  A table with fewer chunks has no work for
+// the rest.
+//
+// Bound by the field products of the additions (VALU issue): about 1500
+// instructions per addition, one per nonzero digit.  512 threads over 147 KB
+// of LDS are one workgroup, two waves per SIMD; sorts of 8192 values give each
+// thread runs of 16 additions before the runs' partials are merged.  Nine-bit
+// signed digits fill 256 buckets (8-bit unsigned ones 255) with fewer digits:
+// 2 instead of 3 for 18-bit values, 7 instead of 8 for 60-bit words.  The
+// windows of one chunk are adjacent workgroups on one XCD (workgroups go to
+// the XCDs in turn), so its generators are fetched into one L2.
+__global__ __launch_bounds__(kPipThreads) void k_pip_buckets(char *ws, MsmBatch bt, const uint32_t *__restrict__ gens)
+{
+    __shared__ int16_t dig[kPipSub];
+    __shared__ uint16_t perm[kPipSub], pd[kPipParts];
+    __shared__ uint32_t cnt[kPipBuckets + 1], cur[kPipBuckets + 1], first[kPipBuckets + 1];
+    __shared__ uint32_t sc[kPipThreads / 64], tot[2];
+    __shared__ uint32_t pp[kPipParts][kPtWords];
+    const int tid = threadIdx.x;
+    const uint32_t nw = bt.wpre[bt.count], x = blockIdx.x >> 3;
+    const uint32_t gw = x % nw, c = x / nw * 8 + (blockIdx.x & 7);
+    const int t = batch_table(bt, gw);
+    const int W = (int)(bt.wpre[t + 1] - bt.wpre[t]), w = (int)(gw - bt.wpre[t]), kind = bt.kind[t];
+    if (c >= bt.C[t]) return;
+    const void *vals = bt.vals[t];
+    const uint64_t lo = (uint64_t)c * bt.per, hi = lo + bt.per < bt.n[t] ? lo + bt.per : bt.n[t];
+    // thread b - 1's bucket b, kept in memory between the sorts
+    uint32_t *bucket =
+        batch_chunks(ws, bt, t) + (((size_t)w * bt.C[t] + c) * kPipBuckets + (tid & (kPipBuckets - 1))) * kPtWords;
+    bool empty = true;
+    for (uint64_t base = lo; base < hi; base += kPipSub) {
+        const int len = (int)(hi - base < (uint64_t)kPipSub ? hi - base : (uint64_t)kPipSub);
+        if (tid <= kPipBuckets) {
+            cnt[tid] = 0;
+            first[tid] = 0xFFFFFFFFu;
+        }
+        if (tid == 0) cnt[kPipBuckets] = 0;
+        __syncthreads();
+        for (int i = tid; i < len; i += kPipThreads) {
+            uint64_t mag;
+            int neg;
+            scalar(vals, kind, base + i, mag, neg);
+            int d = signed_digit(mag, w, W);
+            if (neg) d = -d;
+            dig[i] = (int16_t)d;
+            atomicAdd(&cnt[d < 0 ? -d : d], 1u);
+        }
+        __syncthreads();
+        // counting sort by |digit|: perm[start(d) ..] holds the positions of digit +-d
+        const uint32_t st = block_scan(tid <= kPipBuckets ? cnt[tid] : 0, sc, nullptr);
+        if (tid <= kPipBuckets) cur[tid] = st;
+        if (tid == 1) tot[0] = st;  // the start of digit 1: the number of zero digits
+        __syncthreads();
+        const int skip = (int)tot[0];
+        if (skip == len) continue;  // no digit in this window (the next sort's first barrier orders LDS)
+        for (int i = tid; i < len; i += kPipThreads) {
+            const int d = dig[i];
+            perm[atomicAdd(&cur[d < 0 ? -d : d], 1u)] = (uint16_t)i;
+        }
+        __syncthreads();
+        // runs of the sorted list past the zero digits: thread t takes [r0, r1)
+        const int run = (len - skip + kPipThreads - 1) / kPipThreads;
+        const int r0 = skip + tid * run < len ? skip + tid * run : len;
+        const int r1 = r0 + run < len ? r0 + run : len;
+        uint32_t np = 0;  // partials of this run: its distinct |digits|
+        for (int q = r0, prev = 0; q < r1; q++) {
+            const int d = abs((int)dig[perm[q]]);
+            if (d != prev) np++;
+            prev = d;
+        }
+        const uint32_t off = block_scan(np, sc, &tot[1]);
+        if (r0 < r1) {
+            Pt acc = secp29::identity();
+            int cd = 0;
+            uint32_t k = off;
+            uint32_t nx[16];
+            auto fetch = [&](int i) {  // the next generator, while this one is added
+                const uint4 *gp = (const uint4 *)(gens + 16 * (base + i));
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const uint4 y = gp[v];
+                    nx[4 * v] = y.x;
+                    nx[4 * v + 1] = y.y;
+                    nx[4 * v + 2] = y.z;
+                    nx[4 * v + 3] = y.w;
+                }
+            };
+            int i = perm[r0];
+            fetch(i);
+            for (int q = r0; q < r1; q++) {
+                const int d = dig[i], ad = abs(d);
+                const F x = secp29::from_limbs32(nx);
+                F y = secp29::from_limbs32(nx + 8);
+                if (d < 0) y = secp29::neg(y);
+                if (q + 1 < r1) {
+                    i = perm[q + 1];
+                    fetch(i);
+                }
+                if (ad != cd) {  // a new bucket starts with this point
+                    if (cd) {
+                        secp29::store(pp[k], acc);
+                        pd[k++] = (uint16_t)cd;
+                    }
+                    acc = Pt{x, y, secp29::one(), secp29::one()};
+                    cd = ad;
+                } else if (secp29::is_identity(acc)) {  // a point and its opposite before this one
+                    acc = Pt{x, y, secp29::one(), secp29::one()};
+                } else {
+                    secp29::add_affine(acc, x, y);
+                }
+            }
+            secp29::store(pp[k], acc);
+            pd[k] = (uint16_t)cd;
+        }
+        __syncthreads();
+        // The partials are in digit order.  A digit spread over many runs (a
+        // heavy bucket) has many partials: they are summed by a segmented tree
+        // (round s: partial p of a segment, p a multiple of 2s, adds the one
+        // s after it) until every segment's first partial holds its sum.
+        const uint32_t nparts = tot[1];
+        if (tid == 0) tot[0] = 1;  // the longest segment
+        for (uint32_t k = tid; k < nparts; k += kPipThreads) {
+            if (k == 0 || pd[k] != pd[k - 1]) first[pd[k]] = k;
+            atomicAdd(&cnt[pd[k]], 1u << 16);  // the partials of digit d, above cnt's 14-bit counts
+        }
+        __syncthreads();
+        if (tid < kPipBuckets) atomicMax(&tot[0], cnt[tid + 1] >> 16);
+        __syncthreads();
+        const uint32_t longest = tot[0];
+        for (uint32_t sd = 1; sd < longest; sd <<= 1) {
+#pragma unroll 1
+            for (uint32_t k = tid; k + sd < nparts; k += kPipThreads)
+                if (((k - first[pd[k]]) & (2 * sd - 1)) == 0 && pd[k + sd] == pd[k])
+                    secp29::store(pp[k], secp29::add(secp29::load(pp[k]), secp29::load(pp[k + sd])));
+            __syncthreads();
+        }
+        if (tid < kPipBuckets && first[tid + 1] != 0xFFFFFFFFu) {
+            const Pt s = secp29::load(pp[first[tid + 1]]);
+            secp29::store(bucket, empty ? s : secp29::add(secp29::load(bucket), s));
+            empty = false;
+        }
+        __syncthreads();  // LDS reused by the next sort
+    }
+    if (tid < kPipBuckets && empty) secp29::store(bucket, secp29::identity());
+}
+
+// Sums of G points per group of G threads (each thread's point in p[tid]) by a
+// tree in LDS; the group's first thread ends with the sum in p.
+template <int G> __device__ __forceinline__ void group_tree(uint32_t (*p)[kPtWords])
+{
+    const int tid = threadIdx.x, j = tid & (G - 1);
+#pragma unroll 1
+    for (int st = G / 2; st >= 1; st >>= 1) {
+        __syncthreads();
+        if (j < st) secp29::store(p[tid], secp29::add(secp29::load(p[tid]), secp29::load(p[tid + st])));
+    }
+    __syncthreads();
+}
+
+// S[w][b] = sum over the C chunks of the chunks' bucket b of window w: 16
+// threads per bucket, each a strided share, then a tree.  Sixteen buckets of
 // one window per workgroup; the workgroups run over the batch's windows.
 __global__ __launch_bounds__(256) void k_pip_bucket_sums(char *ws, MsmBatch bt)
 {
-    __shared__ uint32_t part[256][kJacWords];
-    const int tid = threadIdx.x, g = tid >> 6, j = tid & 63;
-    const uint32_t wb = blockIdx.x * 4 + g, gw = wb >> 8, b = wb & 255;  // (global window, bucket)
-    const int t = batch_table(bt, gw);                                     // workgroup-uniform
-    const uint32_t w = gw - bt.wpre[t];
-    const int C = (int)bt.C[t];
+    __shared__ uint32_t part[256][kPtWords];
+    const int tid = threadIdx.x, j = tid & 15;
+    const uint32_t wb = blockIdx.x * 16 + (tid >> 4), gw = wb / kPipBuckets, b = wb % kPipBuckets;
+    const int t = batch_table(bt, gw);  // workgroup-uniform
+    const uint32_t w = gw - bt.wpre[t], C = bt.C[t];
     const uint32_t *in = batch_chunks(ws, bt, t);
-    Jac acc = secp::jac_inf();
-    if (b >= 1)
-        for (int c = j; c < C; c += 64) acc = secp::jac_add(acc, load_jac(in + (((size_t)w * C + c) * 256 + b) * kJacWords));
-    store_jac(part[tid], acc);
-    group64_tree(part);
-    if (j == 0) store_jac(batch_S(ws, bt, t) + ((size_t)w * 256 + b) * kJacWords, load_jac(part[tid]));
+    Pt acc = secp29::identity();
+#pragma unroll 1
+    for (uint32_t c = j; c < C; c += 16)
+        acc = secp29::add(acc, secp29::load(in + (((size_t)w * C + c) * kPipBuckets + b) * kPtWords));
+    secp29::store(part[tid], acc);
+    group_tree<16>(part);
+    if (j == 0) secp29::store(batch_S(ws, bt, t) + ((size_t)w * kPipBuckets + b) * kPtWords, secp29::load(part[tid]));
 }
 
-// U[w][k] = sum over the b with bit k of S[w][b] (128 buckets): 64 threads
-// per (w, k), two buckets each, then a tree.
-__global__ __launch_bounds__(256) void k_pip_bit_sums(char *ws, MsmBatch bt)
+// U[w][k] = sum over the buckets b with bit k of S[w][b]: 64 threads per (w,
+// k), two buckets each (k < 8: 128 of them; k = 8: bucket 256 alone).
+__global__ __launch_bounds__(64) void k_pip_bit_sums(char *ws, MsmBatch bt)
 {
-    __shared__ uint32_t part[256][kJacWords];
-    const int tid = threadIdx.x, g = tid >> 6, j = tid & 63;
-    const uint32_t wk = blockIdx.x * 4 + g, gw = wk >> 3, k = wk & 7;
-    const int t = batch_table(bt, gw);  // workgroup-uniform (four bits of one window)
+    __shared__ uint32_t part[64][kPtWords];
+    const int tid = threadIdx.x;
+    const uint32_t gw = blockIdx.x / kBitSums, k = blockIdx.x % kBitSums;
+    const int t = batch_table(bt, gw);
     const uint32_t w = gw - bt.wpre[t];
-    const uint32_t *S = batch_S(ws, bt, t);
-    Jac acc = secp::jac_inf();
-    for (int q = j; q < 128; q += 64) {  // the q-th b with bit k set
-        const int b = ((q >> k) << (k + 1)) | (1 << k) | (q & ((1 << k) - 1));
-        acc = secp::jac_add(acc, load_jac(S + ((size_t)w * 256 + b) * kJacWords));
+    const uint32_t *S = batch_S(ws, bt, t) + (size_t)w * kPipBuckets * kPtWords;
+    Pt acc = secp29::identity();
+    if (k == 8) {
+        if (tid == 0) acc = secp29::load(S + 255 * kPtWords);
+    } else {
+#pragma unroll 1
+        for (uint32_t q = tid; q < 128; q += 64) {  // the q-th b below 256 with bit k set
+            const uint32_t b = ((q >> k) << (k + 1)) | (1u << k) | (q & ((1u << k) - 1));
+            acc = secp29::add(acc, secp29::load(S + (size_t)(b - 1) * kPtWords));
+        }
     }
-    store_jac(part[tid], acc);
-    group64_tree(part);
-    if (j == 0) store_jac(batch_U(ws, bt, t) + ((size_t)w * 8 + k) * kJacWords, load_jac(part[tid]));
+    secp29::store(part[tid], acc);
+    group_tree<64>(part);
+    if (tid == 0) secp29::store(batch_U(ws, bt, t) + ((size_t)w * kBitSums + k) * kPtWords, secp29::load(part[0]));
 }
 
-// P = sum_w 2^(8w) T_w, T_w = sum_k 2^k U[w][k]: the windows' T_w by one
-// thread each, then Horner over the windows; affine bytes to out + 64 t.
+// P = sum over (w, k) of 2^(9w + k) U[w][k]: each pair's doublings by a thread
+// of its own, side by side, then a tree and the affine bytes to out + 64 t.
 // One workgroup per table.
-__global__ __launch_bounds__(64) void k_pip_final(char *ws, MsmBatch bt, uint8_t *__restrict__ out)
+__global__ __launch_bounds__(128) void k_pip_final(char *ws, MsmBatch bt, uint8_t *__restrict__ out)
 {
-    __shared__ uint32_t T[8][kJacWords];
+    __shared__ uint32_t T[128][kPtWords];
     const int tid = threadIdx.x, t = blockIdx.x;
     const int W = (int)(bt.wpre[t + 1] - bt.wpre[t]);
     const uint32_t *U = batch_U(ws, bt, t);
-    if (tid < W) {
-        Jac acc = secp::jac_inf();
-        for (int k = 7; k >= 0; k--) {
-            acc = secp::jac_dbl(acc);
-            acc = secp::jac_add(acc, load_jac(U + ((size_t)tid * 8 + k) * kJacWords));
+    Pt p = secp29::identity();
+    if (tid < W * kBitSums) {
+        p = secp29::load(U + (size_t)tid * kPtWords);  // 9 w + k is the thread's number
+        if (!secp29::is_identity(p)) {
+            secp29::Jac q = secp29::to_jac(p);
+#pragma unroll 1
+            for (int i = 0; i < tid; i++) q = secp29::dbl(q);
+            p = secp29::from_jac(q);
         }
-        store_jac(T[tid], acc);
     }
-    __syncthreads();
+    secp29::store(T[tid], p);
+    group_tree<128>(T);
     if (tid == 0) {
-        Jac p = secp::jac_inf();
-        for (int w = W - 1; w >= 0; w--) {
-            for (int q = 0; q < 8; q++) p = secp::jac_dbl(p);
-            p = secp::jac_add(p, load_jac(T[w]));
-        }
+        p = secp29::load(T[0]);
         uint8_t bytes[64];
-        secp::jac_encode(p, bytes);
+        for (int i = 0; i < 64; i++) bytes[i] = 0;
+        if (!secp29::is_identity(p)) {  // x = X / ZZ, y = Y / ZZZ, 1 / ZZ = (ZZ / ZZZ)^2
+            const F iz3 = secp29::inverse(p.ZZZ), iz = secp29::mul(iz3, p.ZZ);
+            const secp::Fe x = secp29::canon(secp29::mul(p.X, secp29::sqr(iz)));
+            const secp::Fe y = secp29::canon(secp29::mul(p.Y, iz3));
+            for (int i = 0; i < 32; i++) {
+                bytes[i] = (uint8_t)(x.v[7 - i / 4] >> (8 * (3 - i % 4)));
+                bytes[32 + i] = (uint8_t)(y.v[7 - i / 4] >> (8 * (3 - i % 4)));
+            }
+        }
         for (int i = 0; i < 64; i++) out[64 * (size_t)t + i] = bytes[i];
     }
 }
@@ -397,21 +451,25 @@ void launch_commit_batch(const void *const *vals, const int *kinds, const uint64
     bt.count = count;
     size_t offs[kCommitBatchMax];
     msm_batch_offsets(kinds, count, offs);
+    uint64_t nmax = 1;
+    for (int t = 0; t < count; t++) nmax = std::max(nmax, ns[t]);
+    const uint64_t subs = (nmax + kPipSub - 1) / kPipSub, Cmax = std::min<uint64_t>(subs, kPipChunks);
+    bt.per = (subs + Cmax - 1) / Cmax * kPipSub;  // whole sorts per chunk but the last
+    uint32_t chunks = 1;
     for (int t = 0; t < count; t++) {
-        const int W = msm_windows(kinds[t]);
-        const uint64_t n = ns[t], subs = (n + kPipSub - 1) / kPipSub;
-        const int C = (int)(subs < (uint64_t)kMsmChunks ? (subs ? subs : 1) : kMsmChunks);
-        const uint64_t per = ((n + C - 1) / C + kPipSub - 1) / kPipSub * kPipSub;  // whole sorts per chunk but the last
-        bt.wpre[t + 1] = bt.wpre[t] + (uint32_t)W;
-        bt.C[t] = (uint32_t)C;
+        bt.wpre[t + 1] = bt.wpre[t] + (uint32_t)msm_windows(kinds[t]);
+        bt.C[t] = (uint32_t)((ns[t] + bt.per - 1) / bt.per);
+        chunks = std::max(chunks, bt.C[t]);
+        bt.kind[t] = (uint8_t)kinds[t];
         bt.off[t] = offs[t];
-        hipLaunchKernelGGL(k_pip_buckets, dim3(C, W), dim3(256), 0, st, vals[t], kinds[t], n, gens, per,
-                           (uint32_t *)((char *)ws + offs[t]));
+        bt.n[t] = ns[t];
+        bt.vals[t] = vals[t];
     }
     const uint32_t nw = bt.wpre[count];
-    hipLaunchKernelGGL(k_pip_bucket_sums, dim3(nw * 64), dim3(256), 0, st, (char *)ws, bt);
-    hipLaunchKernelGGL(k_pip_bit_sums, dim3(nw * 2), dim3(256), 0, st, (char *)ws, bt);
-    hipLaunchKernelGGL(k_pip_final, dim3(count), dim3(64), 0, st, (char *)ws, bt, out);
+    hipLaunchKernelGGL(k_pip_buckets, dim3((chunks + 7) / 8 * 8 * nw), dim3(kPipThreads), 0, st, (char *)ws, bt, gens);
+    hipLaunchKernelGGL(k_pip_bucket_sums, dim3(nw * (kPipBuckets / 16)), dim3(256), 0, st, (char *)ws, bt);
+    hipLaunchKernelGGL(k_pip_bit_sums, dim3(nw * kBitSums), dim3(64), 0, st, (char *)ws, bt);
+    hipLaunchKernelGGL(k_pip_final, dim3(count), dim3(128), 0, st, (char *)ws, bt, out);
 }
 
 void launch_commit(const void *vals, int kind, uint64_t n, const uint32_t *gens, void *ws, uint8_t *out,
