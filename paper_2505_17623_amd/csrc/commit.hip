@@ -87,7 +87,7 @@ void launch_commit_generators(const uint8_t *domain, uint64_t first, uint64_t co
 using secp29::F;
 using secp29::Pt;
 constexpr int kPipThreads = 512;
-constexpr int kPipSub = 8192;              // values a workgroup sorts at a time (one workgroup's LDS)
+constexpr int kPipSub = 16384;             // values a workgroup sorts at a time, at most (LDS)
 constexpr int kPipBits = 9;                // window width; digits -256 .. 255, buckets 1 .. 256
 constexpr int kPipBuckets = 256;
 constexpr int kPipParts = kPipThreads + kPipBuckets - 1;  // run partials of one sort, at most
@@ -169,6 +169,7 @@ struct MsmBatch {
     uint64_t n[kCommitBatchMax];
     const void *vals[kCommitBatchMax];
     uint64_t per;                    // values per chunk, the same for every table
+    uint32_t sort;                   // values per sort
 };
 __device__ __forceinline__ int batch_table(const MsmBatch &b, uint32_t gw)
 {
@@ -192,24 +193,28 @@ __device__ __forceinline__ uint32_t *batch_U(char *ws, const MsmBatch &b, int t)
 }
 
 // Workgroup (window, chunk): the window's bucket sums over the chunk's values,
-// in sorts of kPipSub values.  A table with fewer chunks has no work for
-// the rest.
+// in sorts of bt.sort values.  A table with fewer chunks has no work for the
+// rest.
 //
-// Bound by the field products of the additions (VALU issue): about 1500
-// instructions per addition, one per nonzero digit.  512 threads over 147 KB
-// of LDS are one workgroup, two waves per SIMD; sorts of 8192 values give each
-// thread runs of 16 additions before the runs' partials are merged.  Nine-bit
+// Bound by the field products of the additions (VALU issue): about 1700
+// instructions per addition, one per nonzero digit, 1.7 of the pass's
+// 2.6 ms for the five witness tables of 2^21 outputs.  512 threads over
+// 148 KB of LDS are one workgroup, two waves per SIMD.  A sort's partials
+// cost full additions (1.1 ms with sorts of 8192 values), so a sort takes
+// 16384 values where there are enough; the digits are formed twice rather
+// than kept, and the sorted list holds position and sign in 16 bits.  Nine-bit
 // signed digits fill 256 buckets (8-bit unsigned ones 255) with fewer digits:
 // 2 instead of 3 for 18-bit values, 7 instead of 8 for 60-bit words.  The
 // windows of one chunk are adjacent workgroups on one XCD (workgroups go to
 // the XCDs in turn), so its generators are fetched into one L2.
 __global__ __launch_bounds__(kPipThreads) void k_pip_buckets(char *ws, MsmBatch bt, const uint32_t *__restrict__ gens)
 {
-    __shared__ int16_t dig[kPipSub];
-    __shared__ uint16_t perm[kPipSub], pd[kPipParts];
-    __shared__ uint32_t cnt[kPipBuckets + 1], cur[kPipBuckets + 1], first[kPipBuckets + 1];
+    __shared__ uint16_t perm[kPipSub];  // position, sign in the top bit; sorted by |digit|
+    __shared__ uint16_t pd[kPipParts];
+    __shared__ uint32_t cnt[kPipBuckets + 1], end[kPipBuckets + 1], first[kPipBuckets + 1];
     __shared__ uint32_t sc[kPipThreads / 64], tot[2];
     __shared__ uint32_t pp[kPipParts][kPtWords];
+    static_assert(kPipSub <= 1 << 14, "a position and a sign in 16 bits; counts in 16");
     const int tid = threadIdx.x;
     const uint32_t nw = bt.wpre[bt.count], x = blockIdx.x >> 3;
     const uint32_t gw = x % nw, c = x / nw * 8 + (blockIdx.x & 7);
@@ -222,50 +227,63 @@ __global__ __launch_bounds__(kPipThreads) void k_pip_buckets(char *ws, MsmBatch 
     uint32_t *bucket =
         batch_chunks(ws, bt, t) + (((size_t)w * bt.C[t] + c) * kPipBuckets + (tid & (kPipBuckets - 1))) * kPtWords;
     bool empty = true;
-    for (uint64_t base = lo; base < hi; base += kPipSub) {
-        const int len = (int)(hi - base < (uint64_t)kPipSub ? hi - base : (uint64_t)kPipSub);
+    for (uint64_t base = lo; base < hi; base += bt.sort) {
+        const int len = (int)(hi - base < (uint64_t)bt.sort ? hi - base : (uint64_t)bt.sort);
+        // f(i, digit of value i), every i once; eight loads in flight per thread
+        auto each_digit = [&](auto f) {
+            constexpr int U = 8;
+            for (int i0 = tid; i0 < len; i0 += U * kPipThreads) {
+                uint64_t mag[U];
+                int neg[U];
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int i = i0 + u * kPipThreads;
+                    scalar(vals, kind, base + (i < len ? i : i0), mag[u], neg[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int i = i0 + u * kPipThreads, d = signed_digit(mag[u], w, W);
+                    if (i < len) f(i, neg[u] ? -d : d);
+                }
+            }
+        };
         if (tid <= kPipBuckets) {
             cnt[tid] = 0;
             first[tid] = 0xFFFFFFFFu;
         }
-        if (tid == 0) cnt[kPipBuckets] = 0;
         __syncthreads();
-        for (int i = tid; i < len; i += kPipThreads) {
-            uint64_t mag;
-            int neg;
-            scalar(vals, kind, base + i, mag, neg);
-            int d = signed_digit(mag, w, W);
-            if (neg) d = -d;
-            dig[i] = (int16_t)d;
-            atomicAdd(&cnt[d < 0 ? -d : d], 1u);
-        }
+        each_digit([&](int, int d) { atomicAdd(&cnt[abs(d)], 1u); });
         __syncthreads();
-        // counting sort by |digit|: perm[start(d) ..] holds the positions of digit +-d
+        // counting sort by |digit|; end[d] is the start of digit d, and after the scatter its end
         const uint32_t st = block_scan(tid <= kPipBuckets ? cnt[tid] : 0, sc, nullptr);
-        if (tid <= kPipBuckets) cur[tid] = st;
-        if (tid == 1) tot[0] = st;  // the start of digit 1: the number of zero digits
+        if (tid <= kPipBuckets) end[tid] = st;
+        const int skip = (int)cnt[0];  // zero digits
         __syncthreads();
-        const int skip = (int)tot[0];
-        if (skip == len) continue;  // no digit in this window (the next sort's first barrier orders LDS)
-        for (int i = tid; i < len; i += kPipThreads) {
-            const int d = dig[i];
-            perm[atomicAdd(&cur[d < 0 ? -d : d], 1u)] = (uint16_t)i;
-        }
+        if (skip == len) continue;  // no digit in this window
+        each_digit([&](int i, int d) {
+            if (d) perm[atomicAdd(&end[abs(d)], 1u)] = (uint16_t)(i | (d < 0 ? 1 << 15 : 0));
+        });
         __syncthreads();
         // runs of the sorted list past the zero digits: thread t takes [r0, r1)
         const int run = (len - skip + kPipThreads - 1) / kPipThreads;
         const int r0 = skip + tid * run < len ? skip + tid * run : len;
         const int r1 = r0 + run < len ? r0 + run : len;
-        uint32_t np = 0;  // partials of this run: its distinct |digits|
-        for (int q = r0, prev = 0; q < r1; q++) {
-            const int d = abs((int)dig[perm[q]]);
-            if (d != prev) np++;
-            prev = d;
+        int d0 = 0;       // the digit at r0: the first whose end is past it
+        uint32_t np = 0;  // partials of this run: its distinct digits
+        if (r0 < r1) {
+            int a = 1, b = kPipBuckets;
+            while (a < b) {
+                const int m = (a + b) >> 1;
+                if ((int)end[m] > r0) b = m;
+                else a = m + 1;
+            }
+            d0 = a;
+            np = 1;
+            for (int d = a; (int)end[d] < r1; d++) np += cnt[d + 1] != 0;
         }
         const uint32_t off = block_scan(np, sc, &tot[1]);
         if (r0 < r1) {
             Pt acc = secp29::identity();
-            int cd = 0;
             uint32_t k = off;
             uint32_t nx[16];
             auto fetch = [&](int i) {  // the next generator, while this one is added
@@ -279,32 +297,31 @@ __global__ __launch_bounds__(kPipThreads) void k_pip_buckets(char *ws, MsmBatch 
                     nx[4 * v + 3] = y.w;
                 }
             };
-            int i = perm[r0];
-            fetch(i);
+            int i = perm[r0], de = (int)end[d0];
+            fetch(i & 0x7FFF);
+            bool fresh = true;
+#pragma unroll 1
             for (int q = r0; q < r1; q++) {
-                const int d = dig[i], ad = abs(d);
                 const F x = secp29::from_limbs32(nx);
                 F y = secp29::from_limbs32(nx + 8);
-                if (d < 0) y = secp29::neg(y);
+                if (i >> 15) y = secp29::neg(y);
                 if (q + 1 < r1) {
                     i = perm[q + 1];
-                    fetch(i);
+                    fetch(i & 0x7FFF);
                 }
-                if (ad != cd) {  // a new bucket starts with this point
-                    if (cd) {
-                        secp29::store(pp[k], acc);
-                        pd[k++] = (uint16_t)cd;
-                    }
-                    acc = Pt{x, y, secp29::one(), secp29::one()};
-                    cd = ad;
-                } else if (secp29::is_identity(acc)) {  // a point and its opposite before this one
-                    acc = Pt{x, y, secp29::one(), secp29::one()};
-                } else {
-                    secp29::add_affine(acc, x, y);
+                if (q == de) {  // a new bucket starts with this point
+                    secp29::store(pp[k], acc);
+                    pd[k++] = (uint16_t)d0;
+                    do de = (int)end[++d0];
+                    while (de == q);
+                    fresh = true;
                 }
+                if (fresh) acc = Pt{x, y, secp29::one(), secp29::one()};
+                else secp29::add_affine(acc, x, y);
+                fresh = secp29::is_identity(acc);  // a point and its opposite
             }
             secp29::store(pp[k], acc);
-            pd[k] = (uint16_t)cd;
+            pd[k] = (uint16_t)d0;
         }
         __syncthreads();
         // The partials are in digit order.  A digit spread over many runs (a
@@ -315,17 +332,24 @@ __global__ __launch_bounds__(kPipThreads) void k_pip_buckets(char *ws, MsmBatch 
         if (tid == 0) tot[0] = 1;  // the longest segment
         for (uint32_t k = tid; k < nparts; k += kPipThreads) {
             if (k == 0 || pd[k] != pd[k - 1]) first[pd[k]] = k;
-            atomicAdd(&cnt[pd[k]], 1u << 16);  // the partials of digit d, above cnt's 14-bit counts
+            atomicAdd(&cnt[pd[k]], 1u << 16);  // the partials of digit d, above its count
         }
         __syncthreads();
         if (tid < kPipBuckets) atomicMax(&tot[0], cnt[tid + 1] >> 16);
         __syncthreads();
         const uint32_t longest = tot[0];
         for (uint32_t sd = 1; sd < longest; sd <<= 1) {
-#pragma unroll 1
+            // the round's additions, listed (at most nparts / 2, less than the threads) where perm was
+            if (tid == 0) tot[1] = 0;
+            __syncthreads();
             for (uint32_t k = tid; k + sd < nparts; k += kPipThreads)
                 if (((k - first[pd[k]]) & (2 * sd - 1)) == 0 && pd[k + sd] == pd[k])
-                    secp29::store(pp[k], secp29::add(secp29::load(pp[k]), secp29::load(pp[k + sd])));
+                    perm[atomicAdd(&tot[1], 1u)] = (uint16_t)k;
+            __syncthreads();
+            if ((uint32_t)tid < tot[1]) {
+                const uint32_t k = perm[tid];
+                secp29::store(pp[k], secp29::add(secp29::load(pp[k]), secp29::load(pp[k + sd])));
+            }
             __syncthreads();
         }
         if (tid < kPipBuckets && first[tid + 1] != 0xFFFFFFFFu) {
@@ -453,11 +477,16 @@ void launch_commit_batch(const void *const *vals, const int *kinds, const uint64
     msm_batch_offsets(kinds, count, offs);
     uint64_t nmax = 1;
     for (int t = 0; t < count; t++) nmax = std::max(nmax, ns[t]);
-    const uint64_t subs = (nmax + kPipSub - 1) / kPipSub, Cmax = std::min<uint64_t>(subs, kPipChunks);
-    bt.per = (subs + Cmax - 1) / Cmax * kPipSub;  // whole sorts per chunk but the last
+    for (int t = 0; t < count; t++) bt.wpre[t + 1] = bt.wpre[t] + (uint32_t)msm_windows(kinds[t]);
+    // Sorts of kPipSub values (their partials' additions weigh least), less
+    // while that leaves fewer than 1024 workgroups (four per CU), but at least
+    // two values per thread.
+    const uint64_t want = nmax * bt.wpre[count] / 1024;
+    bt.sort = (uint32_t)(std::min<uint64_t>(std::max<uint64_t>(want, 1024), kPipSub) + 511) / 512 * 512;
+    const uint64_t subs = (nmax + bt.sort - 1) / bt.sort, Cmax = std::min<uint64_t>(subs, kPipChunks);
+    bt.per = (subs + Cmax - 1) / Cmax * bt.sort;  // whole sorts per chunk but the last
     uint32_t chunks = 1;
     for (int t = 0; t < count; t++) {
-        bt.wpre[t + 1] = bt.wpre[t] + (uint32_t)msm_windows(kinds[t]);
         bt.C[t] = (uint32_t)((ns[t] + bt.per - 1) / bt.per);
         chunks = std::max(chunks, bt.C[t]);
         bt.kind[t] = (uint8_t)kinds[t];

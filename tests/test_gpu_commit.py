@@ -175,3 +175,37 @@ def test_commit_batch_matches_single_calls(ra, ctx, gens_small):
     assert L.ra_commit_batch(ctx.h, one, dts, ns, 65, dev_gens.data_ptr(), None, 0, out) == -9  # RA_E_NOT_IMPLEMENTED
     dts[1] = ra.RA_I64
     assert L.ra_commit_batch(ctx.h, one, dts, ns, 2, dev_gens.data_ptr(), None, 0, out) == -1  # RA_E_INVAL
+
+
+# values at the edges of the 9-bit signed digits (a digit of -256, 255, 256, a carry into the top digit and out of
+# 64 bits), and lengths at the edges of a sort and of a chunk
+@pytest.mark.parametrize("n", [511, 1024, 1025, 2049])
+@pytest.mark.parametrize("dt,code", DTYPES)
+def test_commit_digit_and_sort_edges(ra, ctx, gens_small, n, dt, code):
+    dev_gens, gens = gens_small
+    info = np.iinfo(dt)
+    edges = [(1 << b) + d for b in (0, 8, 9, 17, 18, 26, 27, 62, 63, 64) for d in (-1, 0, 1)]
+    edges += [256 * sum(512 ** i for i in range(k)) + d for k in range(1, 8) for d in (-1, 0)]
+    edges = [x for e in edges for x in (e, -e) if info.min <= x <= info.max] + [info.min, info.max]
+    v = np.zeros(n, dtype=dt)
+    pos = np.linspace(0, n - 1, len(edges)).astype(int)
+    v[pos] = np.array(edges, dtype=dt)
+    t = torch.from_numpy(v.view(np.int16 if dt == np.uint16 else (np.int64 if dt == np.uint64 else dt))).cuda()
+    got = ra.commit(ctx, t, dev_gens, getattr(ra, code) if code else None)
+    at = [int(i) for i in np.nonzero(v)[0]]
+    assert got == ec.encode(ec.commit([int(v[i]) for i in at], [gens[i] for i in at]))
+
+
+@pytest.mark.parametrize("n", [2, 700, 20000])
+def test_commit_equal_and_opposite_points(ra, ctx, gens_small, n):
+    """One generator at every position: sums of equal points (doublings), of
+    opposite ones (the identity, in the middle of a run too) and of both."""
+    dev_gens, gens = gens_small
+    same = dev_gens[:1].expand(n, 16).contiguous()
+    rng = np.random.default_rng(n)
+    mixed = rng.integers(-300, 300, size=n).astype(np.int32)
+    pairs = np.where(np.arange(n) & 1, -77, 77).astype(np.int32)
+    pairs[n // 2 * 2:] = 0
+    for v in (np.full(n, 5, dtype=np.int32), pairs, mixed):
+        got = ra.commit(ctx, torch.from_numpy(v).cuda(), same)
+        assert got == ec.encode(ec.commit([int(v.sum())], [gens[0]])), int(v.sum())
