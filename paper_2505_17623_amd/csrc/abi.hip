@@ -1574,7 +1574,6 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
         pa.cst = cst;
         pa.range_sum = tr + 14;
         pa.fs = c->d_fs;
-        pa.sig_out = sig;
         pa.sig_tab = SIG;
         pa.err = err;
         launch_f2_planes(pa, s);

@@ -342,9 +342,8 @@ struct F2PlaneArgs {
     uint64_t *cst;                    // out: c_eq, c_w
     uint64_t *range_sum;              // out: the claimed sum
     // Fiat-Shamir (fs != nullptr): sigma_p is drawn round by round from the
-    // transcript (after each round's values) into sig_out instead of read
+    // transcript (after each round's values) instead of read
     sha::Transcript *fs = nullptr;
-    uint64_t *sig_out = nullptr;
     F2Tab sig_tab{nullptr, nullptr};  // optional, out: eq(sigma_p, .), zero past P (64 entries)
     uint32_t *err = nullptr;
 };

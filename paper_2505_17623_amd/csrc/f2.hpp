@@ -65,6 +65,14 @@ __device__ __forceinline__ f2 l2mul(f2 a, f2 b)
 }
 // lo + r (hi - lo)
 __device__ __forceinline__ f2 l2fold(f2 lo, f2 hi, f2 r) { return l2add(lo, l2mul(r, l2sub(hi, lo))); }
+// a c for 0 <= c <= 7
+__device__ __forceinline__ f2 l2small(f2 a, uint32_t c) { return f2{m61::fold(a.re * c), m61::fold(a.im * c)}; }
+// eq(z, X) for X >= 0
+__device__ __forceinline__ f2 l2eq1x(f2 z, int X)
+{
+    const f2 one_x = f2{X ? m61::P + 1 - X : 1, 0};  // 1 - X
+    return X ? l2add(one_x, l2small(z, 2 * X - 1)) : l2sub(one_x, z);
+}
 __device__ __forceinline__ f2 l2canon(f2 a) { return f2{m61::canon(a.re), m61::canon(a.im)}; }
 
 // A sum of products with its three Karatsuba parts summed apart, combined once.

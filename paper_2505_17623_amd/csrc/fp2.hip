@@ -436,6 +436,7 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
     constexpr int GS = 65;  // row stride of the staged Gram matrix (odd, so rows start in different banks)
     __shared__ uint64_t g_re[64 * GS], g_im[64 * GS];
     __shared__ f2 W[64], dv[64], es[64], tau[8], sig[8], lam[4], pre[8], tot[8], gsh[4];
+    __shared__ f2 ev[4 * kMaxPlaneLog];  // the rounds' values: stores to memory would be waited for at each barrier
     __shared__ FsLds fsl;  // the transcript (Fiat-Shamir mode)
     const int tid = threadIdx.x, lP = a.lP, P = a.P;
     for (int e = tid; e < P * P; e += blockDim.x) {
@@ -506,18 +507,14 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
             A = f2sub(f2sub(A, f2small(tot[3], u)), f2small(tot[4], X));
             const f2 B = f2add(f2add(f2small(tot[5], u * u), f2small(cross, X * u)), f2small(tot[6], X * X));
             const f2 g = f2add(f2mul(f2mul(pre[jj], eq1x(tau[jj], X)), A), f2mul(mu, B));
-            stp(a.ev + 8 * jj + 2 * tid, g);
+            ev[4 * jj + tid] = g;
             gsh[tid] = g;
         }
         __syncthreads();
         if (a.fs) {  // the round's values absorbed, sigma_jj drawn
             if (!fs_absorb(fsl, (const uint32_t *)gsh, 16) && tid == 0) *a.err = 1;
             fs_draw(fsl);
-            if (jj == lP - 1) fs_push(a.fs, fsl);
-            if (tid == 0) {
-                sig[jj] = f2{fsl.out[0], fsl.out[1]};
-                stp(a.sig_out + 2 * jj, sig[jj]);
-            }
+            if (tid == 0) sig[jj] = f2{fsl.out[0], fsl.out[1]};
             __syncthreads();
         }
         const f2 sg = sig[jj];
@@ -540,6 +537,8 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
             }
         __syncthreads();
     }
+    if (a.fs) fs_push(a.fs, fsl);
+    if (tid >= 192 && tid - 192 < 4 * lP) stp(a.ev + 2 * (tid - 192), ev[tid - 192]);
     if (tid < 64 && a.sig_tab.re) stt(a.sig_tab, tid, tid < P ? l2canon(eq_entry(sig, lP, tid)) : f2of(0));
     if (tid == 64) {  // x rounds' constants
         stp(a.cst, pre[lP]);

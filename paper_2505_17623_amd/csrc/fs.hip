@@ -138,13 +138,18 @@ void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *r
 // ---------------------------------------------------------------------------
 constexpr int kFsThreads = 128;  // one wave runs the rounds, one the message schedules
 
-// ndraw challenges in a row to out.
+// ndraw challenges (at most kFsDraws) in a row to out.  They are kept in LDS
+// until the last: a store to memory before a barrier is waited for there.
+constexpr int kFsDraws = 64;
 __device__ __forceinline__ void fs_draws(FsLds &f, uint64_t *out, int ndraw)
 {
+    __shared__ uint64_t drawn[2 * kFsDraws];
     for (int i = 0; i < ndraw; i++) {
         fs_draw(f);
-        if (threadIdx.x < 2) out[2 * i + threadIdx.x] = f.out[threadIdx.x];
+        if (threadIdx.x < 2) drawn[2 * i + threadIdx.x] = f.out[threadIdx.x];
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * ndraw; i += blockDim.x) out[i] = drawn[i];
 }
 
 __global__ __launch_bounds__(kFsThreads) void k_fs_header(sha::Transcript *fs, FsHeader h,
@@ -379,24 +384,91 @@ void launch_fs_pass(const FsPassArgs &a, hipStream_t st)
     }
 }
 
+// ---------------------------------------------------------------------------
 // The last v rounds (tables of 2^v <= 2^kFsTailLog entries once the previous
 // pass's round is finished and folded), the instance's final values, and
-// their absorption.
+// their absorption, in one workgroup.
+//
+// A round's hash takes about 5 us on two waves, so the rest of a round runs
+// beside it on the others: with T_c the tables bound at rho_{<c}, the sums of
+// round c + 1 are quadratic in rho_c, its pairs being lo = x0 + rho (x2 - x0),
+// hi = x1 + rho (x3 - x1) over T_c's quads, and are taken at rho = 0 (x0, x1),
+// 1 (x2, x3) and infinity (the differences) while rho_c is being hashed.  Once
+// it is there, wave 0 alone interpolates them, forms the round's values and
+// goes on hashing while the other waves fold.  Eleven rounds in sequence (sums
+// over the block, values, hash, fold) took 111 us; so they take 88 (range).
+// ---------------------------------------------------------------------------
+constexpr int kTailWorkers = kFsTailThreads / 64 - 2;  // waves 2 ..
+
+// Sums over pairs weighted by w: ll = lo lo', hh = hi hi', and lo hi' (range)
+// or (lo + hi)(lo' + hi') (else).
+struct PairSums {
+    K3 ll, lh, hh;
+    template <int KIND> __device__ __forceinline__ void add(f2 a0, f2 a1, f2 b0, f2 b1)
+    {
+        ll.add(a0, b0);
+        if (KIND == F2_RANGE) lh.add(a0, b1);
+        else lh.add(l2add(a0, a1), l2add(b0, b1));
+        hh.add(a1, b1);
+    }
+};
+// values (3 e + q) for e = 0, 1, infinity and q = ll, lh, hh; range: 9 + 2 e + b the sums of lo (b = 0), hi at e = 0, 1
+constexpr int tail_values(int kind) { return kind == F2_RANGE ? 13 : 9; }
+
+struct FsTailLds {
+    uint64_t part[kTailWorkers][2 * 13];  // a wave's sums, canonical
+    uint64_t tr[kTailWorkers][8 * 64];    // its transposes
+    f2 co[5][2];                          // K_{c+1} eq(r_{c+1}, Y), Y = 0 .. 3, and K_{c+1}, linear in rho_c
+};
+
+// Sums of NV values per lane of the wave, to out (2 NV words); tr: 512 words.
+template <int NV>
+__device__ __forceinline__ void wave_totals(const f2 (&x)[NV], uint64_t *tr, uint64_t *out)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q0 = 0; q0 < NV; q0 += 4) {  // eight words at a time: 8 lanes per word, 8 entries each
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const f2 v = q0 + q < NV ? x[q0 + q < NV ? q0 + q : 0] : f2of(0);
+            tr[(2 * q) * 64 + lane] = v.re;
+            tr[(2 * q + 1) * 64 + lane] = v.im;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint64_t *src = tr + (lane >> 3) * 64 + (lane & 7);
+        uint64_t v = 0;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) v = m61::fold(v + src[8 * e] + src[8 * e + 8]);
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) v = m61::fold(v + __shfl_xor(v, off, 64));
+        const int w = 2 * q0 + (lane >> 3);
+        if ((lane & 7) == 0 && w < 2 * NV) out[w] = m61::canon(v);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+__device__ __forceinline__ f2 lane_of(f2 v, int i) { return f2{__shfl(v.re, i, 64), __shfl(v.im, i, 64)}; }
+
 template <int KIND>
 __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
 {
-    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2, S = 1 << kFsTailLog;
+    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2, S = 1 << kFsTailLog, NV = tail_values(KIND);
     constexpr int D1 = KIND == F2_MATMUL ? 3 : 4;
     // red: also the byte tables while Bx is formed
     constexpr int RED = NW * kFsTailThreads > 8 * 512 ? NW * kFsTailThreads : 8 * 512;
     __shared__ f2 T[NT][S], LS[KIND == F2_MATMUL ? 1 : S];
-    __shared__ uint64_t red[RED];
+    __shared__ union {
+        uint64_t red[RED];
+        FsTailLds t;
+    } u;
     __shared__ FsFinLds l;
     __shared__ f2 sig[KIND == F2_RANGE ? 64 : 1], fin[3];
-    const int tid = threadIdx.x, n0 = 1 << a.v;
+    __shared__ f2 ev[D1 * kFsTailLog], rs[kFsTailLog];  // the rounds' values, written out at the end; r_j0 ..
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n0 = 1 << a.v;
     f2 rho{0, 0};
     if (KIND != F2_MATMUL)
         for (int i = tid; i < n0; i += blockDim.x) LS[i] = a.LS[i];  // entries 2^k + y, k < v
+    if (KIND != F2_MATMUL && tid < a.v) rs[tid] = ldp(a.r + 2 * (a.j0 + tid));
     const bool prev = a.fin.nb > 0;
     if (prev) {
         rho = fs_finish_prev<KIND>(l, a.fin, true);
@@ -405,7 +477,7 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
         if (tid == 0) l.K = f2of(1);
     }
     if (KIND == F2_RANGE && !prev) {
-        f2(*tab)[256] = (f2(*)[256])red;
+        f2(*tab)[256] = (f2(*)[256])u.red;
         if (tid < 64) sig[tid] = ldt(a.sig, tid);
         __syncthreads();
         f2_byte_tables(sig, a.tabs, tab);
@@ -433,8 +505,13 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
             }
     }
     __syncthreads();
-    for (int c = 0; c < a.v; c++) {
-        const int h = n0 >> (c + 1);
+    f2 ceq = f2of(0), cd = f2of(0);
+    if (KIND == F2_RANGE) {
+        ceq = ldp(a.cst);
+        cd = f2sub(ldp(a.cst + 2), ceq);
+    }
+    if (a.v > 0) {  // the first round's sums, by every thread
+        const int h = n0 >> 1;
         F2Sums<KIND> acc;
         for (int i = tid; i < h; i += blockDim.x) {
             f2 lo[2], hi[2];
@@ -453,13 +530,139 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
         }
         uint64_t v[NW];
         acc.words(v, false, f2of(1));
-        f2_totals<NW>(v, red, l.tot, h < 64 ? 64 : (h < kFsTailThreads ? h : kFsTailThreads));
-        const f2 r = KIND == F2_MATMUL ? f2of(0) : ldp(a.r + 2 * (a.j0 + c));
-        rho = fs_finish_round<KIND>(l, r, a.cst, a.ev + 2 * D1 * (a.j0 + c), true, a.err);
-        if (KIND != F2_MATMUL && tid == blockDim.x - 1) l.K = f2mul(l.K, eq1z(r, rho));
-        for (int i = tid; i < h; i += blockDim.x)
+        f2_totals<NW>(v, u.red, l.tot, h < 64 ? 64 : (h < kFsTailThreads ? h : kFsTailThreads));
+        // the factors of the first round's values (no rho before it)
+        if (KIND != F2_MATMUL && tid < 5)
+            u.t.co[tid][0] = tid < 4 ? f2mul(l.K, eq1x(rs[0], tid)) : l.K;
+        if (tid < 5) u.t.co[tid][1] = f2of(0);
+        __syncthreads();
+    }
+    for (int c = 0; c < a.v; c++) {
+        const int lg = a.v - c;                         // T_c holds 2^lg entries
+        const int n = lg >= 2 ? 1 << (lg - 2) : 0;      // its quads
+        const f2 z = c ? f2{l.f.out[0], l.f.out[1]} : f2of(0);  // rho_{c-1}
+        if (wave == 0) {
+            // the round's sums at rho_{c-1}, in lanes 0 .. 4: ll, lh, hh, l, h; in lanes 5 .. 9 the factors
+            f2 p0 = f2of(0), p1 = f2of(0), pi = f2of(0);
+            const int q = lane < 3 ? lane : (KIND == F2_RANGE && lane < 5 ? lane : 0);
+            if (c == 0) {
+                constexpr int rmap[5] = {2, 3, 4, 0, 1}, omap[3] = {0, 2, 1};  // of F2Sums' words
+                const int at = KIND == F2_RANGE ? (q == 0 ? rmap[0] : q == 1 ? rmap[1] : q == 2 ? rmap[2] : q == 3 ? rmap[3] : rmap[4])
+                                                : (q == 0 ? omap[0] : q == 1 ? omap[1] : omap[2]);
+                p0 = p1 = f2{l.tot[2 * at], l.tot[2 * at + 1]};
+            } else {
+                const int nq = 1 << (lg - 1), nw = nq < 64 * kTailWorkers ? (nq + 63) >> 6 : kTailWorkers;  // of T_{c-1}
+                const int i0 = q < 3 ? q : 6 + q, i1 = q < 3 ? 3 + q : 8 + q, ii = q < 3 ? 6 + q : i0;
+                for (int w = 0; w < nw; w++) {
+                    const uint64_t *t = u.t.part[w];
+                    p0 = l2add(p0, f2{t[2 * i0], t[2 * i0 + 1]});
+                    p1 = l2add(p1, f2{t[2 * i1], t[2 * i1 + 1]});
+                    if (q < 3) pi = l2add(pi, f2{t[2 * ii], t[2 * ii + 1]});
+                }
+            }
+            f2 b = l2sub(p1, p0);
+            if (KIND != F2_MATMUL && lane >= 5 && lane < 10) {
+                p0 = u.t.co[lane - 5][0];
+                b = u.t.co[lane - 5][1];
+                pi = f2of(0);
+            }
+            const f2 v = l2add(p0, l2mul(z, l2add(b, l2mul(l2sub(z, f2of(1)), pi))));
+            // s(0), s(1), s(infinity) (the leading coefficient) in lanes 0, 1, 2
+            const f2 ll = lane_of(v, 0), lh = lane_of(v, 1), hh = lane_of(v, 2), t2 = l2add(ll, hh);
+            f2 sv;
+            if (KIND == F2_RANGE) {
+                const f2 inf = l2sub(t2, l2add(lh, lh)), l0 = lane_of(v, 3), h0 = lane_of(v, 4);
+                const f2 lin = l2mul(cd, lane == 0 ? l0 : h0), qd = l2mul(ceq, lane == 0 ? ll : (lane == 1 ? hh : inf));
+                sv = lane == 2 ? qd : l2add(qd, lin);
+            } else {
+                sv = lane == 0 ? ll : (lane == 1 ? hh : l2sub(l2add(t2, t2), lh));
+            }
+            const f2 s0 = lane_of(sv, 0), s1 = lane_of(sv, 1), si = lane_of(sv, 2);
+            const int X = lane & 3;
+            f2 g = l2add(l2add(s0, l2small(l2sub(s1, s0), X)), l2small(si, X * (X - 1)));
+            if (KIND != F2_MATMUL) {
+                const f2 ke = lane_of(v, 5 + X);
+                g = l2mul(ke, g);
+                if (lane == 9) l.K = v;  // K_c
+            }
+            g = l2canon(g);
+            // the values: to the transcript, behind what is pending
+            const uint32_t qlen = l.f.m[8];
+            const bool ok = qlen + 16 * D1 <= sha::kFsPending;
+            if (lane < D1) {
+                ev[D1 * c + lane] = g;
+                uint32_t *m = l.f.m + 9 + (qlen >> 2) + 4 * lane;
+                if (ok) {
+                    m[0] = (uint32_t)g.re;
+                    m[1] = (uint32_t)(g.re >> 32);
+                    m[2] = (uint32_t)g.im;
+                    m[3] = (uint32_t)(g.im >> 32);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane == 0) {
+                if (ok) l.f.m[8] = qlen + 16 * D1;
+                else *a.err = 1;
+            }
+        } else if (wave >= 2 && c > 0) {  // T_c from T_{c-1}: an entry's two sources are read by its own thread only
+            for (int i = tid - 128; i < (n ? n : 1); i += 64 * kTailWorkers)
 #pragma unroll
-            for (int q = 0; q < NT; q++) T[q][i] = l2fold(T[q][i], T[q][i + h], rho);
+                for (int e = 0; e < 4; e++) {
+                    const int p = n ? i + e * n : e, hs = 1 << lg;
+                    if (p < hs)
+#pragma unroll
+                        for (int q = 0; q < NT; q++) T[q][p] = l2fold(T[q][p], T[q][p + hs], z);
+                }
+        }
+        __syncthreads();
+        if (wave < 2) {
+            fs_hash(l.f);
+        } else if (n) {
+            if (tid - 128 < (n > 64 ? n : 64) || wave == 2) {
+                PairSums at[3];
+                f2 lin[2][2] = {{f2of(0), f2of(0)}, {f2of(0), f2of(0)}};
+                for (int i = tid - 128; i < n; i += 64 * kTailWorkers) {
+                    f2 x[4], y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        y[e] = T[NT - 1][i + e * n];
+                        x[e] = T[0][i + e * n];
+                        if (KIND != F2_MATMUL) x[e] = l2mul(LS[n + i], x[e]);
+                    }
+                    at[0].template add<KIND>(x[0], x[1], y[0], y[1]);
+                    at[1].template add<KIND>(x[2], x[3], y[2], y[3]);
+                    at[2].template add<KIND>(l2sub(x[2], x[0]), l2sub(x[3], x[1]), l2sub(y[2], y[0]), l2sub(y[3], y[1]));
+                    if (KIND == F2_RANGE)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) lin[e >> 1][e & 1] = l2add(lin[e >> 1][e & 1], x[e]);
+                }
+                f2 val[NV];
+#pragma unroll
+                for (int e = 0; e < 3; e++) {
+                    val[3 * e] = at[e].ll.value();
+                    val[3 * e + 1] = at[e].lh.value();
+                    val[3 * e + 2] = at[e].hh.value();
+                }
+                if constexpr (KIND == F2_RANGE)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) val[9 + e] = lin[e >> 1][e & 1];
+                wave_totals<NV>(val, u.t.tr[wave - 2], u.t.part[wave - 2]);
+            }
+            if (KIND != F2_MATMUL && wave == kTailWorkers + 1 && lane < 5) {
+                // K_{c+1} = K_c eq(r_c, rho_c) = K_c (1 - r_c) + rho_c K_c (2 r_c - 1), with its factors for round c + 1
+                const f2 K = l.K, r = rs[c];
+                const f2 k0 = l2mul(K, f2sub(f2of(1), r)), k1 = l2mul(K, f2sub(f2add(r, r), f2of(1)));
+                f2 e = f2of(1);
+                if (lane < 4) e = l2eq1x(rs[c + 1], lane);
+                u.t.co[lane][0] = l2mul(k0, e);
+                u.t.co[lane][1] = l2mul(k1, e);
+            }
+        }
+        __syncthreads();
+    }
+    if (a.v > 0) {
+        if (tid < NT) T[tid][0] = l2fold(T[tid][0], T[tid][1], f2{l.f.out[0], l.f.out[1]});
+        if (tid >= 64 && tid - 64 < D1 * a.v) stp(a.ev + 2 * (D1 * a.j0 + tid - 64), ev[tid - 64]);
         __syncthreads();
     }
     constexpr uint64_t inv2 = 1ull << 60;  // 2 2^60 = 2^61 = 1 mod p
@@ -470,7 +673,7 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
         fin[1] = KIND == F2_RELU ? f2scale(f2sub(y, x), inv2) : y;
         if (KIND == F2_MATMUL) {  // c0 = g_1(0) + g_1(1), or a b with no rounds
             const bool any = a.j0 + a.v > 0;
-            stp(a.out, any ? f2add(ldp(a.ev), ldp(a.ev + 2)) : f2mul(x, y));
+            stp(a.out, any ? (a.j0 ? f2add(ldp(a.ev), ldp(a.ev + 2)) : f2add(ev[0], ev[1])) : f2mul(x, y));
         }
         for (int q = 0; q < nfin; q++) stp(a.out + (KIND == F2_MATMUL ? 2 : 0) + 2 * q, fin[q]);
     }

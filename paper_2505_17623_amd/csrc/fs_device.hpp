@@ -27,6 +27,7 @@ struct FsLds {
     uint32_t m[kFsMaxBlocks * 16];    // the message, room for its padding
     uint4 kw[kFsMaxBlocks * 16];      // schedule plus round constants, 64 words per block
     uint64_t out[2];                  // the last challenge drawn
+    uint32_t ready;                   // quarters of the first schedules wave 1 has stored (0 between draws)
 };
 
 __device__ __forceinline__ uint32_t vgpr(uint32_t x)  // the value, kept in vector registers
@@ -40,6 +41,7 @@ __device__ inline void fs_pull(FsLds &f, const sha::Transcript *g)
 {
     const uint32_t *s = (const uint32_t *)g;
     for (int i = threadIdx.x; i < kFsMsgWords; i += blockDim.x) f.m[i] = s[i];
+    if (threadIdx.x == 0) f.ready = 0;
 }
 
 // The block: f back into the transcript (after a barrier).
@@ -109,53 +111,58 @@ __device__ __forceinline__ void fs_schedule16(uint32_t (&w)[16], uint4 *kw)
     for (int q = 0; q < 4; q++) kw[4 * P + q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
 }
 
-// The block: S = H(S || LE32(|Q|) || Q), Q emptied; the challenge's two words
-// to f.out.  Barriers on both sides.
-__device__ inline void fs_draw(FsLds &f)
+// The draw proper, by waves 0 and 1 between two barriers of the block (the
+// message complete before the first; the other waves may do other work):
+// S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two words to f.out.
+// Wave 0 waits in LDS for each quarter of the first block's schedule; wave 1
+// stores every quarter without waiting for anything.
+__device__ inline void fs_hash(FsLds &f)
 {
-    __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int words = 9 + (int)(f.m[8] >> 2), nblk = (4 * words + 9 + 63) / 64;
-    uint32_t w[16], v[8], st[8];
-    if (wave == 1 && lane < nblk) {
+    auto publish = [&](uint32_t p) {  // LDS operations of a wave stay in order
+        __hip_atomic_store(&f.ready, p, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto await = [&](uint32_t p) {
+        while (__hip_atomic_load(&f.ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < p) {
+        }
+    };
+    if (wave == 1 && lane < nblk) {  // the lanes without a block take no part: they would publish ahead of the others
+        uint32_t w[16];
+        uint4 *kw = f.kw + 16 * lane;
         // the padded message: 0x80 after its last word, its bit length at the end
+#pragma unroll
+        for (int t = 0; t < 16; t++) w[t] = f.m[16 * lane + t];  // m has room for the last block
 #pragma unroll
         for (int t = 0; t < 16; t++) {
             const int g = 16 * lane + t;
-            uint32_t x = g < words ? __builtin_bswap32(f.m[g]) : (g == words ? 0x80000000u : 0u);
-            if (t == 15 && lane == nblk - 1) x = 32u * (uint32_t)words;
-            w[t] = x;
+            w[t] = g < words ? __builtin_bswap32(w[t]) : (g == words ? 0x80000000u : 0u);
         }
-        uint4 *kw = f.kw + 16 * lane;
+        if (lane == nblk - 1) w[15] = 32u * (uint32_t)words;
 #pragma unroll
         for (int q = 0; q < 4; q++)
             kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
                                w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
+        publish(1);
+        fs_schedule16<1>(w, kw);
+        publish(2);
+        fs_schedule16<2>(w, kw);
+        publish(3);
+        fs_schedule16<3>(w, kw);
+        publish(4);
     } else if (wave == 0) {
+        uint32_t v[8], st[8];
 #pragma unroll
-        for (int i = 0; i < 8; i++) v[i] = st[i] = vgpr(sha::kConsts.h[i]);
-    }
-    __syncthreads();
-    // wave 1 stays sixteen words ahead of wave 0 in the first block; by its
-    // end every block's schedule is there
-    if (wave == 0) fs_rounds16(v, f.kw);
-    else if (wave == 1 && lane < nblk) fs_schedule16<1>(w, f.kw + 16 * lane);
-    __syncthreads();
-    if (wave == 0) fs_rounds16(v, f.kw + 4);
-    else if (wave == 1 && lane < nblk) fs_schedule16<2>(w, f.kw + 16 * lane);
-    __syncthreads();
-    if (wave == 0) fs_rounds16(v, f.kw + 8);
-    else if (wave == 1 && lane < nblk) fs_schedule16<3>(w, f.kw + 16 * lane);
-    __syncthreads();
-    if (wave == 0) {
-        fs_rounds16(v, f.kw + 12);
-#pragma unroll
-        for (int i = 0; i < 8; i++) st[i] += v[i];
-        for (int b = 1; b < nblk; b++) {
+        for (int i = 0; i < 8; i++) st[i] = vgpr(sha::kConsts.h[i]);
+#pragma unroll 1
+        for (int b = 0; b < nblk; b++) {
 #pragma unroll
             for (int i = 0; i < 8; i++) v[i] = st[i];
 #pragma unroll 1
-            for (int p = 0; p < 4; p++) fs_rounds16(v, f.kw + 16 * b + 4 * p);
+            for (int p = 0; p < 4; p++) {
+                if (b == 0) await(p + 1);
+                fs_rounds16(v, f.kw + 16 * b + 4 * p);
+            }
 #pragma unroll
             for (int i = 0; i < 8; i++) st[i] += v[i];
         }
@@ -163,6 +170,7 @@ __device__ inline void fs_draw(FsLds &f)
 #pragma unroll
             for (int i = 0; i < 8; i++) f.m[i] = st[i] = __builtin_bswap32(st[i]);  // S as its bytes in order
             f.m[8] = 0;
+            f.ready = 0;
             constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
 #pragma unroll
             for (int q = 0; q < 2; q++) {
@@ -172,6 +180,13 @@ __device__ inline void fs_draw(FsLds &f)
             }
         }
     }
+}
+
+// The block: a draw with its barriers.
+__device__ inline void fs_draw(FsLds &f)
+{
+    __syncthreads();
+    fs_hash(f);
     __syncthreads();
 }
 
