@@ -451,7 +451,7 @@ RangeLayout range_layout(uint64_t N, int lP, int relu)
 // range rounds (8 each, for up to 6 + log N) and the ReLU rounds (8 each).
 constexpr int kF2TrFixed = 22;
 struct Fp2Layout {
-    size_t o_gemm, o_e1, o_e2, o_scr, o_a, o_b, o_eq, o_eqr, o_eqz, o_bx, o_d, o_s, o_sig, o_one, o_gp0, o_gp1, o_g,
+    size_t o_gemm, o_e1, o_e2, o_scr, o_a, o_b, o_eq, o_bx, o_d, o_s, o_sig, o_one, o_gp0, o_gp1, o_g,
         o_part, o_cpart, o_cst, o_tr, tr_words, o_hs, o_ls, o_fsch, o_fsk, o_fst, o_dig0, o_dig1, o_root, o_err, bytes;
 };
 // leaves of the witness tables' Merkle tree (R, Rm, Y, Z int32 / uint16, the bit words)
@@ -460,6 +460,8 @@ uint64_t witness_leaves(uint64_t N)
     auto ch = [](uint64_t b) { return (b + 1023) / 1024; };
     return 3 * ch(4 * N) + ch(2 * N) + ch(8 * N);
 }
+// passes of an instance of v rounds (two rounds each, until 2^kF2TailLog entries are left)
+int f2_passes(int v) { return v > kF2TailLog ? (v - kF2TailLog + 1) / 2 : 0; }
 Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
 {
     const uint64_t N = (uint64_t)n * k, H = N > 1 ? N / 2 : 1;
@@ -474,8 +476,6 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_a = cv.take<uint64_t>(2 * (size_t)m);
     l.o_b = cv.take<uint64_t>(2 * (size_t)m);
     l.o_eq = cv.take<uint64_t>(2 * N);
-    l.o_eqr = cv.take<uint64_t>(2 * H);
-    l.o_eqz = cv.take<uint64_t>(2 * H);
     l.o_bx = cv.take<uint64_t>(2 * N);
     l.o_d = cv.take<uint64_t>(2 * H);
     l.o_s = cv.take<uint64_t>(2 * H);
@@ -484,7 +484,8 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_gp0 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_gp1 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_g = cv.take<uint64_t>(2 * 4096);
-    l.o_part = cv.take<uint64_t>((size_t)(lm + 2 * lN + 1) * kF2MaxBlocks * 8);
+    // given challenges: every pass's partials; hashed: two copies of ten words per block
+    l.o_part = cv.take<uint64_t>((size_t)std::max(1, f2_passes(lm) + 2 * f2_passes(lN)) * kF2PassPart);
     l.o_cpart = cv.take<uint64_t>((size_t)kF2MaxBlocks * 8);
     l.o_cst = cv.take<uint64_t>(8);
     l.tr_words = kF2TrFixed + 6 * (size_t)lm + 8 * (size_t)(kMaxPlaneLog + lN) + 8 * (size_t)lN;
@@ -1128,13 +1129,11 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     };
     const uint64_t H = N > 1 ? N / 2 : 1;
     const F2Tab E1 = tab(L.o_e1, n), E2 = tab(L.o_e2, k), Ta = tab(L.o_a, m), Tb = tab(L.o_b, m);
-    const F2Tab EQ = tab(L.o_eq, N), EQr = tab(L.o_eqr, H), EQz = tab(L.o_eqz, H), Bx = tab(L.o_bx, N);
+    const F2Tab EQ = tab(L.o_eq, N), Bx = tab(L.o_bx, N);
     const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64), ONE = tab(L.o_one, 1);
     uint64_t *scr = (uint64_t *)(ws + L.o_scr), *part = (uint64_t *)(ws + L.o_part);
     uint64_t *cpart = (uint64_t *)(ws + L.o_cpart), *cst = (uint64_t *)(ws + L.o_cst);
     uint64_t *tr = (uint64_t *)(ws + L.o_tr), *Gre = (uint64_t *)(ws + L.o_g), *Gim = Gre + 4096;
-    const size_t pstride = (size_t)kF2MaxBlocks * 8;
-
     // the witness: the exact product, then t and P (given: fixed on the host)
     launch_gemm_mfma(d_A, a_dtype == RA_I32, d_B, d_C, n, m, k, ws + L.o_gemm, s, nullptr, nullptr, false, nullptr);
     int P = 0, lP = 0, t = io->t;
@@ -1166,8 +1165,8 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     const uint64_t *r1 = c->d_chal + c->cursor, *r2 = r1 + 2 * ln, *rho = r2 + 2 * lk, *lam = rho + 2 * lm;
     const uint64_t *tau = lam + 8, *sig = tau + 2 * lP, *rho2 = sig + 2 * (lP + lN);
 
-    launch_f2_eq(r1, ln, E1, s);
-    launch_f2_eq(r2, lk, E2, s);
+    f2 *HS = (f2 *)(ws + L.o_hs), *LS = (f2 *)(ws + L.o_ls);
+    launch_f2_eqs(r1, ln, lk, E1, E2, HS, LS, s);
     // R, Rm, Y, Z, the bit table (the F_p claims this pass also forms are not used)
     launch_witness_rescale(d_C, N, lk, E1.re, E2.re, d_R, d_Rm, d_Y, d_Z, d_bits, (uint64_t *)(c->d_wit + kWitClaims),
                            c->d_params, c->d_claims, nullptr, s, io->t >= 0 ? &hp : nullptr,
@@ -1180,41 +1179,6 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     launch_bind_cols(d_B, RA_I16, m, k, E2.re, Tb.re, s);
     launch_bind_cols(d_B, RA_I16, m, k, E2.im, Tb.im, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
-    uint64_t *p_mm = part, *p_rs = p_mm + (size_t)lm * pstride, *p_zc = p_rs + (size_t)lN * pstride;
-    // each instance: one launch per round while its tables hold more than
-    // 2^kF2TailLog entries, then the rest in one workgroup
-    const int tm = std::min(lm, kF2TailLog), jm = lm - tm;
-    for (int j = 0; j < jm; j++) {
-        F2RoundArgs ra{};
-        ra.kind = F2_MATMUL;
-        ra.h = (uint64_t)m >> (j + 1);
-        ra.src[0] = ra.dst[0] = Ta;
-        ra.src[1] = ra.dst[1] = Tb;
-        ra.rho = rho + 2 * j;
-        ra.part = p_mm + (size_t)j * pstride;
-        launch_f2_round(ra, s);
-    }
-    if (tm > 0) {
-        F2TailArgs ta{};
-        ta.kind = F2_MATMUL;
-        ta.v = tm;
-        ta.src[0] = ta.dst[0] = Ta;
-        ta.src[1] = ta.dst[1] = Tb;
-        ta.rho = rho + 2 * jm;
-        ta.part = p_mm + (size_t)jm * pstride;
-        launch_f2_tail(ta, s);
-    }
-    {
-        F2FinishArgs fa{};
-        fa.kind = F2_MATMUL;
-        fa.v = lm;
-        fa.part = p_mm;
-        fa.ev = ev_mm;
-        fa.t[0] = Ta;
-        fa.t[1] = Tb;
-        fa.fin = tr;
-        launch_f2_finish(fa, s);
-    }
     // the claims at (r1, r2)
     launch_f2_outer(E1, E2, lk, N, EQ, s);
     launch_f2_claims(EQ, d_R, d_Rm, d_Y, d_Z, N, cpart, s);
@@ -1248,89 +1212,61 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
         pa.range_sum = tr + 14;
         launch_f2_planes(pa, s);
     }
-    // rounds over x of the range instance (tables EQ, Bx), then the ReLU zero-check (EQ, D, S)
-    const int tx = std::min(lN, kF2TailLog), jx = lN - tx;
-    for (int j = 0; j < jx; j++) {
-        F2RoundArgs ra{};
-        ra.kind = F2_RANGE;
-        ra.first = j == 0;
-        ra.h = N >> (j + 1);
-        ra.src[0] = j == 0 ? EQ : EQr;
-        ra.dst[0] = EQr;
-        ra.src[1] = ra.dst[1] = Bx;
-        ra.rho = sig + 2 * (lP + j);
-        ra.cst = cst;
-        ra.part = p_rs + (size_t)j * pstride;
-        launch_f2_round(ra, s);
-    }
-    if (tx > 0) {
-        F2TailArgs ta{};
-        ta.kind = F2_RANGE;
-        ta.first = jx == 0;
-        ta.v = tx;
-        ta.src[0] = jx == 0 ? EQ : EQr;
-        ta.dst[0] = EQr;
-        ta.src[1] = ta.dst[1] = Bx;
-        ta.rho = sig + 2 * (lP + jx);
-        ta.cst = cst;
-        ta.part = p_rs + (size_t)jx * pstride;
-        launch_f2_tail(ta, s);
-    }
-    {
-        F2FinishArgs fa{};
-        fa.kind = F2_RANGE;
-        fa.v = lN;
-        fa.part = p_rs;
-        fa.ev = ev_rs + 8 * (size_t)lP;
-        fa.t[0] = EQr;
-        fa.t[1] = Bx;
-        fa.fin = tr + 16;
-        launch_f2_finish(fa, s);
-    }
-    if (relu) {
-        for (int j = 0; j < jx; j++) {
-            F2RoundArgs ra{};
-            ra.kind = F2_RELU;
-            ra.first = j == 0;
-            ra.h = N >> (j + 1);
-            ra.src[0] = j == 0 ? EQ : EQz;
-            ra.dst[0] = EQz;
-            ra.src[1] = ra.dst[1] = Dt;
-            ra.src[2] = ra.dst[2] = St;
-            ra.R = d_R;
-            ra.Y = d_Y;
-            ra.rho = rho2 + 2 * j;
-            ra.part = p_zc + (size_t)j * pstride;
-            launch_f2_round(ra, s);
+    // the rounds over tables: the passes of the matrix instance, those of the
+    // range and the ReLU instance side by side, then what is left in one launch
+    struct Inst {
+        int kind, v;
+        F2Tab t[2];
+        const uint64_t *rho;
+        uint64_t *part, *ev, *out;
+    };
+    const int pm = f2_passes(lm), px = f2_passes(lN);
+    const Inst mm{F2_MATMUL, lm, {Ta, Tb}, rho, part, ev_mm, tr};
+    const Inst rs{F2_RANGE, lN, {Bx, Bx}, sig + 2 * lP, mm.part + (size_t)pm * kF2PassPart, ev_rs + 8 * (size_t)lP, tr + 16};
+    const Inst zc{F2_RELU, lN, {Dt, St}, rho2, rs.part + (size_t)px * kF2PassPart, ev_zc, tr + 18};
+    auto pass_args = [&](const Inst &x, int p) {
+        F2PassArgs pa{};
+        pa.kind = x.kind;
+        pa.n = 1ull << (x.v - 2 * p - 2);
+        for (int q = 0; q < 2; q++) pa.src[q] = pa.dst[q] = x.t[q];
+        if (x.kind == F2_RELU && p == 0) {
+            pa.R = d_R;
+            pa.Y = d_Y;
         }
-        if (tx > 0) {
-            F2TailArgs ta{};
-            ta.kind = F2_RELU;
-            ta.first = jx == 0;
-            ta.v = tx;
-            ta.src[0] = jx == 0 ? EQ : EQz;
-            ta.dst[0] = EQz;
-            ta.src[1] = ta.dst[1] = Dt;
-            ta.src[2] = ta.dst[2] = St;
+        pa.HS = HS;
+        pa.LS = LS;
+        pa.r = r1 + 4 * p;
+        pa.rho = x.rho + 4 * p;
+        pa.part = x.part + (size_t)p * kF2PassPart;
+        return pa;
+    };
+    auto tail_args = [&](const Inst &x) {
+        F2TailArgs ta{};
+        const int p = f2_passes(x.v);
+        ta.v = x.v - 2 * p;
+        ta.j0 = 2 * p;
+        ta.n0 = p ? 1ull << (x.v - 2) : 0;
+        for (int q = 0; q < 2; q++) ta.src[q] = x.t[q];
+        if (x.kind == F2_RELU && p == 0) {
             ta.R = d_R;
             ta.Y = d_Y;
-            ta.rho = rho2 + 2 * jx;
-            ta.part = p_zc + (size_t)jx * pstride;
-            launch_f2_tail(ta, s);
         }
-        F2FinishArgs fa{};
-        fa.kind = F2_RELU;
-        fa.v = lN;
-        fa.part = p_zc;
-        fa.ev = ev_zc;
-        fa.t[0] = EQz;
-        fa.t[1] = Dt;
-        fa.t[2] = St;
-        fa.fin = tr + 18;
-        fa.R = d_R;
-        fa.Y = d_Y;
-        launch_f2_finish(fa, s);
+        ta.LS = LS;
+        ta.r = r1;
+        ta.rho = x.rho;
+        ta.cst = cst;
+        ta.part = x.part;
+        ta.ev = x.ev;
+        ta.out = x.out;
+        return ta;
+    };
+    for (int p = 0; p < pm; p++) launch_f2_pass(pass_args(mm, p), nullptr, s);
+    for (int p = 0; p < px; p++) {
+        const F2PassArgs z = pass_args(zc, p);
+        launch_f2_pass(pass_args(rs, p), relu ? &z : nullptr, s);
     }
+    const F2TailArgs tz = tail_args(zc);
+    launch_f2_tails(tail_args(mm), tail_args(rs), relu ? &tz : nullptr, s);
     RA_HIP(hipGetLastError());
     // the transcript and the witness status into the context's pinned area
     // (nothing else is pending there: the call drained on entry)

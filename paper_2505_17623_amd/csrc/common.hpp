@@ -299,40 +299,36 @@ __host__ __device__ inline int f2_blocks(uint64_t h)
     const uint64_t b = (h + 255) / 256;
     return (int)(b < (uint64_t)kF2MaxBlocks ? (b ? b : 1) : kF2MaxBlocks);
 }
-// one round over tables of 2h entries: src -> dst (equal but for the first
-// round of the range / ReLU instances); rho and cst point at pairs (re, im)
-struct F2RoundArgs {
-    int kind, first;
-    uint64_t h;
-    F2Tab src[3], dst[3];
-    const int32_t *R, *Y;  // ReLU first round: D = R - Y, S = R + Y
-    const uint64_t *rho;
-    const uint64_t *cst;   // range: c_eq, c_w
-    uint64_t *part;        // f2_blocks(h) x 8 words
+constexpr int kF2TailLog = 11;      // the last rounds, over at most 2^11 entries
+constexpr int kF2TailThreads = 512;
+constexpr int kF2PassPart = 20 * kF2MaxBlocks;  // words of a pass's partials (two rounds, ten words each)
+struct f2;
+// Two rounds over tables of 4n entries, folded to n (given challenges).
+struct F2PassArgs {
+    int kind;
+    uint64_t n;
+    F2Tab src[2], dst[2];      // B; D, S; a, b
+    const int32_t *R, *Y;      // ReLU: D, S are read from these instead (null: from src)
+    const f2 *HS, *LS;         // suffix eq tables (launch_f2_eqs)
+    const uint64_t *r, *rho;   // the two rounds' variables of (r1, r2) and challenges (pairs)
+    uint64_t *part;            // word q of round b and block x at (10 b + q) kF2MaxBlocks + x
 };
-// the last v rounds (v <= kF2TailLog) of an instance, from its round j0 on,
-// in one workgroup: src -> dst as in F2RoundArgs (first: j0 == 0); rho: the
-// challenges of rounds j0 .. j0 + v - 1; part: round j0's partial slots
-constexpr int kF2TailLog = 10;
+void launch_f2_pass(const F2PassArgs &a, const F2PassArgs *relu, hipStream_t st);  // relu: that instance beside the range one
+// The values of rounds 0 .. j0 - 1 from the passes' partials, rounds j0 ..
+// j0 + v - 1 from the tables (2^v entries), and the final values.
 struct F2TailArgs {
-    int kind, first, v;
-    F2Tab src[3], dst[3];
-    const int32_t *R, *Y;
-    const uint64_t *rho;
-    const uint64_t *cst;
-    uint64_t *part;
+    int v, j0;
+    uint64_t n0;               // the first pass's n
+    F2Tab src[2];
+    const int32_t *R, *Y;      // as F2PassArgs
+    const f2 *LS;
+    const uint64_t *r, *rho;   // (r1, r2) and the instance's challenges (pairs)
+    const uint64_t *cst;       // range: c_eq, c_w
+    const uint64_t *part;      // kF2PassPart words per pass
+    uint64_t *ev;              // round j's values at ev + 2 (D + 1) j
+    uint64_t *out;             // matrix c0, a*, b*; range b~(sigma); ReLU R~, Y~
 };
-void launch_f2_tail(const F2TailArgs &a, hipStream_t st);
-// the evaluations of an instance's v rounds (partials of round j at part +
-// j kF2MaxBlocks 8) and its final words
-struct F2FinishArgs {
-    int kind, v;
-    const uint64_t *part;
-    uint64_t *ev;
-    F2Tab t[3];
-    uint64_t *fin;
-    const int32_t *R, *Y;  // ReLU with no rounds (one output): D, S from R, Y
-};
+void launch_f2_tails(const F2TailArgs &mm, const F2TailArgs &rs, const F2TailArgs *zc, hipStream_t st);
 struct F2PlaneArgs {
     const uint64_t *G_re, *G_im;      // 64 x 64
     const uint64_t *tau, *sig, *lam;  // pairs: tau_p, sigma_p, (lambda1, lambda2, lambda3, mu)
@@ -352,8 +348,6 @@ void launch_f2_outer(F2Tab E1, F2Tab E2, int lk, uint64_t N, F2Tab out, hipStrea
 void launch_f2_claims(F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y, const int32_t *Z, uint64_t N,
                       uint64_t *part, hipStream_t st);
 void launch_f2_sum8(const uint64_t *part, int nb, uint64_t *out, hipStream_t st);
-void launch_f2_round(const F2RoundArgs &a, hipStream_t st);
-void launch_f2_finish(const F2FinishArgs &a, hipStream_t st);
 void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st);
 void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
                         uint64_t *G_im, hipStream_t st);
@@ -404,7 +398,7 @@ struct FsPassArgs {
     const uint64_t *bits;      // range, first pass: the bit words, with eq(sigma_p, .) (64 entries)
     F2Tab sig;
     int tabs;                  // bytes of a bit word that can hold set bits
-    const struct f2 *HS, *LS;  // suffix eq tables (f2.hpp)
+    const f2 *HS, *LS;  // suffix eq tables (f2.hpp)
     uint64_t *part;
     FsFinArgs fin;
 };
@@ -416,7 +410,7 @@ struct FsTailArgs {
     const uint64_t *bits;
     F2Tab sig;
     int tabs;
-    const struct f2 *LS;
+    const f2 *LS;
     const uint64_t *r;         // (r1, r2), pairs
     const uint64_t *cst;
     uint64_t *ev;              // round j's values at ev + 2 (D + 1) j
@@ -428,7 +422,7 @@ struct FsTailArgs {
 void launch_fs_tail(const FsTailArgs &a, hipStream_t st);
 // The eq tables of (r1, r2) = r (lN pairs): E1 (2^ln), E2 (2^lk) and the
 // suffix tables LS (2^(low + 1) entries, low = min(lN, kF2Low)) and HS (2^(lN - low + 1)).
-void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, struct f2 *HS, struct f2 *LS, hipStream_t st);
+void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st);
 void launch_fill0(uint64_t *p, uint64_t n, hipStream_t st);
 
 // ---- the gather link between layers (link.hip) ----

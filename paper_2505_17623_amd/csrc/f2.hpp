@@ -215,6 +215,13 @@ __device__ __forceinline__ void relu_ints(const int32_t *R, const int32_t *Y, ui
     s = m61::from_i64(r + y);
 }
 
+// lo + r (hi - lo) for lo, hi in F_p
+__device__ __forceinline__ f2 fold_real(uint64_t lo, uint64_t hi, f2 r)
+{
+    const uint64_t d = m61::lsub(hi, lo);
+    return f2{m61::lmacc(lo, r.re, d), m61::lmul(r.im, d)};
+}
+
 // The sums of eq(sigma_p, q) over the set bits q of a byte, for each byte of a
 // bit word: tab[t][e], byte t (256 threads; tabs bytes, sig: 64 entries in
 // LDS).  A word's plane-bound value is then one lookup and add per byte.

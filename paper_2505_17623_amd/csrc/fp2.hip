@@ -7,17 +7,16 @@
 // The witness (C, R, Rm, Y, Z, the bit table) is integer-valued and is made
 // by the F_p kernels.  Everything that depends on a challenge is an element
 // of F_{p^2}, held as two F_p tables (real and imaginary parts, "SoA"):
-//   - the eq tables E1 = eq(r1, .), E2 = eq(r2, .) and EQ(x) = E1 E2;
+//   - the eq tables E1 = eq(r1, .), E2 = eq(r2, .) and, for the claims and the
+//     Gram pass, EQ(x) = E1 E2;
 //   - the bound sides of the product (an integer table bound at a point of
 //     F_{p^2} is the pair of its F_p bindings with the eq table's two parts,
 //     so the F_p binding kernels serve);
 //   - the plane rounds' Gram matrix G = sum_x EQ(x) bit bit^T, whose two
 //     parts the F_p Gram pass computes from EQ's two parts;
 //   - every folded table of the rounds.
-// Rounds run one launch per round (a pass over the pairs that evaluates the
-// round polynomial and folds the tables in place) while the tables are
-// large, and the last rounds of an instance in one workgroup over LDS; this
-// is slower than the F_p path's fused passes.
+#include <algorithm>
+
 #include "common.hpp"
 #include "f2.hpp"
 #include "gram_reduce.hpp"
@@ -169,231 +168,223 @@ void launch_f2_sum8(const uint64_t *part, int nb, uint64_t *out, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------
-// One round of a sum-check instance over tables of 2h entries (Sec. II-D):
-// for every pair (i, i + h) the summand at X = 0..3 (each table is lo +
-// X (hi - lo) there), summed per block, and the fold T[i] <- lo + rho
-// (hi - lo) into the destination tables.  Summands:
-//   F2_MATMUL  a b                                  (tables a, b; degree 2)
-//   F2_RANGE   EQ B (c_eq (B - 1) + c_w)            (tables EQ, B; degree 3),
-//              the range summand once the plane variables are bound:
-//              c_eq = eq(tau_p, sigma_p), c_w = mu W~(sigma_p)
-//   F2_RELU    EQ D S, D = R - Y, S = R + Y         (Eq. (6); degree 3)
-// The first round of the ReLU instance reads R, Y (int32) for D, S.
+// The rounds over tables with given challenges (Sec. II-D; eq factored, see
+// F2Sums): the matrix instance, the range instance once its plane variables
+// are bound, and the ReLU zero-check.
+//
+// While a table holds more than 2^kF2TailLog entries a pass takes two rounds
+// per launch in registers: a thread reads the four entries of a quad, sums
+// both rounds and writes the one entry left, so a table crosses memory 1.25
+// times per two rounds, and the range and the ReLU instance share the launch.
+// Bound by the field products (20 of F_{p^2} per range quad, about 1100 VALU
+// instructions).  One round per launch over tables that carried EQ took 430 us
+// for the two instances of 2^21 and the one of 2^21 without ReLU; this takes
+// 160 (MI355X).
 // ---------------------------------------------------------------------------
-// The summand of one pair at X = 0..3 added into acc, and the folded values
-// lo + rho (hi - lo) into lo.
-template <int KIND>
-__device__ __forceinline__ void f2_pair(f2 (&lo)[3], const f2 (&hi)[3], f2 rho, f2 ceq, f2 cw, f2 (&acc)[4])
+template <int KIND, bool INTS>
+__device__ __forceinline__ void f2_pass(const F2PassArgs &a, uint64_t *red, uint64_t *tot)
 {
-    constexpr int NT = KIND == F2_RELU ? 3 : 2;
-    f2 v[3], d[3];
-#pragma unroll
-    for (int q = 0; q < NT; q++) {
-        v[q] = lo[q];
-        d[q] = f2sub(hi[q], lo[q]);
-    }
-#pragma unroll
-    for (int X = 0; X < 4; X++) {
-        if (X > 0)
-#pragma unroll
-            for (int q = 0; q < NT; q++) v[q] = f2add(v[q], d[q]);  // the tables at X
-        f2 f;
-        if (KIND == F2_MATMUL) {
-            if (X == 3) break;
-            f = f2mul(v[0], v[1]);
-        } else if (KIND == F2_RANGE) {
-            f = f2mul(f2mul(v[0], v[1]), f2add(f2mul(ceq, f2sub(v[1], f2of(1))), cw));
-        } else {
-            f = f2mul(f2mul(v[0], v[1]), v[2]);
+    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2;
+    const f2 rho0 = ldp(a.rho), rho1 = ldp(a.rho + 2);
+    f2 r1 = f2of(0);
+    if (KIND != F2_MATMUL) r1 = ldp(a.r + 2);  // the second round's variable
+    const f2 nr1 = f2sub(f2of(1), r1);
+    F2Sums<KIND> s0, s1;
+    const uint64_t n = a.n, first = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint64_t i = first; i < n; i += (uint64_t)f2_blocks(n) * blockDim.x) {
+        // weights: the high variables here (the same for the whole workgroup), the low ones at the end;
+        // the first round's pairs (x0, x2), (x1, x3) carry the second variable's factors
+        f2 w = f2of(1), w0 = f2of(1), w1 = f2of(1);
+        if (KIND != F2_MATMUL) {
+            w = a.HS[(n >> kF2Low ? n >> kF2Low : 1) + (i >> kF2Low)];
+            w0 = l2mul(w, nr1);
+            w1 = l2sub(w, w0);
         }
-        acc[X] = f2add(acc[X], f);
-    }
+        f2 y[2][2];
+        if (INTS) {
+            uint64_t d[4], s[4];
 #pragma unroll
-    for (int q = 0; q < NT; q++) lo[q] = f2add(lo[q], f2mul(rho, d[q]));
-}
-
-// The ReLU instance's first round reads D = R - Y and S = R + Y from the
-// integer tables.
-__device__ __forceinline__ void f2_relu_ints(const int32_t *R, const int32_t *Y, uint64_t i, f2 &d, f2 &s)
-{
-    const int64_t r = R[i], y = Y[i];
-    d = f2of(m61::from_i64(r - y));
-    s = f2of(m61::from_i64(r + y));
-}
-
-template <int KIND>
-__global__ __launch_bounds__(256) void k_f2_round(F2RoundArgs a)
-{
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    constexpr int NT = KIND == F2_RELU ? 3 : 2;
-    const f2 rho = ldp(a.rho);
-    f2 ceq = f2of(0), cw = f2of(0);
-    if (KIND == F2_RANGE) {
-        ceq = ldp(a.cst);
-        cw = ldp(a.cst + 2);
-    }
-    f2 acc[4] = {f2of(0), f2of(0), f2of(0), f2of(0)};
-    const uint64_t h = a.h;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < h; i += (uint64_t)gridDim.x * blockDim.x) {
-        f2 lo[3], hi[3];
-        lo[0] = ldt(a.src[0], i);
-        hi[0] = ldt(a.src[0], i + h);
-        if (KIND == F2_RELU && a.first) {
-            f2_relu_ints(a.R, a.Y, i, lo[1], lo[2]);
-            f2_relu_ints(a.R, a.Y, i + h, hi[1], hi[2]);
+            for (int t = 0; t < 4; t++) relu_ints(a.R, a.Y, i + t * n, d[t], s[t]);
+            if constexpr (KIND == F2_RELU) {
+                s0.add_int(w0, d[0], d[2], s[0], s[2]);
+                s0.add_int(w1, d[1], d[3], s[1], s[3]);
+            }
+            y[0][0] = fold_real(d[0], d[2], rho0);
+            y[0][1] = fold_real(d[1], d[3], rho0);
+            y[1][0] = fold_real(s[0], s[2], rho0);
+            y[1][1] = fold_real(s[1], s[3], rho0);
         } else {
+            f2 x[NT][4];
 #pragma unroll
-            for (int q = 1; q < NT; q++) {
-                lo[q] = ldt(a.src[q], i);
-                hi[q] = ldt(a.src[q], i + h);
+            for (int q = 0; q < NT; q++)
+#pragma unroll
+                for (int t = 0; t < 4; t++) x[q][t] = ldt(a.src[q], i + t * n);
+            if constexpr (KIND == F2_MATMUL) {
+                s0.add(x[0][0], x[0][2], x[NT - 1][0], x[NT - 1][2]);
+                s0.add(x[0][1], x[0][3], x[NT - 1][1], x[NT - 1][3]);
+            } else {
+                s0.add(l2mul(w0, x[0][0]), l2mul(w0, x[0][2]), x[NT - 1][0], x[NT - 1][2]);
+                s0.add(l2mul(w1, x[0][1]), l2mul(w1, x[0][3]), x[NT - 1][1], x[NT - 1][3]);
+            }
+#pragma unroll
+            for (int q = 0; q < NT; q++)
+#pragma unroll
+                for (int t = 0; t < 2; t++) y[q][t] = l2fold(x[q][t], x[q][t + 2], rho0);
+        }
+        if constexpr (KIND == F2_MATMUL) s1.add(y[0][0], y[0][1], y[NT - 1][0], y[NT - 1][1]);
+        else s1.add(l2mul(w, y[0][0]), l2mul(w, y[0][1]), y[NT - 1][0], y[NT - 1][1]);
+#pragma unroll
+        for (int q = 0; q < NT; q++) stt(a.dst[q], i, l2fold(y[q][0], y[q][1], rho1));
+    }
+    f2 w = f2of(1);
+    if (KIND != F2_MATMUL) {
+        const uint32_t low = n < (1u << kF2Low) ? (uint32_t)n : 1u << kF2Low;
+        w = a.LS[low + (uint32_t)(first & (low - 1))];
+    }
+    uint64_t v[NW];
+    s0.words(v, KIND != F2_MATMUL, w);
+    f2_totals<NW>(v, red, tot, blockDim.x);
+    if (threadIdx.x < NW) a.part[(size_t)threadIdx.x * kF2MaxBlocks + blockIdx.x] = tot[threadIdx.x];
+    s1.words(v, KIND != F2_MATMUL, w);
+    f2_totals<NW>(v, red, tot, blockDim.x);
+    if (threadIdx.x < NW) a.part[(size_t)(10 + threadIdx.x) * kF2MaxBlocks + blockIdx.x] = tot[threadIdx.x];
+}
+
+template <int KIND> __global__ __launch_bounds__(256) void k_f2_pass(F2PassArgs a)
+{
+    __shared__ uint64_t red[10 * 256], tot[10];
+    f2_pass<KIND, false>(a, red, tot);
+}
+
+// The range and the ReLU instance side by side.
+template <bool INTS> __global__ __launch_bounds__(256) void k_f2_pass_both(F2PassArgs range, F2PassArgs relu)
+{
+    __shared__ uint64_t red[10 * 256], tot[10];
+    if (blockIdx.y == 0) f2_pass<F2_RANGE, false>(range, red, tot);
+    else f2_pass<F2_RELU, INTS>(relu, red, tot);
+}
+
+void launch_f2_pass(const F2PassArgs &a, const F2PassArgs *relu, hipStream_t st)
+{
+    const dim3 grid(f2_blocks(a.n), relu ? 2 : 1), blk(kThreads);
+    if (relu && relu->R) hipLaunchKernelGGL(k_f2_pass_both<true>, grid, blk, 0, st, a, *relu);
+    else if (relu) hipLaunchKernelGGL(k_f2_pass_both<false>, grid, blk, 0, st, a, *relu);
+    else if (a.kind == F2_RANGE) hipLaunchKernelGGL(k_f2_pass<F2_RANGE>, grid, blk, 0, st, a);
+    else hipLaunchKernelGGL(k_f2_pass<F2_MATMUL>, grid, blk, 0, st, a);
+}
+
+// ---------------------------------------------------------------------------
+// The last v <= kF2TailLog rounds of every instance, all rounds' values and
+// the final values, in one launch.  The challenges are known, so the rounds
+// need not wait for each other: workgroup c folds the table c times in LDS
+// (each half the work of the one before) and sums round c alone; the rounds
+// of the passes have a workgroup each too, which sums their partials.  (All
+// rounds of an instance in one workgroup took 53 us.)
+// ---------------------------------------------------------------------------
+struct F2TailLds {
+    f2 T[2][1 << kF2TailLog], g[4], K;
+    uint64_t red[10 * kF2TailThreads], tot[10];
+};
+
+template <int KIND> __device__ __forceinline__ void f2_tail(const F2TailArgs &a, F2TailLds &s)
+{
+    constexpr int NW = f2_sum_words(KIND), NT = KIND == F2_RANGE ? 1 : 2, D1 = KIND == F2_MATMUL ? 3 : 4;
+    const int tid = threadIdx.x, rounds = a.j0 + a.v, j = blockIdx.x;  // this workgroup's round; j = rounds: the final values
+    if (j > rounds) return;
+    if (tid < 64) {  // K_j
+        f2 k = f2of(1);
+        if (KIND != F2_MATMUL && tid < j && j < rounds) k = eq1z(ldp(a.r + 2 * tid), ldp(a.rho + 2 * tid));
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) k = l2mul(k, f2{__shfl_xor(k.re, off, 64), __shfl_xor(k.im, off, 64)});
+        if (tid == 0) s.K = l2canon(k);
+    }
+    if (j < a.j0) {  // a pass's round
+        const uint64_t *part = a.part + (size_t)(j >> 1) * kF2PassPart + (size_t)(j & 1) * 10 * kF2MaxBlocks;
+        const int nb = f2_blocks(a.n0 >> (j & ~1)), lane = tid & 63;
+        for (int q = tid >> 6; q < NW; q += blockDim.x >> 6) {
+            uint64_t v = 0;
+            for (int b = lane; b < nb; b += 64) v = m61::fold(v + part[(size_t)q * kF2MaxBlocks + b]);
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) v = m61::fold(v + __shfl_xor(v, off, 64));
+            if (lane == 0) s.tot[q] = m61::canon(v);
+        }
+        __syncthreads();
+    } else {
+        const int c = j - a.j0;
+        int n = 1 << a.v;  // entries
+        for (int i = tid; i < n; i += blockDim.x)
+#pragma unroll
+            for (int q = 0; q < NT; q++) {
+                f2 x;
+                if (KIND == F2_RELU && a.R) {
+                    const int64_t r = a.R[i], y = a.Y[i];
+                    x = f2of(m61::from_i64(q == 0 ? r - y : r + y));
+                } else {
+                    x = ldt(a.src[q], i);
+                }
+                s.T[q][i] = x;
+            }
+        __syncthreads();
+        for (int b = 0; b < c; b++) {  // an entry's two sources are read by its own thread only
+            const f2 rho = ldp(a.rho + 2 * (a.j0 + b));
+            n >>= 1;
+            for (int i = tid; i < n; i += blockDim.x)
+#pragma unroll
+                for (int q = 0; q < NT; q++) s.T[q][i] = l2fold(s.T[q][i], s.T[q][i + n], rho);
+            __syncthreads();
+        }
+        if (j == rounds) {
+            constexpr uint64_t inv2 = 1ull << 60;  // 2 2^60 = 2^61 = 1 mod p
+            if (tid != 0) return;
+            const f2 x = l2canon(s.T[0][0]), y = l2canon(s.T[NT - 1][0]);
+            if (KIND == F2_MATMUL) {  // a*, b*, and with no rounds c0 = a b
+                if (rounds == 0) stp(a.out, f2mul(x, y));
+                stp(a.out + 2, x);
+                stp(a.out + 4, y);
+            } else if (KIND == F2_RANGE) {
+                stp(a.out, x);
+            } else {  // R~ = (D + S) / 2, Y~ = (S - D) / 2
+                stp(a.out, f2scale(f2add(x, y), inv2));
+                stp(a.out + 2, f2scale(f2sub(y, x), inv2));
+            }
+            return;
+        }
+        const int h = n >> 1;
+        F2Sums<KIND> acc;
+        for (int i = tid; i < h; i += blockDim.x) {
+            if constexpr (KIND == F2_MATMUL) {
+                acc.add(s.T[0][i], s.T[0][i + h], s.T[NT - 1][i], s.T[NT - 1][i + h]);
+            } else {
+                const f2 w = a.LS[h + i];
+                acc.add(l2mul(w, s.T[0][i]), l2mul(w, s.T[0][i + h]), s.T[NT - 1][i], s.T[NT - 1][i + h]);
             }
         }
-        f2_pair<KIND>(lo, hi, rho, ceq, cw, acc);
-#pragma unroll
-        for (int q = 0; q < NT; q++) stt(a.dst[q], i, lo[q]);
+        uint64_t v[NW];
+        acc.words(v, false, f2of(1));
+        f2_totals<NW>(v, s.red, s.tot, h < 64 ? 64 : (h < kF2TailThreads ? h : kF2TailThreads));
     }
-    f2_block_out(acc, red, a.part + 8 * (size_t)blockIdx.x);
-}
-
-// ---------------------------------------------------------------------------
-// The last v <= kF2TailLog rounds of an instance in one workgroup: the tables
-// (2^v entries) are staged in LDS and folded there, round after round; each
-// round's sums go to its first partial slot (the round's other slots are
-// zeroed, so the finish kernel reads the same layout as after k_f2_round),
-// and the final values to index 0 of the destination tables.
-// ---------------------------------------------------------------------------
-template <int KIND>
-__global__ __launch_bounds__(256) void k_f2_tail(F2TailArgs a)
-{
-    constexpr int NT = KIND == F2_RELU ? 3 : 2, S = 1 << kF2TailLog;
-    __shared__ uint64_t T[NT][2][S];  // (re, im) of each table
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    __shared__ uint64_t rz[2 * kF2TailLog];
-    const int tid = threadIdx.x, n0 = 1 << a.v;
-    f2 ceq = f2of(0), cw = f2of(0);
-    if (KIND == F2_RANGE) {
-        ceq = ldp(a.cst);
-        cw = ldp(a.cst + 2);
-    }
-    if (tid < 2 * a.v) rz[tid] = a.rho[tid];
-    for (int i = tid; i < n0; i += blockDim.x) {
-        f2 t[3];
-        t[0] = ldt(a.src[0], i);
-        if (KIND == F2_RELU && a.first) {
-            f2_relu_ints(a.R, a.Y, i, t[1], t[2]);
-        } else {
-#pragma unroll
-            for (int q = 1; q < NT; q++) t[q] = ldt(a.src[q], i);
-        }
-#pragma unroll
-        for (int q = 0; q < NT; q++) {
-            T[q][0][i] = t[q].re;
-            T[q][1][i] = t[q].im;
-        }
+    if (tid < D1) {
+        const f2 r = KIND == F2_MATMUL ? f2of(0) : ldp(a.r + 2 * j);
+        const f2 g = f2_round_value(KIND, s.tot, tid, s.K, r, a.cst);
+        stp(a.ev + 2 * (D1 * j + tid), g);
+        s.g[tid] = g;
     }
     __syncthreads();
-    for (int c = 0; c < a.v; c++) {
-        const int h = n0 >> (c + 1);
-        const f2 rho{rz[2 * c], rz[2 * c + 1]};
-        f2 acc[4] = {f2of(0), f2of(0), f2of(0), f2of(0)};
-        // a pair's entries are read and its fold written by one thread only
-        for (int i = tid; i < h; i += blockDim.x) {
-            f2 lo[3], hi[3];
-#pragma unroll
-            for (int q = 0; q < NT; q++) {
-                lo[q] = f2{T[q][0][i], T[q][1][i]};
-                hi[q] = f2{T[q][0][i + h], T[q][1][i + h]};
-            }
-            f2_pair<KIND>(lo, hi, rho, ceq, cw, acc);
-#pragma unroll
-            for (int q = 0; q < NT; q++) {
-                T[q][0][i] = lo[q].re;
-                T[q][1][i] = lo[q].im;
-            }
-        }
-        uint64_t *part = a.part + (size_t)c * kF2MaxBlocks * 8;
-        const int nb = f2_blocks((uint64_t)h);
-        if (tid >= 1 && tid < nb)
-#pragma unroll
-            for (int q = 0; q < 8; q++) part[8 * tid + q] = 0;
-        f2_block_out(acc, red, part);  // its barriers also order this round's folds before the next reads
-        __syncthreads();
-    }
-    if (tid == 0)
-#pragma unroll
-        for (int q = 0; q < NT; q++) stt(a.dst[q], 0, f2{T[q][0][0], T[q][1][0]});
+    if (KIND == F2_MATMUL && j == 0 && tid == 0) stp(a.out, f2add(s.g[0], s.g[1]));  // c0 = g_1(0) + g_1(1)
 }
 
-void launch_f2_tail(const F2TailArgs &a, hipStream_t st)
+__global__ __launch_bounds__(kF2TailThreads) void k_f2_tails(F2TailArgs mm, F2TailArgs rs, F2TailArgs zc)
 {
-    switch (a.kind) {
-    case F2_MATMUL: hipLaunchKernelGGL(k_f2_tail<F2_MATMUL>, dim3(1), dim3(kThreads), 0, st, a); break;
-    case F2_RANGE: hipLaunchKernelGGL(k_f2_tail<F2_RANGE>, dim3(1), dim3(kThreads), 0, st, a); break;
-    default: hipLaunchKernelGGL(k_f2_tail<F2_RELU>, dim3(1), dim3(kThreads), 0, st, a); break;
-    }
+    __shared__ F2TailLds s;
+    if (blockIdx.y == 0) f2_tail<F2_MATMUL>(mm, s);
+    else if (blockIdx.y == 1) f2_tail<F2_RANGE>(rs, s);
+    else f2_tail<F2_RELU>(zc, s);
 }
 
-void launch_f2_round(const F2RoundArgs &a, hipStream_t st)
+void launch_f2_tails(const F2TailArgs &mm, const F2TailArgs &rs, const F2TailArgs *zc, hipStream_t st)
 {
-    const dim3 grid(f2_blocks(a.h));
-    switch (a.kind) {
-    case F2_MATMUL: hipLaunchKernelGGL(k_f2_round<F2_MATMUL>, grid, dim3(kThreads), 0, st, a); break;
-    case F2_RANGE: hipLaunchKernelGGL(k_f2_round<F2_RANGE>, grid, dim3(kThreads), 0, st, a); break;
-    default: hipLaunchKernelGGL(k_f2_round<F2_RELU>, grid, dim3(kThreads), 0, st, a); break;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The rounds' evaluations from the blocks' partials (one workgroup per
-// round: round j of an instance over 2^v entries had f2_blocks(2^(v-1-j))
-// blocks), written as pairs, D + 1 per round; workgroup 0 also writes the
-// instance's final words:
-//   F2_MATMUL  c0 = g_1(0) + g_1(1) (a b with no rounds), a*, b*
-//   F2_RANGE   b~(sigma)
-//   F2_RELU    R~(rho') = (D + S) / 2, Y~(rho') = (S - D) / 2
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_f2_finish(F2FinishArgs a)
-{
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    const int j = blockIdx.x, D = a.kind == F2_MATMUL ? 2 : 3;
-    uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (j < a.v) {
-        const int nb = f2_blocks(1ull << (a.v - 1 - j));
-        const uint64_t *p = a.part + (size_t)j * kF2MaxBlocks * 8;
-        for (int b = threadIdx.x; b < nb; b += blockDim.x)
-#pragma unroll
-            for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], p[8 * (size_t)b + q]);
-        m61::block_sum<8>(v, red);
-        if (threadIdx.x == 0)
-            for (int q = 0; q < 2 * (D + 1); q++) a.ev[2 * (D + 1) * j + q] = v[q];
-    }
-    if (j != 0 || threadIdx.x != 0) return;
-    if (a.kind == F2_MATMUL) {
-        const f2 t0 = ldt(a.t[0], 0), t1 = ldt(a.t[1], 0);
-        const f2 c0 = a.v > 0 ? f2add(f2{v[0], v[1]}, f2{v[2], v[3]}) : f2mul(t0, t1);
-        stp(a.fin, c0);
-        stp(a.fin + 2, t0);
-        stp(a.fin + 4, t1);
-    } else if (a.kind == F2_RANGE) {
-        stp(a.fin, ldt(a.t[1], 0));
-    } else {
-        f2 Dv, Sv;
-        if (a.v > 0) {
-            Dv = ldt(a.t[1], 0);
-            Sv = ldt(a.t[2], 0);
-        } else {
-            Dv = f2of(m61::from_i64((int64_t)a.R[0] - a.Y[0]));
-            Sv = f2of(m61::from_i64((int64_t)a.R[0] + a.Y[0]));
-        }
-        constexpr uint64_t inv2 = 1ull << 60;  // 2 2^60 = 2^61 = 1 mod p
-        stp(a.fin, f2scale(f2add(Dv, Sv), inv2));
-        stp(a.fin + 2, f2scale(f2sub(Sv, Dv), inv2));
-    }
-}
-
-void launch_f2_finish(const F2FinishArgs &a, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_f2_finish, dim3(a.v > 0 ? a.v : 1), dim3(kThreads), 0, st, a);
+    const int x = 1 + std::max(mm.j0 + mm.v, rs.j0 + rs.v);
+    hipLaunchKernelGGL(k_f2_tails, dim3(x, zc ? 3 : 2), dim3(kF2TailThreads), 0, st, mm, rs, zc ? *zc : F2TailArgs{});
 }
 
 // ---------------------------------------------------------------------------

@@ -289,13 +289,6 @@ __device__ __forceinline__ f2 fs_finish_prev(FsFinLds &l, const FsFinArgs &a, bo
 // words (range: Bx formed from them and written).
 enum { FS_FIELD = 0, FS_INTS = 1, FS_BITS = 2 };
 
-// lo + r (hi - lo) for lo, hi in F_p
-__device__ __forceinline__ f2 fold_real(uint64_t lo, uint64_t hi, f2 r)
-{
-    const uint64_t d = m61::lsub(hi, lo);
-    return f2{m61::lmacc(lo, r.re, d), m61::lmul(r.im, d)};
-}
-
 template <int KIND, int SRC, bool FOLD>
 __global__ __launch_bounds__(256) void k_fs_pass(FsPassArgs a)
 {

@@ -85,6 +85,18 @@ SHAPES = [
 ]
 
 
+# the rounds' launches: every table within 2^11 entries, one pass of two rounds before that (2^12), two (2^14, the
+# second reading the first one's tables), with and without ReLU, and the matrix instance's (m = 4096, 16384)
+PASS_SHAPES = [(32, 4, 64, 7, True, 0, 300), (64, 4, 64, 7, True, 0, 300), (64, 2, 128, 7, False, 0, 300),
+               (128, 2, 128, 7, True, 1, 300), (1, 2, 8192, 7, True, 0, 300), (2, 4096, 4, 9, True, 0, 64),
+               (1, 16384, 2, 9, False, 0, 64)]
+
+
+@pytest.mark.parametrize("n,m,k,s,relu,mode,mag", PASS_SHAPES)
+def test_fp2_round_passes(ra, n, m, k, s, relu, mode, mag):
+    test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag)
+
+
 @pytest.mark.parametrize("n,m,k,s,relu,mode,mag", SHAPES)
 def test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag):
     rng = np.random.default_rng(n * 131 + m * 7 + k)
