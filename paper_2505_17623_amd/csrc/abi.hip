@@ -451,7 +451,7 @@ RangeLayout range_layout(uint64_t N, int lP, int relu)
 // range rounds (8 each, for up to 6 + log N) and the ReLU rounds (8 each).
 constexpr int kF2TrFixed = 22;
 struct Fp2Layout {
-    size_t o_gemm, o_e1, o_e2, o_scr, o_a, o_b, o_eq, o_bx, o_d, o_s, o_sig, o_one, o_gp0, o_gp1, o_g,
+    size_t o_gemm, o_e1, o_e2, o_scr, o_a, o_b, o_eq, o_bx, o_d, o_s, o_sig, o_gp0, o_gp1, o_g,
         o_part, o_cpart, o_cst, o_tr, tr_words, o_hs, o_ls, o_fsch, o_fsk, o_fst, o_dig0, o_dig1, o_root, o_err, bytes;
 };
 // leaves of the witness tables' Merkle tree (R, Rm, Y, Z int32 / uint16, the bit words)
@@ -472,7 +472,7 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_gemm = cv.take<char>(gemm_workspace_bytes(a_i32, n, m, k));
     l.o_e1 = cv.take<uint64_t>(2 * (size_t)n);
     l.o_e2 = cv.take<uint64_t>(2 * (size_t)k);
-    l.o_scr = cv.take<uint64_t>((size_t)bind_rows_chunks(n, m) * m);
+    l.o_scr = cv.take<uint64_t>(2 * (size_t)bind_rows_chunks(n, m) * m);
     l.o_a = cv.take<uint64_t>(2 * (size_t)m);
     l.o_b = cv.take<uint64_t>(2 * (size_t)m);
     l.o_eq = cv.take<uint64_t>(2 * N);
@@ -480,7 +480,6 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_d = cv.take<uint64_t>(2 * H);
     l.o_s = cv.take<uint64_t>(2 * H);
     l.o_sig = cv.take<uint64_t>(2 * 64);
-    l.o_one = cv.take<uint64_t>(2);
     l.o_gp0 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_gp1 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_g = cv.take<uint64_t>(2 * 4096);
@@ -1130,7 +1129,7 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     const uint64_t H = N > 1 ? N / 2 : 1;
     const F2Tab E1 = tab(L.o_e1, n), E2 = tab(L.o_e2, k), Ta = tab(L.o_a, m), Tb = tab(L.o_b, m);
     const F2Tab EQ = tab(L.o_eq, N), Bx = tab(L.o_bx, N);
-    const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64), ONE = tab(L.o_one, 1);
+    const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64);
     uint64_t *scr = (uint64_t *)(ws + L.o_scr), *part = (uint64_t *)(ws + L.o_part);
     uint64_t *cpart = (uint64_t *)(ws + L.o_cpart), *cst = (uint64_t *)(ws + L.o_cst);
     uint64_t *tr = (uint64_t *)(ws + L.o_tr), *Gre = (uint64_t *)(ws + L.o_g), *Gim = Gre + 4096;
@@ -1149,11 +1148,15 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
         hp.mode = (int)io->round_mode;
         hp.t_in = t;
     } else {
+        size_t off = 0;
+        if ((st = stage_take(c, 8, &off)) != RA_OK) return st;
         launch_witness_params(d_C, N, (int)io->s, relu, (int)io->round_mode, -1, (int64_t *)(c->d_wit + kWitMinMax),
-                              c->d_params, s);
-        WitParams got;
-        RA_HIP(hipMemcpyAsync(&got, c->d_params, sizeof(got), hipMemcpyDeviceToHost, s));
+                              c->d_params, s, (WitParams *)(c->d_stage + off));
+        RA_HIP(hipGetLastError());
         RA_HIP(hipStreamSynchronize(s));
+        WitParams got;
+        std::memcpy(&got, c->h_stage + off, sizeof(got));
+        c->stage_used = 0;
         if (got.status != 0) return got.status;
         t = got.t;
         P = got.P;
@@ -1166,34 +1169,28 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     const uint64_t *tau = lam + 8, *sig = tau + 2 * lP, *rho2 = sig + 2 * (lP + lN);
 
     f2 *HS = (f2 *)(ws + L.o_hs), *LS = (f2 *)(ws + L.o_ls);
-    launch_f2_eqs(r1, ln, lk, E1, E2, HS, LS, s);
-    // R, Rm, Y, Z, the bit table (the F_p claims this pass also forms are not used)
-    launch_witness_rescale(d_C, N, lk, E1.re, E2.re, d_R, d_Rm, d_Y, d_Z, d_bits, (uint64_t *)(c->d_wit + kWitClaims),
-                           c->d_params, c->d_claims, nullptr, s, io->t >= 0 ? &hp : nullptr,
-                           (uint32_t *)(c->d_wit + kWitFlags), nullptr);
+    launch_f2_eqs(r1, ln, lk, E1, E2, HS, LS, s, sig, lP, SIG);
+    // R, Rm, Y, Z, the bit table (no claims over F_p)
+    ClaimsJob wit{};
+    launch_witness_rescale(d_C, N, lk, nullptr, nullptr, d_R, d_Rm, d_Y, d_Z, d_bits, nullptr, c->d_params, nullptr,
+                           nullptr, s, io->t >= 0 ? &hp : nullptr, (uint32_t *)(c->d_wit + kWitFlags), &wit);
 
-    // matrix instance: a = the rows of A bound at r1, b = the columns of B at
-    // r2 (two F_p bindings each), log m rounds
-    launch_bind_rows(d_A, a_dtype, n, m, E1.re, scr, Ta.re, s);
-    launch_bind_rows(d_A, a_dtype, n, m, E1.im, scr, Ta.im, s);
-    launch_bind_cols(d_B, RA_I16, m, k, E2.re, Tb.re, s);
-    launch_bind_cols(d_B, RA_I16, m, k, E2.im, Tb.im, s);
+    // matrix instance: a = the rows of A bound at r1, b = the columns of B at r2
+    launch_f2_bind(d_A, a_dtype, d_B, n, m, k, E1, E2, scr, Ta, Tb, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
-    // the claims at (r1, r2)
-    launch_f2_outer(E1, E2, lk, N, EQ, s);
-    launch_f2_claims(EQ, d_R, d_Rm, d_Y, d_Z, N, cpart, s);
-    launch_f2_sum8(cpart, f2_blocks(N), tr + 6, s);
+    // the claims at (r1, r2), as partials
+    launch_f2_claims(E1, E2, lk, EQ, d_R, d_Rm, d_Y, relu, N, cpart, s);
     // plane rounds: the Gram matrix's two parts from EQ's two parts (the F_p
-    // Gram pass with EQ as its row table and a one-entry column table), and
-    // the plane-bound table Bx with the two parts of eq(sigma_p, .)
-    launch_f2_eq(sig, lP, SIG, s);
-    launch_f2_eq(sig, 0, ONE, s);
+    // Gram pass with EQ as its row table and a column table of one entry, 1,
+    // which the suffix tables hold), and the plane-bound table Bx with the two
+    // parts of eq(sigma_p, .), in one launch
     const int pused = (int)io->s + (t + 2) * (relu ? 2 : 1);  // planes the witness writes
     const int gt = plane_gram_tiles(lP, pused), gb = plane_gram_blocks(N, lP);
     uint64_t *gp0 = (uint64_t *)(ws + L.o_gp0), *gp1 = (uint64_t *)(ws + L.o_gp1);
-    launch_plane_gram(lP, d_bits, N, 0, EQ.re, ONE.re, sig, Bx.re, gp0, nullptr, s, SIG.re, pused);
-    launch_plane_gram(lP, d_bits, N, 0, EQ.im, ONE.re, sig, Bx.im, gp1, nullptr, s, SIG.im, pused);
-    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, s);
+    const GramPair gpair{N, 64, N, (uint64_t)(gp1 - gp0)};
+    launch_plane_gram(lP, d_bits, N, 0, EQ.re, (const uint64_t *)(ws + L.o_ls) + 2, sig, Bx.re, gp0, nullptr, s, SIG.re,
+                      pused, &gpair);
+    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, cpart, f2_blocks(N), tr + 6, s);
     {
         F2PlaneArgs pa{};
         pa.G_re = Gre;
@@ -1270,12 +1267,11 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
     RA_HIP(hipGetLastError());
     // the transcript and the witness status into the context's pinned area
     // (nothing else is pending there: the call drained on entry)
-    const size_t prm_words = (sizeof(WitParams) + 7) / 8;
     size_t off = 0;
-    if ((st = stage_take(c, L.tr_words + prm_words, &off)) != RA_OK) return st;
+    if ((st = stage_take(c, L.tr_words + 9, &off)) != RA_OK) return st;
     const uint64_t *h = c->h_stage + off;
-    RA_HIP(hipMemcpyAsync(c->h_stage + off, tr, L.tr_words * 8, hipMemcpyDeviceToHost, s));
-    RA_HIP(hipMemcpyAsync(c->h_stage + off + L.tr_words, c->d_params, sizeof(WitParams), hipMemcpyDeviceToHost, s));
+    launch_f2_publish(F2Publish{tr, (int)L.tr_words, wit, nullptr, nullptr, c->d_stage + off}, s);
+    RA_HIP(hipGetLastError());
     RA_HIP(hipStreamSynchronize(s));
     WitParams prm;
     std::memcpy(&prm, h + L.tr_words, sizeof(prm));
@@ -1344,7 +1340,7 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     const uint64_t H = N > 1 ? N / 2 : 1;
     const F2Tab E1 = tab(L.o_e1, n), E2 = tab(L.o_e2, k), Ta = tab(L.o_a, m), Tb = tab(L.o_b, m);
     const F2Tab EQ = tab(L.o_eq, N), Bx = tab(L.o_bx, N);
-    const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64), ONE = tab(L.o_one, 1);
+    const F2Tab Dt = tab(L.o_d, H), St = tab(L.o_s, H), SIG = tab(L.o_sig, 64);
     uint64_t *scr = (uint64_t *)(ws + L.o_scr), *part = (uint64_t *)(ws + L.o_part);
     uint64_t *cpart = (uint64_t *)(ws + L.o_cpart), *cst = (uint64_t *)(ws + L.o_cst);
     uint64_t *tr = (uint64_t *)(ws + L.o_tr), *Gre = (uint64_t *)(ws + L.o_g), *Gim = Gre + 4096;
@@ -1353,8 +1349,7 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     uint8_t *root = (uint8_t *)(ws + L.o_root);
 
     // the witness: the exact product, t and P, then R, Rm, Y, Z and the bit
-    // table (the F_p claims that pass also forms are not used: its eq tables
-    // are zero here)
+    // table (no claims over F_p)
     launch_gemm_mfma(d_A, a_dtype == RA_I32, d_B, d_C, n, m, k, ws + L.o_gemm, s, nullptr, nullptr, false, nullptr);
     int P = 0, lP = 0, t = io->t;
     WitParams hp{};
@@ -1369,22 +1364,23 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
         hp.mode = (int)io->round_mode;
         hp.t_in = t;
     } else {
+        size_t off = 0;
+        if ((st = stage_take(c, 8, &off)) != RA_OK) return st;
         launch_witness_params(d_C, N, (int)io->s, relu, (int)io->round_mode, -1, (int64_t *)(c->d_wit + kWitMinMax),
-                              c->d_params, s);
-        WitParams got;
-        RA_HIP(hipMemcpyAsync(&got, c->d_params, sizeof(got), hipMemcpyDeviceToHost, s));
+                              c->d_params, s, (WitParams *)(c->d_stage + off));
+        RA_HIP(hipGetLastError());
         RA_HIP(hipStreamSynchronize(s));
+        WitParams got;
+        std::memcpy(&got, c->h_stage + off, sizeof(got));
+        c->stage_used = 0;
         if (got.status != 0) return got.status;
         t = got.t;
         P = got.P;
         lP = got.lP;
     }
-    launch_fill0(E1.re, n, s);
-    launch_fill0(E2.re, k, s);
-    launch_fill0((uint64_t *)err, 1, s);
-    launch_witness_rescale(d_C, N, lk, E1.re, E2.re, d_R, d_Rm, d_Y, d_Z, d_bits, (uint64_t *)(c->d_wit + kWitClaims),
-                           c->d_params, c->d_claims, nullptr, s, io->t >= 0 ? &hp : nullptr,
-                           (uint32_t *)(c->d_wit + kWitFlags), nullptr);
+    ClaimsJob wit{};
+    launch_witness_rescale(d_C, N, lk, nullptr, nullptr, d_R, d_Rm, d_Y, d_Z, d_bits, nullptr, c->d_params, nullptr,
+                           nullptr, s, io->t >= 0 ? &hp : nullptr, (uint32_t *)(c->d_wit + kWitFlags), &wit);
     // the witness bound into the transcript before any challenge: its Merkle
     // root with the layer header and the caller's public digest; r1, r2
     MerkleArgs ma{};
@@ -1472,27 +1468,22 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     };
 
     // matrix instance: A's rows bound at r1, B's columns at r2; a*, b* absorbed at its end
-    launch_bind_rows(d_A, a_dtype, n, m, E1.re, scr, Ta.re, s);
-    launch_bind_rows(d_A, a_dtype, n, m, E1.im, scr, Ta.im, s);
-    launch_bind_cols(d_B, RA_I16, m, k, E2.re, Tb.re, s);
-    launch_bind_cols(d_B, RA_I16, m, k, E2.im, Tb.im, s);
+    launch_f2_bind(d_A, a_dtype, d_B, n, m, k, E1, E2, scr, Ta, Tb, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
     instance(F2_MATMUL, lm, Ta, Tb, Ta, Tb, ev_mm, tr);
     // the claims at (r1, r2) absorbed; lambda, mu, tau_p drawn
-    launch_f2_outer(E1, E2, lk, N, EQ, s);
-    launch_f2_claims(EQ, d_R, d_Rm, d_Y, d_Z, N, cpart, s);
+    launch_f2_claims(E1, E2, lk, EQ, d_R, d_Rm, d_Y, relu, N, cpart, s);
     launch_fs_claims(cpart, f2_blocks(N), tr + 6, c->d_fs, lam, 4 + lP, err, s);
-    // plane rounds: the Gram matrix's two parts (their pass's plane-bound
-    // output is not used: sigma_p does not exist yet), then the rounds, which
-    // draw sigma_p as they go
-    launch_fill0(SIG.re, 64, s);
-    launch_f2_eq(lam, 0, ONE, s);
+    // plane rounds: the Gram matrix's two parts in one launch (no plane-bound
+    // table: sigma_p does not exist yet), then the rounds, which draw sigma_p as
+    // they go
     const int pused = (int)io->s + (t + 2) * (relu ? 2 : 1);  // planes the witness writes
     const int gt = plane_gram_tiles(lP, pused), gb = plane_gram_blocks(N, lP);
     uint64_t *gp0 = (uint64_t *)(ws + L.o_gp0), *gp1 = (uint64_t *)(ws + L.o_gp1);
-    launch_plane_gram(lP, d_bits, N, 0, EQ.re, ONE.re, SIG.re, Bx.re, gp0, nullptr, s, SIG.re, pused);
-    launch_plane_gram(lP, d_bits, N, 0, EQ.im, ONE.re, SIG.re, Bx.im, gp1, nullptr, s, SIG.re, pused);
-    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, s);
+    const GramPair gpair{N, 0, 0, (uint64_t)(gp1 - gp0)};
+    launch_plane_gram(lP, d_bits, N, 0, EQ.re, (const uint64_t *)(ws + L.o_ls) + 2, nullptr, nullptr, gp0, nullptr, s,
+                      nullptr, pused, &gpair);
+    launch_f2_gram_sum(gp0, gp1, gb, gt, Gre, Gim, nullptr, 0, nullptr, s);
     {
         F2PlaneArgs pa{};
         pa.G_re = Gre;
@@ -1521,23 +1512,19 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     RA_HIP(hipGetLastError());
     // the transcript, the witness status, the transcript status and the root
     // into the context's pinned area (nothing else is pending there)
-    const size_t prm_words = (sizeof(WitParams) + 7) / 8;
     size_t off = 0;
-    if ((st = stage_take(c, L.tr_words + prm_words + 5, &off)) != RA_OK) return st;
+    if ((st = stage_take(c, L.tr_words + 13, &off)) != RA_OK) return st;
     uint64_t *h = c->h_stage + off;
-    RA_HIP(hipMemcpyAsync(h, tr, L.tr_words * 8, hipMemcpyDeviceToHost, s));
-    RA_HIP(hipMemcpyAsync(h + L.tr_words, c->d_params, sizeof(WitParams), hipMemcpyDeviceToHost, s));
-    RA_HIP(hipMemcpyAsync(h + L.tr_words + prm_words, err, 4, hipMemcpyDeviceToHost, s));
-    RA_HIP(hipMemcpyAsync(h + L.tr_words + prm_words + 1, root, 32, hipMemcpyDeviceToHost, s));
+    launch_f2_publish(F2Publish{tr, (int)L.tr_words, wit, err, (const uint32_t *)root, c->d_stage + off}, s);
+    RA_HIP(hipGetLastError());
     RA_HIP(hipStreamSynchronize(s));
     WitParams prm;
     std::memcpy(&prm, h + L.tr_words, sizeof(prm));
-    uint32_t e = 0;
-    std::memcpy(&e, h + L.tr_words + prm_words, 4);
+    const uint64_t e = h[L.tr_words + 8];
     c->stage_used = 0;
     if (prm.status != 0) return prm.status;  // a given t that does not hold R
     if (e) return RA_E_INVAL;                // a transcript message longer than the pending area
-    if (root_out) std::memcpy(root_out, h + L.tr_words + prm_words + 1, 32);
+    if (root_out) std::memcpy(root_out, h + L.tr_words + 9, 32);
     auto pr = [&](size_t o) { return ra_fp2{h[o], h[o + 1]}; };
     io->t = t;
     io->P = (uint32_t)P;

@@ -140,7 +140,7 @@ void launch_bind_cols(const void *T, int dtype, uint32_t rows, uint32_t cols, co
                       hipStream_t st, const ChunkSum *cs = nullptr);
 int witness_blocks(uint64_t N);
 void launch_witness_params(const int64_t *C, uint64_t N, int s, int relu, int mode, int t_in, int64_t *mm_part,
-                           WitParams *params, hipStream_t st);
+                           WitParams *params, hipStream_t st, WitParams *mirror = nullptr);
 // mirror (optional): 12 words, the parameters (words 0-7) and the claims (8-11).
 // known (optional): parameters computed on the host for a given t (status 0);
 // then no params pass runs before, the range of R is checked here (flags:
@@ -343,14 +343,29 @@ struct F2PlaneArgs {
     F2Tab sig_tab{nullptr, nullptr};  // optional, out: eq(sigma_p, .), zero past P (64 entries)
     uint32_t *err = nullptr;
 };
-void launch_f2_eq(const uint64_t *z, int v, F2Tab out, hipStream_t st);
-void launch_f2_outer(F2Tab E1, F2Tab E2, int lk, uint64_t N, F2Tab out, hipStream_t st);
-void launch_f2_claims(F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y, const int32_t *Z, uint64_t N,
-                      uint64_t *part, hipStream_t st);
-void launch_f2_sum8(const uint64_t *part, int nb, uint64_t *out, hipStream_t st);
-void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st);
+// The row binding of A (n x m, int16 / int32) at E1 and the column binding of
+// B (m x k) at E2 into Ta, Tb (contiguous re, im); scr: 2 m bind_rows_chunks words.
+void launch_f2_bind(const void *A, int a_dtype, const int16_t *B, uint32_t n, uint32_t m, uint32_t k, F2Tab E1,
+                    F2Tab E2, uint64_t *scr, F2Tab Ta, F2Tab Tb, hipStream_t st);
+// EQ = E1 (x) E2 and the claims R~, Rm~, Y~, Z~ as partials, eight words per block (f2_blocks(N)).
+void launch_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y,
+                      int relu, uint64_t N, uint64_t *part, hipStream_t st);
+// The Gram matrix's two parts from the partial tiles, and (claims given) the claims' totals.
 void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
-                        uint64_t *G_im, hipStream_t st);
+                        uint64_t *G_im, const uint64_t *cpart, int cblocks, uint64_t *claims, hipStream_t st);
+// A proof's end: nw transcript words, the witness parameters (8 words, with
+// the status from the rescale pass's range flags when t was given), the
+// transcript's status and the Merkle root (4 words; Fiat-Shamir) to mapped
+// host memory.
+struct F2Publish {
+    const uint64_t *tr;
+    int nw;
+    ClaimsJob wit;
+    const uint32_t *err, *root;
+    uint64_t *dst;
+};
+void launch_f2_publish(const F2Publish &a, hipStream_t st);
+void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st);
 
 // ---- the non-interactive layer proof (fs.hip) ----
 struct MerkleSeg {
@@ -370,8 +385,6 @@ struct FsHeader {
 };
 void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *root, uint64_t *out, int ndraw,
                       uint32_t *err, hipStream_t st);
-void launch_fs_absorb_draw(sha::Transcript *fs, const uint64_t *w, int nw, uint64_t *out, int ndraw, uint32_t *err,
-                           hipStream_t st);
 void launch_fs_claims(const uint64_t *part, int nb, uint64_t *out8, sha::Transcript *fs, uint64_t *out, int ndraw,
                       uint32_t *err, hipStream_t st);
 constexpr int kFsTailLog = 11;       // the last rounds, over at most 2^11 entries, run in one workgroup
@@ -422,7 +435,9 @@ struct FsTailArgs {
 void launch_fs_tail(const FsTailArgs &a, hipStream_t st);
 // The eq tables of (r1, r2) = r (lN pairs): E1 (2^ln), E2 (2^lk) and the
 // suffix tables LS (2^(low + 1) entries, low = min(lN, kF2Low)) and HS (2^(lN - low + 1)).
-void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st);
+// sig (optional): eq(sig, .) of lP variables to SIG, zero past 2^lP (64 entries).
+void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st,
+                   const uint64_t *sig = nullptr, int lP = 0, F2Tab SIG = F2Tab{});
 void launch_fill0(uint64_t *p, uint64_t n, hipStream_t st);
 
 // ---- the gather link between layers (link.hip) ----
@@ -468,9 +483,14 @@ int plane_gram_set_up_threads(uint64_t N, int lP);
 // plane_gram_set_up_threads), the pass also runs the set-up of the rounds
 // over x, which depends on challenges only.
 // eqs (optional): the P values eq(sigma_p, q) given instead of computed from sig.
+// Bx null: not written (then sig may be null with eqs given).  pair (optional): a second pass over the same bits
+// in the launch, its tables that many words further on (with eqs).
+struct GramPair {
+    uint64_t e1, eqs, bx, gpart;
+};
 void launch_plane_gram(int lP, const uint64_t *bits, uint64_t N, int lk, const uint64_t *E1, const uint64_t *E2,
                        const uint64_t *sig, uint64_t *Bx, uint64_t *gpart, const XSetupArgs *xs, hipStream_t st,
-                       const uint64_t *eqs = nullptr, int pused = 64);
+                       const uint64_t *eqs = nullptr, int pused = 64, const GramPair *pair = nullptr);
 // the Gram matrix G (gsum: 64 x 64 words, both triangles) from the partial
 // tiles; further workgroups run the set-up of the range check (rc, xs)
 void launch_gram_reduce(int lP, uint64_t N, const uint64_t *gpart, uint64_t *gsum, const RangeConsts &rc,

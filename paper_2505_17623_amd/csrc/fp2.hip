@@ -20,58 +20,31 @@
 #include "common.hpp"
 #include "f2.hpp"
 #include "gram_reduce.hpp"
+#include "ra.h"
 #include "fs_device.hpp"
 #include "sha256.hpp"
 
 namespace ra {
 
-// Block sum of the eight words of four F_{p^2} values; thread 0 writes them.
-__device__ __forceinline__ void f2_block_out(const f2 (&acc)[4], uint64_t *red, uint64_t *out)
-{
-    uint64_t v[8];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        v[2 * q] = acc[q].re;
-        v[2 * q + 1] = acc[q].im;
-    }
-    m61::block_sum<8>(v, red);
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int q = 0; q < 8; q++) out[q] = v[q];
-}
-
-// ---------------------------------------------------------------------------
-// eq tables (Eq. (1)) of points of F_{p^2}: the point is v challenges stored
-// as pairs (re, im); the table goes to two F_p arrays.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_f2_eq(const uint64_t *__restrict__ z, int v, F2Tab out)
-{
-    __shared__ f2 zl[64];
-    if ((int)threadIdx.x < v) zl[threadIdx.x] = ldp(z + 2 * threadIdx.x);
-    __syncthreads();
-    const uint64_t n = 1ull << v;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        f2 acc = f2of(1);
-        for (int j = 0; j < v; j++) acc = f2mul(acc, eq1b(zl[j], (int)((i >> (v - 1 - j)) & 1)));
-        stt(out, i, acc);
-    }
-}
-
-void launch_f2_eq(const uint64_t *z, int v, F2Tab out, hipStream_t st)
-{
-    const uint64_t n = 1ull << v;
-    const int nb = (int)((n + kThreads - 1) / kThreads < 1024 ? (n + kThreads - 1) / kThreads : 1024);
-    hipLaunchKernelGGL(k_f2_eq, dim3(nb), dim3(kThreads), 0, st, z, v, out);
-}
-
 // The eq tables of a layer in one launch: segments E1, E2 (SoA), LS, HS
 // (f2.hpp; heaps, entry 2^k + y), each entry the product of its variables'
 // factors.
 __global__ __launch_bounds__(256) void k_f2_eqs(const uint64_t *__restrict__ r, int ln, int lk, F2Tab E1, F2Tab E2,
-                                                f2 *__restrict__ HS, f2 *__restrict__ LS)
+                                                f2 *__restrict__ HS, f2 *__restrict__ LS,
+                                                const uint64_t *__restrict__ sig, int lP, F2Tab SIG)
 {
     __shared__ f2 z[64];
     const int lN = ln + lk, low = lN < kF2Low ? lN : kF2Low, hs = lN - low;
+    if (sig && blockIdx.x == gridDim.x - 1) {  // eq(sig, .)
+        if ((int)threadIdx.x < lP) z[threadIdx.x] = ldp(sig + 2 * threadIdx.x);
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            f2 e = f2of((int)threadIdx.x < (1 << lP) ? 1 : 0);
+            for (int j = 0; j < lP; j++) e = l2mul(e, eq1b(z[j], (int)((threadIdx.x >> (lP - 1 - j)) & 1)));
+            stt(SIG, threadIdx.x, l2canon(e));
+        }
+        return;
+    }
     if ((int)threadIdx.x < lN) z[threadIdx.x] = ldp(r + 2 * threadIdx.x);
     __syncthreads();
     const uint64_t n = 1ull << ln, k = 1ull << lk, ls = 2ull << low, nh = 2ull << hs;
@@ -103,68 +76,209 @@ __global__ __launch_bounds__(256) void k_f2_eqs(const uint64_t *__restrict__ r, 
     else HS[i - n - k - ls] = e;
 }
 
-void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st)
+void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS, f2 *LS, hipStream_t st,
+                   const uint64_t *sig, int lP, F2Tab SIG)
 {
     const int lN = ln + lk, low = lN < kF2Low ? lN : kF2Low;
     const uint64_t tot = (1ull << ln) + (1ull << lk) + (2ull << low) + (2ull << (lN - low));
-    hipLaunchKernelGGL(k_f2_eqs, dim3((unsigned)((tot + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, r, ln, lk, E1,
-                       E2, HS, LS);
+    hipLaunchKernelGGL(k_f2_eqs, dim3((unsigned)((tot + kThreads - 1) / kThreads) + (sig ? 1 : 0)), dim3(kThreads), 0, st,
+                       r, ln, lk, E1, E2, HS, LS, sig, lP, SIG);
 }
 
-// EQ(x) = E1[x >> lk] E2[x mod 2^lk] for x < N (the eq table of (r1, r2)).
-__global__ __launch_bounds__(256) void k_f2_outer(F2Tab E1, F2Tab E2, int lk, uint64_t N, F2Tab out)
+// ---------------------------------------------------------------------------
+// The bound sides of the product.  Binding an integer table at a point of
+// F_{p^2} is linear in the eq table, so one pass over the table sums both
+// parts: an eq value is cut into limbs (31 bits for int16 entries, 21 for
+// int32) whose products with the entries add up exactly in int64 over a
+// bounded run of entries, and each run is reduced mod p once.  Two F_p
+// bindings per side read each table twice and took six launches; the two
+// sides of a 512 x 4096 by 4096 x 4096 layer went from 46 to 32 us.
+// ---------------------------------------------------------------------------
+template <typename T> struct BindLimbs;
+template <> struct BindLimbs<int16_t> {
+    static constexpr int kBits = 31, kCount = 2, kRun = 1 << 15;  // |limb entry| < 2^46: 2^15 terms below 2^61
+};
+template <> struct BindLimbs<int32_t> {
+    static constexpr int kBits = 21, kCount = 3, kRun = 1 << 9;  // 2^52
+};
+template <int BITS, int CNT> __device__ __forceinline__ uint64_t limbs_value(const int64_t (&a)[CNT])
 {
-    const uint64_t mask = (1ull << lk) - 1;
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N; x += (uint64_t)gridDim.x * blockDim.x)
-        stt(out, x, f2mul(ldt(E1, x >> lk), ldt(E2, x & mask)));
+    uint64_t v = 0;
+#pragma unroll
+    for (int i = 0; i < CNT; i++) v = m61::add(v, m61::rotl(m61::from_i64(a[i]), BITS * i));
+    return v;
 }
 
-void launch_f2_outer(F2Tab E1, F2Tab E2, int lk, uint64_t N, F2Tab out, hipStream_t st)
+// part[chunk][2 cols]: the sums over a chunk's rows, real parts then imaginary
+template <typename T>
+__global__ __launch_bounds__(256) void k_f2_bind_rows(const T *__restrict__ A, uint32_t rows, uint32_t cols, F2Tab E,
+                                                      uint32_t per_chunk, uint64_t *__restrict__ part)
 {
-    hipLaunchKernelGGL(k_f2_outer, dim3(f2_blocks(N)), dim3(kThreads), 0, st, E1, E2, lk, N, out);
-}
-
-// The claims R~, Rm~, Y~, Z~ at (r1, r2): sum_x EQ(x) v(x), per-block
-// partials (eight words per block).
-__global__ __launch_bounds__(256) void k_f2_claims(F2Tab EQ, const int32_t *__restrict__ R,
-                                                   const uint16_t *__restrict__ Rm, const int32_t *__restrict__ Y,
-                                                   const int32_t *__restrict__ Z, uint64_t N, uint64_t *part)
-{
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    f2 acc[4] = {f2of(0), f2of(0), f2of(0), f2of(0)};
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N; x += (uint64_t)gridDim.x * blockDim.x) {
-        const f2 e = ldt(EQ, x);
-        acc[0] = f2add(acc[0], f2small(e, R[x]));
-        acc[1] = f2add(acc[1], f2small(e, (int32_t)Rm[x]));
-        acc[2] = f2add(acc[2], f2small(e, Y[x]));
-        acc[3] = f2add(acc[3], f2small(e, Z[x]));
+    using L = BindLimbs<T>;
+    __shared__ uint64_t red[4][2][64];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t c = blockIdx.x * 64 + lane;
+    const uint32_t r0 = blockIdx.y * per_chunk;
+    const uint32_t r1 = r0 + per_chunk < rows ? r0 + per_chunk : rows;
+    uint64_t re = 0, im = 0;
+    for (uint32_t b = r0 + wid; b < r1; b += 4 * L::kRun) {  // a wave's run: rows b, b + 4, ..
+        const uint64_t e1 = (uint64_t)b + 4ull * L::kRun;
+        const uint32_t e = e1 < r1 ? (uint32_t)e1 : r1;
+        int64_t sr[L::kCount] = {}, si[L::kCount] = {};
+#pragma unroll 4
+        for (uint32_t r = b; r < e; r += 4) {
+            const int32_t z = c < cols ? (int32_t)A[(size_t)r * cols + c] : 0;
+            const uint64_t x = E.re[r], y = E.im[r];
+#pragma unroll
+            for (int i = 0; i < L::kCount; i++) {
+                sr[i] += (int64_t)(int32_t)((x >> (L::kBits * i)) & ((1u << L::kBits) - 1)) * z;
+                si[i] += (int64_t)(int32_t)((y >> (L::kBits * i)) & ((1u << L::kBits) - 1)) * z;
+            }
+        }
+        re = m61::add(re, limbs_value<L::kBits>(sr));
+        im = m61::add(im, limbs_value<L::kBits>(si));
     }
-    f2_block_out(acc, red, part + 8 * (size_t)blockIdx.x);
+    red[wid][0][lane] = re;
+    red[wid][1][lane] = im;
+    __syncthreads();
+    if (wid < 2 && c < cols)
+        part[((size_t)blockIdx.y * 2 + wid) * cols + c] =
+            m61::add(m61::add(red[0][wid][lane], red[1][wid][lane]), m61::add(red[2][wid][lane], red[3][wid][lane]));
 }
 
-void launch_f2_claims(F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y, const int32_t *Z, uint64_t N,
-                      uint64_t *part, hipStream_t st)
+// B's columns, a wave per four rows: lanes take eight consecutive columns (one
+// 16-byte load per row) and read each eq value once for the four rows.
+// Workgroups from nmain on sum the chunks of the row binding (256 of its
+// 2 cols entries each).
+__global__ __launch_bounds__(256) void k_f2_bind_cols(const int16_t *__restrict__ B, uint32_t rows, uint32_t cols,
+                                                      F2Tab E, F2Tab out, uint32_t nmain,
+                                                      const uint64_t *__restrict__ part, int nch, uint32_t acols,
+                                                      uint64_t *__restrict__ aout)
 {
-    hipLaunchKernelGGL(k_f2_claims, dim3(f2_blocks(N)), dim3(kThreads), 0, st, EQ, R, Rm, Y, Z, N, part);
-}
-
-// Sum of nb rows of eight partial words -> out[0..7].
-__global__ __launch_bounds__(256) void k_f2_sum8(const uint64_t *__restrict__ part, int nb, uint64_t *out)
-{
-    __shared__ uint64_t red[m61::block_sum_words(8, 256)];
-    uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nb; b += blockDim.x)
+    if (blockIdx.x >= nmain) {
+        const uint32_t c = (blockIdx.x - nmain) * 256 + threadIdx.x;
+        if (c >= acols) return;
+        uint64_t v = 0;
+#pragma unroll 8
+        for (int q = 0; q < nch; q++) v = m61::fold(v + part[(size_t)q * acols + c]);
+        aout[c] = m61::canon(v);
+        return;
+    }
+    using L = BindLimbs<int16_t>;
+    constexpr int RW = 4;
+    const uint32_t r0 = ((blockIdx.x * blockDim.x + threadIdx.x) >> 6) * RW;  // wave-uniform
+    const int lane = threadIdx.x & 63;
+    if (r0 >= rows) return;
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    f2 acc[RW];
 #pragma unroll
-        for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], part[8 * (size_t)b + q]);
-    m61::block_sum<8>(v, red);
-    if (threadIdx.x == 0)
+    for (int rr = 0; rr < RW; rr++) acc[rr] = f2of(0);
+    for (uint64_t b = 8 * lane; b < cols; b += (uint64_t)512 * (L::kRun / 8)) {  // at most kRun entries per lane
+        int64_t sr[RW][2] = {}, si[RW][2] = {};
+        const uint64_t e = b + (uint64_t)512 * (L::kRun / 8) < cols ? b + (uint64_t)512 * (L::kRun / 8) : cols;
+        for (uint64_t c0 = b; c0 < e; c0 += 512) {
+            int32_t x[8][4];
 #pragma unroll
-        for (int q = 0; q < 8; q++) out[q] = v[q];
+            for (int t = 0; t < 8; t++) {
+                const uint64_t re = E.re[c0 + t], im = E.im[c0 + t];
+                x[t][0] = (int32_t)(re & 0x7FFFFFFFull);
+                x[t][1] = (int32_t)(re >> 31);
+                x[t][2] = (int32_t)(im & 0x7FFFFFFFull);
+                x[t][3] = (int32_t)(im >> 31);
+            }
+#pragma unroll
+            for (int rr = 0; rr < RW; rr++) {
+                if (r0 + rr >= rows) break;
+                const v4i z4 = *(const v4i *)&B[(size_t)(r0 + rr) * cols + c0];
+#pragma unroll
+                for (int t = 0; t < 8; t++) {
+                    const int32_t z = (int32_t)(int16_t)(z4[t >> 1] >> (16 * (t & 1)));
+                    sr[rr][0] += (int64_t)x[t][0] * z;
+                    sr[rr][1] += (int64_t)x[t][1] * z;
+                    si[rr][0] += (int64_t)x[t][2] * z;
+                    si[rr][1] += (int64_t)x[t][3] * z;
+                }
+            }
+        }
+#pragma unroll
+        for (int rr = 0; rr < RW; rr++)
+            acc[rr] = f2add(acc[rr], f2{limbs_value<31>(sr[rr]), limbs_value<31>(si[rr])});
+    }
+#pragma unroll
+    for (int rr = 0; rr < RW; rr++) {
+        f2 v = acc[rr];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) v = l2add(v, f2{__shfl_xor(v.re, off, 64), __shfl_xor(v.im, off, 64)});
+        if (lane == 0 && r0 + rr < rows) stt(out, r0 + rr, l2canon(v));
+    }
 }
 
-void launch_f2_sum8(const uint64_t *part, int nb, uint64_t *out, hipStream_t st)
+void launch_f2_bind(const void *A, int a_dtype, const int16_t *B, uint32_t n, uint32_t m, uint32_t k, F2Tab E1,
+                    F2Tab E2, uint64_t *scr, F2Tab Ta, F2Tab Tb, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f2_sum8, dim3(1), dim3(kThreads), 0, st, part, nb, out);
+    const int nch = bind_rows_chunks(n, m);
+    const uint32_t per = (n + nch - 1) / nch;
+    const dim3 grid((m + 63) / 64, nch);
+    if (a_dtype == RA_I16)
+        hipLaunchKernelGGL(k_f2_bind_rows<int16_t>, grid, dim3(256), 0, st, (const int16_t *)A, n, m, E1, per, scr);
+    else
+        hipLaunchKernelGGL(k_f2_bind_rows<int32_t>, grid, dim3(256), 0, st, (const int32_t *)A, n, m, E1, per, scr);
+    // 16-byte loads of eight columns where B's rows allow them, else the two parts one after the other
+    const bool vec = k >= 8 && ((uintptr_t)B & 15) == 0;
+    const uint32_t nmain = vec ? ((m + 3) / 4 + 3) / 4 : 0, extra = (2 * m + 255) / 256;
+    hipLaunchKernelGGL(k_f2_bind_cols, dim3(nmain + extra), dim3(256), 0, st, B, m, k, E2, Tb, nmain,
+                       (const uint64_t *)scr, nch, 2 * m, Ta.re);
+    if (!vec) {
+        launch_bind_cols(B, RA_I16, m, k, E2.re, Tb.re, st);
+        launch_bind_cols(B, RA_I16, m, k, E2.im, Tb.im, st);
+    }
+}
+
+// EQ(x) = E1[x >> lk] E2[x mod 2^lk] for x < N (the eq table of (r1, r2),
+// folded parts) and, on the way, the claims R~, Rm~, Y~ and Z~ = (R~ + Y~) / 2
+// (ReLU, else R~) at (r1, r2): sum_x EQ(x) v(x) in 21-bit limbs of EQ, exact in
+// int64 over runs of 1024 entries.  Per-block partials, eight words per block.
+__global__ __launch_bounds__(256) void k_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *__restrict__ R,
+                                                   const uint16_t *__restrict__ Rm, const int32_t *__restrict__ Y,
+                                                   int relu, uint64_t N, uint64_t *part)
+{
+    __shared__ uint64_t red[6 * 256], tot[6];
+    const uint64_t mask = (1ull << lk) - 1, stride = (uint64_t)gridDim.x * blockDim.x;
+    uint64_t acc[6] = {0, 0, 0, 0, 0, 0};
+    for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; b < N; b += 1024 * stride) {
+        int64_t s[6][3] = {};
+        const uint64_t e1 = b + 1024 * stride, end = e1 < N ? e1 : N;
+        for (uint64_t x = b; x < end; x += stride) {
+            const int32_t r = R[x], rm = Rm[x], y = Y[x];
+            const f2 e = l2mul(ldt(E1, x >> lk), ldt(E2, x & mask));
+            stt(EQ, x, e);
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                const int32_t a = (int32_t)((e.re >> (21 * i)) & 0x1FFFFF), c = (int32_t)((e.im >> (21 * i)) & 0x1FFFFF);
+                s[0][i] += (int64_t)a * r;
+                s[1][i] += (int64_t)c * r;
+                s[2][i] += (int64_t)a * rm;
+                s[3][i] += (int64_t)c * rm;
+                s[4][i] += (int64_t)a * y;
+                s[5][i] += (int64_t)c * y;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 6; q++) acc[q] = m61::add(acc[q], limbs_value<21>(s[q]));
+    }
+    f2_totals<6>(acc, red, tot, blockDim.x);
+    if (threadIdx.x < 8) {
+        const int p = threadIdx.x & 1;
+        uint64_t v = threadIdx.x < 6 ? tot[threadIdx.x] : tot[p];
+        if (threadIdx.x >= 6 && relu) v = m61::rotl(m61::add(v, tot[4 + p]), 60);  // 1 / 2 = 2^60
+        part[8 * (size_t)blockIdx.x + threadIdx.x] = v;
+    }
+}
+
+void launch_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y,
+                      int relu, uint64_t N, uint64_t *part, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_f2_claims, dim3(f2_blocks(N)), dim3(kThreads), 0, st, E1, E2, lk, EQ, R, Rm, Y, relu, N, part);
 }
 
 // ---------------------------------------------------------------------------
@@ -547,20 +661,58 @@ void launch_f2_planes(const F2PlaneArgs &a, hipStream_t st)
     hipLaunchKernelGGL(k_f2_planes, dim3(1), dim3(kThreads), 0, st, a);
 }
 
-// The Gram matrix's two parts from the partial tiles of their passes.
+// The Gram matrix's two parts from the partial tiles of their passes; the last
+// workgroup in x (part 0) sums the claims' partials.
 __global__ __launch_bounds__(256) void k_f2_gram_sum(const uint64_t *__restrict__ gp_re,
                                                      const uint64_t *__restrict__ gp_im, int nblk, int tiles,
-                                                     uint64_t *__restrict__ G_re, uint64_t *__restrict__ G_im)
+                                                     uint64_t *__restrict__ G_re, uint64_t *__restrict__ G_im,
+                                                     int groups, const uint64_t *__restrict__ cpart, int cblocks,
+                                                     uint64_t *__restrict__ claims)
 {
-    __shared__ uint64_t red[kGramReduceLdsWords];
+    __shared__ uint64_t red[kGramReduceLdsWords > 8 * 256 ? kGramReduceLdsWords : 8 * 256], tot[8];
+    if ((int)blockIdx.x == groups) {
+        if (blockIdx.y) return;
+        uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int b = threadIdx.x; b < cblocks; b += blockDim.x)
+#pragma unroll
+            for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], cpart[8 * (size_t)b + q]);
+        f2_totals<8>(v, red, tot, blockDim.x);
+        if (threadIdx.x < 8) claims[threadIdx.x] = tot[threadIdx.x];
+        return;
+    }
     gram_reduce_block(blockIdx.y ? gp_im : gp_re, nblk, tiles, blockIdx.y ? G_im : G_re, blockIdx.x, red);
 }
 
 void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
-                        uint64_t *G_im, hipStream_t st)
+                        uint64_t *G_im, const uint64_t *cpart, int cblocks, uint64_t *claims, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_f2_gram_sum, dim3(gram_reduce_groups(tiles), 2), dim3(kThreads), 0, st, gp_re, gp_im, nblk,
-                       tiles, G_re, G_im);
+    const int groups = gram_reduce_groups(tiles);
+    hipLaunchKernelGGL(k_f2_gram_sum, dim3(groups + (cpart ? 1 : 0), 2), dim3(kThreads), 0, st, gp_re, gp_im, nblk,
+                       tiles, G_re, G_im, groups, cpart, cblocks, claims);
+}
+
+// The transcript and the statuses to mapped host memory (one launch instead
+// of two to four copies).
+__global__ __launch_bounds__(256) void k_f2_publish(F2Publish a)
+{
+    for (int i = threadIdx.x; i < a.nw; i += blockDim.x) a.dst[i] = a.tr[i];
+    uint64_t *d = a.dst + a.nw;
+    int any = 0;
+    if (a.wit.known)
+        for (int b = threadIdx.x; b < a.wit.nblk; b += blockDim.x) any |= a.wit.flags[b] != 0;
+    any = __syncthreads_or(any);
+    if (threadIdx.x == 0) {
+        WitParams p = a.wit.known ? a.wit.hp : *a.wit.prm;
+        if (any) p.status = RA_E_RANGE;
+        *(WitParams *)d = p;
+        d[8] = a.err ? *a.err : 0;
+    }
+    if (a.root && threadIdx.x >= 64 && threadIdx.x < 72) ((uint32_t *)(d + 9))[threadIdx.x - 64] = a.root[threadIdx.x - 64];
+}
+
+void launch_f2_publish(const F2Publish &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_f2_publish, dim3(1), dim3(kThreads), 0, st, a);
 }
 
 }  // namespace ra

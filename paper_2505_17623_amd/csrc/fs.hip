@@ -162,18 +162,8 @@ __global__ __launch_bounds__(kFsThreads) void k_fs_header(sha::Transcript *fs, F
     fs_pull(f, fs);
     if (tid < 16) msg[tid] = h.words[tid];
     else if (tid < 24) msg[tid] = ((const uint32_t *)root)[tid - 16];
-    if (!fs_absorb(f, msg, 24) && tid == 0) *err = 1;
-    fs_draws(f, out, ndraw);
-    __syncthreads();
-    fs_push(fs, f);
-}
-
-__global__ __launch_bounds__(kFsThreads) void k_fs_absorb_draw(sha::Transcript *fs, const uint64_t *__restrict__ w,
-                                                               int nw, uint64_t *out, int ndraw, uint32_t *err)
-{
-    __shared__ FsLds f;
-    fs_pull(f, fs);
-    if (!fs_absorb(f, (const uint32_t *)w, 2 * nw) && threadIdx.x == 0) *err = 1;
+    const bool ok = fs_absorb(f, msg, 24);
+    if (tid == 0) *err = ok ? 0 : 1;  // the layer's first transcript kernel
     fs_draws(f, out, ndraw);
     __syncthreads();
     fs_push(fs, f);
@@ -183,12 +173,6 @@ void launch_fs_header(sha::Transcript *fs, const FsHeader &h, const uint8_t *roo
                       uint32_t *err, hipStream_t st)
 {
     hipLaunchKernelGGL(k_fs_header, dim3(1), dim3(kFsThreads), 0, st, fs, h, root, out, ndraw, err);
-}
-
-void launch_fs_absorb_draw(sha::Transcript *fs, const uint64_t *w, int nw, uint64_t *out, int ndraw, uint32_t *err,
-                           hipStream_t st)
-{
-    hipLaunchKernelGGL(k_fs_absorb_draw, dim3(1), dim3(kFsThreads), 0, st, fs, w, nw, out, ndraw, err);
 }
 
 // The claims R~, Rm~, Y~, Z~ from their partials (eight words per block),

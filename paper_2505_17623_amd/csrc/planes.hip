@@ -96,8 +96,14 @@ template <int NPL>
 __global__ __launch_bounds__(kGramThreads) void k_plane_gram(
     const uint64_t *__restrict__ bits, uint64_t N, int lk, const uint64_t *__restrict__ E1,
     const uint64_t *__restrict__ E2, const uint64_t *__restrict__ sig, int lP, uint64_t *__restrict__ Bx,
-    uint64_t *__restrict__ gpart, int xs_on, XSetupArgs xs, const uint64_t *__restrict__ eqs)
+    uint64_t *__restrict__ gpart, int xs_on, XSetupArgs xs, const uint64_t *__restrict__ eqs, GramPair pair)
 {
+    if (blockIdx.y) {  // the second of two passes over the same bits
+        E1 += pair.e1;
+        eqs += pair.eqs;
+        if (Bx) Bx += pair.bx;
+        gpart += pair.gpart;
+    }
     using S = GramShape<NPL>;
     constexpr int NB = S::kBlocks, NT = S::kTiles;
     constexpr int kPlaneBytes = NPL * kRow, kTileBytes = NT * kGramTileWords * 8;
@@ -113,7 +119,7 @@ __global__ __launch_bounds__(kGramThreads) void k_plane_gram(
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool producer = wv < kProducers;  // wave-uniform
     const int cw = wv - kProducers;         // consumer index = its digit
-    if (tid < 64) {  // eq(sigma_p, q) for every plane q (or the given values)
+    if (Bx && tid < 64) {  // eq(sigma_p, q) for every plane q (or the given values)
         uint64_t a = 0;
         if (tid < (1 << lP)) {
             if (eqs) {
@@ -162,7 +168,7 @@ __global__ __launch_bounds__(kGramThreads) void k_plane_gram(
     __syncthreads();
     // byte tables of Bx(x) = sum_q eq(sigma_p, q) bit_q(x): lut[b][v] = sum
     // over the set bits i of v of eq(sigma_p, 8 b + i)
-    for (int i = tid; i < 8 * 256; i += kGramThreads) {
+    for (int i = tid; Bx && i < 8 * 256; i += kGramThreads) {
         const int b = i >> 8, v = i & 255;
         uint64_t a = 0;
         for (int k = 0; k < 8; k++)
@@ -180,10 +186,12 @@ __global__ __launch_bounds__(kGramThreads) void k_plane_gram(
                 const bool valid = x < N;
                 const uint64_t w = pw, eqx = m61::lmul(pe1, pe2);  // folded, < 2^61 + 8
                 fetch(i + 1);
-                uint64_t bx = 0;  // eight values below 2^61: the plain sum stays below 2^64
+                if (Bx) {  // uniform
+                    uint64_t bx = 0;  // eight values below 2^61: the plain sum stays below 2^64
 #pragma unroll
-                for (int b = 0; b < 8; b++) bx += s_lut[b * 256 + ((w >> (8 * b)) & 255)];
-                if (valid) Bx[x] = m61::reduce64(bx);
+                    for (int b = 0; b < 8; b++) bx += s_lut[b * 256 + ((w >> (8 * b)) & 255)];
+                    if (valid) Bx[x] = m61::reduce64(bx);
+                }
                 const uint64_t db = balanced_digit_bytes(eqx);
 #pragma unroll
                 for (int t = 0; t < kLimbs; t++) s_d[buf][t][tid] = (int8_t)(db >> (8 * t));
@@ -312,20 +320,21 @@ int plane_gram_blocks(uint64_t N, int lP)
 
 void launch_plane_gram(int lP, const uint64_t *bits, uint64_t N, int lk, const uint64_t *E1, const uint64_t *E2,
                        const uint64_t *sig, uint64_t *Bx, uint64_t *gpart, const XSetupArgs *xs, hipStream_t st,
-                       const uint64_t *eqs, int pused)
+                       const uint64_t *eqs, int pused, const GramPair *pair)
 {
-    const int nb = plane_gram_blocks(N, lP);
+    const dim3 nb(plane_gram_blocks(N, lP), pair ? 2 : 1);
     const XSetupArgs none{};
     const XSetupArgs &x = xs ? *xs : none;
+    const GramPair pr = pair ? *pair : GramPair{};
     if (lP <= 5)
-        hipLaunchKernelGGL(k_plane_gram<32>, dim3(nb), dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
-                           gpart, xs ? 1 : 0, x, eqs);
+        hipLaunchKernelGGL(k_plane_gram<32>, nb, dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
+                           gpart, xs ? 1 : 0, x, eqs, pr);
     else if (plane_gram_tiles(lP, pused) == GramShape<48>::kTiles)  // planes 48 .. 63 are zero
-        hipLaunchKernelGGL(k_plane_gram<48>, dim3(nb), dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
-                           gpart, xs ? 1 : 0, x, eqs);
+        hipLaunchKernelGGL(k_plane_gram<48>, nb, dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
+                           gpart, xs ? 1 : 0, x, eqs, pr);
     else
-        hipLaunchKernelGGL(k_plane_gram<64>, dim3(nb), dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
-                           gpart, xs ? 1 : 0, x, eqs);
+        hipLaunchKernelGGL(k_plane_gram<64>, nb, dim3(kGramThreads), 0, st, bits, N, lk, E1, E2, sig, lP, Bx,
+                           gpart, xs ? 1 : 0, x, eqs, pr);
 }
 
 void launch_gram_reduce(int lP, uint64_t N, const uint64_t *gpart, uint64_t *gsum, const RangeConsts &rc,

@@ -320,7 +320,8 @@ __global__ __launch_bounds__(256) void k_minmax(const int64_t *__restrict__ C, u
 }
 
 __global__ __launch_bounds__(256) void k_wit_params(const int64_t *__restrict__ part, int nblk, int s, int relu,
-                                                    int mode, int t_in, WitParams *__restrict__ prm)
+                                                    int mode, int t_in, WitParams *__restrict__ prm,
+                                                    WitParams *__restrict__ mirror)
 {
     int64_t mn = INT64_MAX, mx = INT64_MIN;
     for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
@@ -362,6 +363,7 @@ __global__ __launch_bounds__(256) void k_wit_params(const int64_t *__restrict__ 
     p.P = P;
     p.lP = lP;
     *prm = p;
+    if (mirror) *mirror = p;
 }
 
 // Pass 2: R, Rm, Y, Z, the bit word and per-block claims, then one block
@@ -420,13 +422,14 @@ __global__ __launch_bounds__(256) void k_rescale(const int64_t *__restrict__ C, 
         } else {
             c[0] = C[x0];
         }
+        if (E1)
 #pragma unroll
-        for (int i = 0; i < V; i++) {
-            const uint64_t x = x0 + i;
-            const uint64_t e = m61::lmul(E1[x >> lk], E2[x & kmask]);
-            el[i] = e & 0x7FFFFFFFull;
-            eh[i] = e >> 31;
-        }
+            for (int i = 0; i < V; i++) {
+                const uint64_t x = x0 + i;
+                const uint64_t e = m61::lmul(E1[x >> lk], E2[x & kmask]);
+                el[i] = e & 0x7FFFFFFFull;
+                eh[i] = e >> 31;
+            }
         int32_t r[V], rm[V], y[V], z[V];
         uint64_t w[V];
 #pragma unroll
@@ -453,6 +456,7 @@ __global__ __launch_bounds__(256) void k_rescale(const int64_t *__restrict__ C, 
             Rm[x0] = (uint16_t)rm[0];
             bits[x0] = w[0];
         }
+        if (!E1) continue;  // the caller takes the claims itself (uniform)
         acc[0] = m61::fold(acc[0] + claim_terms<V>(el, eh, r));
         acc[1] = m61::fold(acc[1] + claim_terms<V>(el, eh, rm));
         acc[2] = m61::fold(acc[2] + claim_terms<V>(el, eh, y));
@@ -462,6 +466,7 @@ __global__ __launch_bounds__(256) void k_rescale(const int64_t *__restrict__ C, 
         const int any = __syncthreads_or(out_of_range);
         if (threadIdx.x == 0) flags[blockIdx.x] = (uint32_t)any;
     }
+    if (!E1) return;
     m61::block_sum<4>(acc, red);
     if (threadIdx.x == 0)
         for (int i = 0; i < 4; i++) claim_part[4 * blockIdx.x + i] = acc[i];
@@ -479,12 +484,12 @@ void launch_claims_final(const ClaimsJob &j, hipStream_t st)
 }
 
 void launch_witness_params(const int64_t *C, uint64_t N, int s, int relu, int mode, int t_in, int64_t *mm_part,
-                           WitParams *params, hipStream_t st)
+                           WitParams *params, hipStream_t st, WitParams *mirror)
 {
     const int nb = witness_blocks(N);
     hipLaunchKernelGGL(k_minmax, dim3(nb), dim3(kThreads), 0, st, C, N, mm_part);
     hipLaunchKernelGGL(k_wit_params, dim3(1), dim3(256), 0, st, (const int64_t *)mm_part, nb, s, relu, mode, t_in,
-                       params);
+                       params, mirror);
 }
 
 void launch_witness_rescale(const int64_t *C, uint64_t N, int lk, const uint64_t *E1, const uint64_t *E2, int32_t *R,
