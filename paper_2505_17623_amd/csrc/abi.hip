@@ -702,26 +702,30 @@ ra_status ra_mle_bind(ra_ctx *c, const void *d_T, ra_dtype dtype, uint32_t rows,
     if (dtype != RA_I16 && dtype != RA_I32 && dtype != RA_I64 && dtype != RA_FIELD) return RA_E_INVAL;
     const int v = log2u(bind_rows ? rows : cols);
     if ((int)point_len != v || (v && !h_point)) return RA_E_INVAL;
-    for (int i = 0; i < v; i++)
+    EqPoint pt{};
+    pt.v = v;  // v <= 31: rows and cols are 32-bit powers of two
+    for (int i = 0; i < v; i++) {
         if (h_point[i] >= kP) return RA_E_INVAL;
-    Carve cv;
-    const size_t o_pt = cv.take<uint64_t>(std::max(v, 1));
-    const size_t o_eq = cv.take<uint64_t>(1ull << v);
-    const size_t o_scr = cv.take<uint64_t>(bind_rows ? (size_t)bind_rows_chunks(rows, cols) * cols : 1);
-    ra_status st = ensure_ws(c, cv.off);
-    if (st != RA_OK) return st;
-    uint64_t *pt = (uint64_t *)(c->ws + o_pt), *eq = (uint64_t *)(c->ws + o_eq), *scr = (uint64_t *)(c->ws + o_scr);
-    // a synchronous utility: land any deferred outputs, then use the staging area for the point
-    st = drain(c);
-    if (st != RA_OK && c->deferred_err == RA_OK) c->deferred_err = st;
-    if ((size_t)v > c->stage_cap) return RA_E_INVAL;  // log2 of a 32-bit dimension
-    if (v) std::memcpy(c->h_stage, h_point, (size_t)v * 8);
-    RA_HIP(hipMemcpyAsync(pt, c->h_stage, (size_t)std::max(v, 1) * 8, hipMemcpyHostToDevice, c->stream));
-    launch_eq_table(pt, v, eq, c->stream);
-    if (bind_rows)
-        launch_bind_rows(d_T, dtype, rows, cols, eq, scr, d_out, c->stream);
-    else
-        launch_bind_cols(d_T, dtype, rows, cols, eq, d_out, c->stream);
+        pt.z[i] = h_point[i];
+    }
+    // a synchronous utility: deferred outputs are landed first
+    ra_status st = RA_OK;
+    if (!c->pending.empty()) {
+        st = drain(c);
+        if (st != RA_OK && c->deferred_err == RA_OK) c->deferred_err = st;
+    }
+    if (bind_rows || !launch_bind_cols_pt(d_T, dtype, rows, cols, pt, d_out, c->stream)) {
+        Carve cv;
+        const size_t o_eq = cv.take<uint64_t>(1ull << v);
+        const size_t o_scr = cv.take<uint64_t>(bind_rows ? (size_t)bind_rows_chunks(rows, cols) * cols : 1);
+        if ((st = ensure_ws(c, cv.off)) != RA_OK) return st;
+        uint64_t *eq = (uint64_t *)(c->ws + o_eq), *scr = (uint64_t *)(c->ws + o_scr);
+        launch_eq_table_val(pt, eq, c->stream);
+        if (bind_rows)
+            launch_bind_rows(d_T, dtype, rows, cols, eq, scr, d_out, c->stream);
+        else
+            launch_bind_cols(d_T, dtype, rows, cols, eq, d_out, c->stream);
+    }
     RA_HIP(hipGetLastError());
     RA_HIP(hipStreamSynchronize(c->stream));
     return RA_OK;

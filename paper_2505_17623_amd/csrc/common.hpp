@@ -74,7 +74,6 @@ struct XSetupArgs {
 };
 
 // ---- launchers (witness.hip) ----
-void launch_eq_table(const uint64_t *z, int v, uint64_t *out, hipStream_t st);
 // a point of at most 32 variables passed by value (kernel argument)
 struct EqPoint {
     uint64_t z[32];
@@ -123,6 +122,9 @@ void launch_front(const void *A, int a_is_i32, const int16_t *B, uint32_t n, uin
                   uint64_t *E2, void *ws, hipStream_t st);
 // rows binding: out[c] = sum_r E[r] T[r, c]; needs scratch of bind_rows_chunks(rows, cols) * cols words
 int bind_rows_chunks(uint32_t rows, uint32_t cols);
+// The column binding at a point by value, one launch; false (nothing done) unless int16, 8 <= cols <= 2^17, 16-byte aligned.
+bool launch_bind_cols_pt(const void *T, int dtype, uint32_t rows, uint32_t cols, const EqPoint &pt, uint64_t *out,
+                         hipStream_t st);
 void launch_bind_rows(const void *T, int dtype, uint32_t rows, uint32_t cols, const uint64_t *E, uint64_t *scratch,
                       uint64_t *out, hipStream_t st);
 // The second pass of a row binding (out = sum of the chunk rows of part).

@@ -20,6 +20,7 @@
 #include "common.hpp"
 #include "f2.hpp"
 #include "gram_reduce.hpp"
+#include "limbs.hpp"
 #include "ra.h"
 #include "fs_device.hpp"
 #include "sha256.hpp"
@@ -88,27 +89,10 @@ void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS
 // ---------------------------------------------------------------------------
 // The bound sides of the product.  Binding an integer table at a point of
 // F_{p^2} is linear in the eq table, so one pass over the table sums both
-// parts: an eq value is cut into limbs (31 bits for int16 entries, 21 for
-// int32) whose products with the entries add up exactly in int64 over a
-// bounded run of entries, and each run is reduced mod p once.  Two F_p
+// parts, by limbs of the eq values (limbs.hpp).  Two F_p
 // bindings per side read each table twice and took six launches; the two
 // sides of a 512 x 4096 by 4096 x 4096 layer went from 46 to 32 us.
 // ---------------------------------------------------------------------------
-template <typename T> struct BindLimbs;
-template <> struct BindLimbs<int16_t> {
-    static constexpr int kBits = 31, kCount = 2, kRun = 1 << 15;  // |limb entry| < 2^46: 2^15 terms below 2^61
-};
-template <> struct BindLimbs<int32_t> {
-    static constexpr int kBits = 21, kCount = 3, kRun = 1 << 9;  // 2^52
-};
-template <int BITS, int CNT> __device__ __forceinline__ uint64_t limbs_value(const int64_t (&a)[CNT])
-{
-    uint64_t v = 0;
-#pragma unroll
-    for (int i = 0; i < CNT; i++) v = m61::add(v, m61::rotl(m61::from_i64(a[i]), BITS * i));
-    return v;
-}
-
 // part[chunk][2 cols]: the sums over a chunk's rows, real parts then imaginary
 template <typename T>
 __global__ __launch_bounds__(256) void k_f2_bind_rows(const T *__restrict__ A, uint32_t rows, uint32_t cols, F2Tab E,

@@ -73,11 +73,13 @@ extern "C" ra_status ra_mle_bind_noalloc(const void *d_T, ra_dtype dtype, uint32
     if (st != RA_OK) return st;
     uint64_t *eq = base, *part = base + eq_bytes / 8;
     hipStream_t s = (hipStream_t)hip_stream;
-    launch_eq_table_val(pt, eq, s);
-    if (bind_rows)
-        launch_bind_rows(d_T, dtype, rows, cols, eq, part, d_out, s);
-    else
-        launch_bind_cols(d_T, dtype, rows, cols, eq, d_out, s);
+    if (bind_rows || !launch_bind_cols_pt(d_T, dtype, rows, cols, pt, d_out, s)) {
+        launch_eq_table_val(pt, eq, s);
+        if (bind_rows)
+            launch_bind_rows(d_T, dtype, rows, cols, eq, part, d_out, s);
+        else
+            launch_bind_cols(d_T, dtype, rows, cols, eq, d_out, s);
+    }
     if (hipGetLastError() != hipSuccess) return RA_E_HIP;
     return RA_OK;
 }

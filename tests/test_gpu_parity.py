@@ -44,6 +44,25 @@ EDGE = {np.int16: [-32768, 32767, -1, 0, 1], np.int32: [-(2 ** 31), 2 ** 31 - 1,
         np.int64: [-(2 ** 62), 2 ** 62, -1, 0, (1 << 61) - 1, -((1 << 61) - 1)]}
 
 
+# the one-launch column binding (int16, 8 to 2^17 columns): lane groups of 1, 2 and 64, one step of 512 columns, four
+# and more at a time, rows past the last group; the shapes past its range; and unaligned rows, which it leaves
+@pytest.mark.parametrize("rows,cols", [(1, 8), (32, 8), (2, 16), (64, 512), (4, 1024), (16, 2048), (2, 1 << 17),
+                                       (1, 1 << 18)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_mle_bind_int16_columns(ra, rows, cols, offset):
+    rng = np.random.default_rng(rows * 7 + cols)
+    T = rng.integers(-(2 ** 15), 2 ** 15, size=(rows, cols)).astype(np.int16)
+    T.flat[: min(T.size, 3)] = [-(2 ** 15), 2 ** 15 - 1, 0][: min(T.size, 3)]
+    buf = torch.zeros(T.size + 8, dtype=torch.int16, device="cuda")
+    dev = buf[offset: offset + T.size].reshape(rows, cols)
+    dev.copy_(torch.from_numpy(T))
+    v = cols.bit_length() - 1
+    z = [int(x) for x in inputs.xorshift64_stream(3 + v, v)]
+    got = ra.ra_mle_bind(ra.Context(seed=4), dev, False, z).cpu().numpy()
+    want = [orc.mle_field([int(x) % P61 for x in T[r]], z) for r in range(rows)]
+    assert [int(x) for x in got] == want
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (4, 8), (64, 32), (512, 256), (8, 2048), (128, 1)])
 @pytest.mark.parametrize("dt", [np.int16, np.int32, np.int64, "field"])
 def test_mle_bind_parity(ra, shape, dt):
