@@ -1561,7 +1561,7 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
 // ---------------------------------------------------------------------------
 namespace {
 struct LinkLayout {
-    size_t o_W, o_T0, o_part, o_E, o_bad, bytes;
+    size_t o_W, o_T0, o_part, o_E, bytes;
 };
 
 // n + m: the eq tables of the layer's (r1, rho); at most 2^31 + 2^15 words
@@ -1570,11 +1570,10 @@ LinkLayout link_layout(uint64_t nz, uint64_t eq_words)
     const int vz = log2u(nz);
     Carve cv;
     LinkLayout L{};
-    L.o_W = cv.take<uint64_t>(nz);
+    L.o_W = cv.take<uint64_t>(nz + 1);  // and the map's status
     L.o_T0 = cv.take<uint64_t>(nz > 1 ? nz / 2 : 1);
     L.o_part = cv.take<uint64_t>((size_t)(vz > 0 ? vz : 1) * kLinkMaxBlocks * 3);
     L.o_E = cv.take<uint64_t>(eq_words);
-    L.o_bad = cv.take<uint32_t>(1);
     L.bytes = cv.off;
     return L;
 }
@@ -1623,7 +1622,8 @@ extern "C" ra_status ra_link_prove(ra_ctx *c, const int32_t *d_Z, uint64_t z_ent
     // context's eq area may still be read by the layer's deferred kernels)
     uint64_t *E1 = (uint64_t *)(ws + L.o_E), *E2 = E1 + c->n;
     const uint64_t *r1 = c->d_chal + c->r12_off, *rho = r1 + ln + lk;
-    launch_eq_tables(r1, ln, E1, rho, lm, E2, s);
+    uint64_t *W = (uint64_t *)(ws + L.o_W);
+    launch_eq_tables(r1, ln, E1, rho, lm, E2, s, W, z_entries + 1);
     LinkArgs la{};
     la.src = d_src;
     la.na = a_entries;
@@ -1632,13 +1632,13 @@ extern "C" ra_status ra_link_prove(ra_ctx *c, const int32_t *d_Z, uint64_t z_ent
     la.E2 = E2;
     la.Z = d_Z;
     la.vz = vz;
-    la.W = (uint64_t *)(ws + L.o_W);
+    la.W = W;
     la.T0 = (uint64_t *)(ws + L.o_T0);
     la.rho = c->d_chal + c->cursor;
     la.part = (uint64_t *)(ws + L.o_part);
     la.tr = c->d_stage + off;
     la.fin = la.tr + 3 * (size_t)vz;
-    la.bad = (uint32_t *)(ws + L.o_bad);
+    la.bad = (uint32_t *)(W + z_entries);
     launch_link(la, s);
     c->cursor += (uint64_t)vz;
     c->link_ok = false;

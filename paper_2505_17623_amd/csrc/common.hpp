@@ -80,9 +80,9 @@ struct EqPoint {
     int v;
 };
 void launch_eq_table_val(const EqPoint &pt, uint64_t *out, hipStream_t st);
-// both tables of a product's two sides in one launch
+// both tables of a product's two sides in one launch, which may clear nz words besides
 void launch_eq_tables(const uint64_t *z1, int v1, uint64_t *out1, const uint64_t *z2, int v2, uint64_t *out2,
-                      hipStream_t st);
+                      hipStream_t st, uint64_t *zero = nullptr, uint64_t nz = 0);
 // ---- launchers (gemm.hip) ----
 constexpr uint32_t kGemmMaxInner = 32768;  // exactness bound of the int32 limb accumulators
 size_t gemm_workspace_bytes(int a_is_i32, uint32_t n, uint32_t m, uint32_t k);
@@ -443,8 +443,11 @@ void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS
 void launch_fill0(uint64_t *p, uint64_t n, hipStream_t st);
 
 // ---- the gather link between layers (link.hip) ----
-constexpr int kLinkMaxBlocks = 512;  // blocks of a round launch (partials per round)
-constexpr int kLinkTailLog = 11;     // the last rounds, over at most 2^11 entries, run in one workgroup
+constexpr int kLinkMaxBlocks = 512;    // blocks of a pass (partials per round)
+constexpr int kLinkTailLog = 11;       // the last rounds, over at most 2^11 entries, run from LDS
+constexpr int kLinkTailThreads = 512;
+constexpr int kLinkPass = 3;           // rounds per pass; the last pass takes what is left
+__host__ __device__ inline int link_pass_rounds(int left) { return left < kLinkPass ? left : kLinkPass; }
 __host__ __device__ inline int link_blocks(uint64_t h)
 {
     const uint64_t b = (h + kThreads - 1) / kThreads;
@@ -457,12 +460,12 @@ struct LinkArgs {
     const uint64_t *E1, *E2;   // eq tables of r1 (rows) and rho (columns)
     const int32_t *Z;          // the previous output, 2^vz entries
     int vz;
-    uint64_t *W, *T0;          // 2^vz and 2^(vz-1) words
+    uint64_t *W, *T0;          // 2^vz words, cleared, and 2^(vz-1)
     const uint64_t *rho;       // vz round challenges
-    uint64_t *part;            // vz x kLinkMaxBlocks x 3 words
+    uint64_t *part;            // vz x 3 x kLinkMaxBlocks words
     uint64_t *tr;              // out: 3 vz words
     uint64_t *fin;             // out: claim, Z~(y*), W~(y*), the map's status (nonzero: an index outside)
-    uint32_t *bad;             // out: nonzero if a gather index is outside [-1, 2^vz)
+    uint32_t *bad;             // cleared; nonzero if a gather index is outside [-1, 2^vz)
 };
 void launch_link(const LinkArgs &a, hipStream_t st);
 void launch_link_gather(const int32_t *Z, uint64_t nz, const int32_t *src, uint64_t na, int32_t *A, hipStream_t st);

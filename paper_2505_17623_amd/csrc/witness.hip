@@ -1,5 +1,7 @@
 // witness.hip -- eq tables, exact integer matrix product, multilinear binding
 // of matrix sides, and the rescale / ReLU / bit-plane witness.
+#include <algorithm>
+
 #include "claims.hpp"
 #include "common.hpp"
 #include "limbs.hpp"
@@ -30,17 +32,24 @@ __device__ __forceinline__ void eq_table_entries(const uint64_t *zl, int v, uint
     }
 }
 
-// Workgroups below nb1 fill the first table (point z1, v1 variables), the
-// others the second; the point is staged in LDS first.
+// Workgroups below nb1 fill the first table (point z1, v1 variables), those
+// below nb1 + nb2 the second, the rest clear nz words; the point is staged in
+// LDS first.
 __global__ __launch_bounds__(256) void k_eq_tables(const uint64_t *__restrict__ z1, int v1, uint64_t *__restrict__ out1,
                                                    int nb1, const uint64_t *__restrict__ z2, int v2,
-                                                   uint64_t *__restrict__ out2)
+                                                   uint64_t *__restrict__ out2, int nb2, uint64_t *__restrict__ zero,
+                                                   uint64_t nz)
 {
     __shared__ uint64_t zl[64];
+    if ((int)blockIdx.x >= nb1 + nb2) {
+        const uint64_t step = (uint64_t)(gridDim.x - nb1 - nb2) * blockDim.x;
+        for (uint64_t i = (uint64_t)(blockIdx.x - nb1 - nb2) * blockDim.x + threadIdx.x; i < nz; i += step) zero[i] = 0;
+        return;
+    }
     const bool second = (int)blockIdx.x >= nb1;
     const uint64_t *z = second ? z2 : z1;
     const int v = second ? v2 : v1, blk = second ? blockIdx.x - nb1 : blockIdx.x;
-    const int nblk = second ? gridDim.x - nb1 : nb1;
+    const int nblk = second ? nb2 : nb1;
     uint64_t *out = second ? out2 : out1;
     if ((int)threadIdx.x < v) zl[threadIdx.x] = z[threadIdx.x];
     __syncthreads();
@@ -68,10 +77,12 @@ void launch_eq_table_val(const EqPoint &pt, uint64_t *out, hipStream_t st)
 }
 
 void launch_eq_tables(const uint64_t *z1, int v1, uint64_t *out1, const uint64_t *z2, int v2, uint64_t *out2,
-                      hipStream_t st)
+                      hipStream_t st, uint64_t *zero, uint64_t nz)
 {
     const int nb1 = eq_blocks(v1), nb2 = eq_blocks(v2);
-    hipLaunchKernelGGL(k_eq_tables, dim3(nb1 + nb2), dim3(kThreads), 0, st, z1, v1, out1, nb1, z2, v2, out2);
+    const int nbz = (int)std::min<uint64_t>((nz + kThreads - 1) / kThreads, 1024);
+    hipLaunchKernelGGL(k_eq_tables, dim3(nb1 + nb2 + nbz), dim3(kThreads), 0, st, z1, v1, out1, nb1, z2, v2, out2, nb2,
+                       zero, nz);
 }
 
 // ---------------------------------------------------------------------------

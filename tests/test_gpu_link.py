@@ -83,6 +83,32 @@ def test_synthetic_gathers_match_oracle(ra, zr, zc, n, m, pad):
     assert ctx.cursor() == ol["cursor"]
 
 
+@pytest.mark.parametrize("vz", [1, 6, 10, 11, 12, 13, 14, 15, 17])
+def test_link_passes_and_shared_sources(ra, vz):
+    """Round counts around the passes' edges (none, one, two or three rounds
+    in the last pass; 1 to 2^11 entries left), with maps in which up to 4096
+    entries read one source, so that a weight's word wraps many times."""
+    rng = np.random.default_rng(900 + vz)
+    zr, zc = 1 << ((vz + 1) // 2), 1 << (vz // 2)
+    n, m = 64, 64
+    A0 = rng.integers(-3000, 3000, size=(zr, 2)).astype(np.int16)
+    B0 = rng.integers(-3000, 3000, size=(2, zc)).astype(np.int16)
+    B1 = rng.integers(-3000, 3000, size=(m, 2)).astype(np.int16)
+    chal = inputs.xorshift64_stream(700 + vz, 2048)
+    o0 = orc.prove_layer(A0, B0, 9, True, 0, chal, 0)
+    for sources in (1, 3):
+        src = rng.choice(rng.integers(0, zr * zc, size=sources), size=n * m).astype(np.int32)
+        A1 = o0["Z"].reshape(-1)[src].reshape(n, m).astype(np.int32)
+        o1 = orc.prove_layer(A1, B1, 9, True, 0, chal, o0["cursor"])
+        ol = orc.prove_link(o0["Z"], src, orc.link_point(n, m, 2, chal, o0["cursor"]), chal, o1["cursor"])
+        ctx = ra.Context(chal)
+        g0 = ra.prove_layer(ctx, torch.from_numpy(A0).cuda(), torch.from_numpy(B0).cuda(), 9, True, 0)
+        ra.prove_layer(ctx, torch.from_numpy(A1).cuda(), torch.from_numpy(B1).cuda(), 9, True, 0)
+        gl = ra.link_prove(ctx, g0["Z"], torch.from_numpy(src).cuda())
+        assert link_words(gl) == link_words(ol)
+        assert ctx.cursor() == ol["cursor"]
+
+
 def test_link_refusals(ra):
     chal = inputs.xorshift64_stream(31, 1024)
     A = torch.full((4, 4), 100, dtype=torch.int16).cuda()
