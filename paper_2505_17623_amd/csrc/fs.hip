@@ -366,7 +366,7 @@ void launch_fs_pass(const FsPassArgs &a, hipStream_t st)
 // pass's round is finished and folded), the instance's final values, and
 // their absorption, in one workgroup.
 //
-// A round's hash takes about 5 us on two waves, so the rest of a round runs
+// A round's hash takes 3.5 us on two waves, so the rest of a round runs
 // beside it on the others: with T_c the tables bound at rho_{<c}, the sums of
 // round c + 1 are quadratic in rho_c, its pairs being lo = x0 + rho (x2 - x0),
 // hi = x1 + rho (x3 - x1) over T_c's quads, and are taken at rho = 0 (x0, x1),
@@ -565,17 +565,12 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
             g = l2canon(g);
             // the values: to the transcript, behind what is pending
             const uint32_t qlen = l.f.m[8];
-            const bool ok = qlen + 16 * D1 <= sha::kFsPending;
             if (lane < D1) {
                 ev[D1 * c + lane] = g;
-                uint32_t *m = l.f.m + 9 + (qlen >> 2) + 4 * lane;
-                if (ok) {
-                    m[0] = (uint32_t)g.re;
-                    m[1] = (uint32_t)(g.re >> 32);
-                    m[2] = (uint32_t)g.im;
-                    m[3] = (uint32_t)(g.im >> 32);
-                }
+                l.g[lane] = g;
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const bool ok = fs_append(l.f, qlen, (const uint32_t *)l.g, 4 * D1, lane, 64);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (lane == 0) {
                 if (ok) l.f.m[8] = qlen + 16 * D1;

@@ -7,15 +7,16 @@
 // by words throughout.
 //
 // A draw is a chain of SHA-256 compressions, each 64 dependent rounds, and
-// one wave issues an instruction every four cycles whatever its lanes do, so
-// the instructions of the chain are its time.  Wave 1 expands the message
-// schedules (one block per lane, every block of the message at once) sixteen
-// words ahead of wave 0, which only runs the rounds: 14 instructions each,
-// the three-input logic on v_bitop3_b32.  All lanes of wave 0 carry the same
-// values; the state is kept out of the scalar unit, which has no rotate.
-// Against one thread working the message through a generic compression: a
-// round's draw with its sums 14.1 -> 7.6 us, the header of a layer with 2^14
-// outputs 88 -> 43 us (MI355X).
+// one wave issues an instruction every four cycles (8-byte encodings: 4.6)
+// whatever its lanes do, so the instructions of the chain are its time.  Wave
+// 1 expands the message schedules (one block per lane, every block of the
+// message at once) sixteen words ahead of wave 0, which only runs the rounds,
+// both halves of the state side by side in its lanes (ShaLanes): 19 ns per
+// round, 25 with all eight variables in one lane.  Nothing is loaded from
+// memory inside a draw (the initial state and the constants wait in LDS), the
+// padding is written with what is absorbed, and wave 0 starts on the message
+// itself.  Against rounds of 14 instructions on one lane: a draw with nothing
+// pending 2.5 -> 1.8 us, with a round's values 4.5 -> 3.5 us (MI355X).
 #pragma once
 #include "sha256.hpp"
 
@@ -27,7 +28,8 @@ struct FsLds {
     uint32_t m[kFsMaxBlocks * 16];    // the message, room for its padding
     uint4 kw[kFsMaxBlocks * 16];      // schedule plus round constants, 64 words per block
     uint64_t out[2];                  // the last challenge drawn
-    uint32_t ready;                   // quarters of the first schedules wave 1 has stored (0 between draws)
+    uint32_t h0[8], k16[16];          // the initial state, the first sixteen round constants
+    uint32_t ready;                   // quarters of the schedules after the first that wave 1 has stored (0 between draws)
 };
 
 __device__ __forceinline__ uint32_t vgpr(uint32_t x)  // the value, kept in vector registers
@@ -36,11 +38,28 @@ __device__ __forceinline__ uint32_t vgpr(uint32_t x)  // the value, kept in vect
     return x;
 }
 
+// Blocks of the padded message of `words` words.
+__device__ __forceinline__ int fs_blocks(int words) { return (4 * words + 9 + 63) / 64; }
+
+// Thread t of nt: the padding behind a message of `words` words (0x80, zeros,
+// the length in bits, as bytes in order), which f.m holds whenever a draw may
+// follow, so that a draw reads whole blocks.
+__device__ __forceinline__ void fs_pad(FsLds &f, int words, int t, int nt)
+{
+    const int end = 16 * fs_blocks(words);
+    for (int i = words + t; i < end; i += nt)
+        f.m[i] = i == words ? 0x80u : (i == end - 1 ? __builtin_bswap32(32u * (uint32_t)words) : 0u);
+}
+
 // The block: the transcript into f (visible after the caller's next barrier).
 __device__ inline void fs_pull(FsLds &f, const sha::Transcript *g)
 {
     const uint32_t *s = (const uint32_t *)g;
-    for (int i = threadIdx.x; i < kFsMsgWords; i += blockDim.x) f.m[i] = s[i];
+    const int words = 9 + (int)(s[8] >> 2);
+    for (int i = threadIdx.x; i < words; i += blockDim.x) f.m[i] = s[i];
+    fs_pad(f, words, threadIdx.x, blockDim.x);
+    if (threadIdx.x < 16) f.k16[threadIdx.x] = sha::kConsts.k[threadIdx.x];
+    if (threadIdx.x < 8) f.h0[threadIdx.x] = sha::kConsts.h[threadIdx.x];
     if (threadIdx.x == 0) f.ready = 0;
 }
 
@@ -52,46 +71,96 @@ __device__ inline void fs_push(sha::Transcript *g, const FsLds &f)
     for (int i = threadIdx.x; i < words; i += blockDim.x) d[i] = f.m[i];
 }
 
+// Threads t of nt: words w[0 .. nw) behind the pending ones and the padding
+// behind them, where they fit (false: more than sha::kFsPending bytes
+// pending).  The length is the caller's to set, once f.m[8] has been read.
+__device__ __forceinline__ bool fs_append(FsLds &f, uint32_t q, const uint32_t *w, int nw, int t, int nt)
+{
+    if (q + 4 * (uint32_t)nw > sha::kFsPending) return false;
+    const int at = 9 + (int)(q >> 2);
+    for (int i = t; i < nw; i += nt) f.m[at + i] = w[i];
+    fs_pad(f, at + nw, t, nt);
+    return true;
+}
+
 // The block: append nw 32-bit words (readable by every thread).  Barriers on
 // both sides; false: more than sha::kFsPending bytes pending.
 __device__ inline bool fs_absorb(FsLds &f, const uint32_t *w, int nw)
 {
     __syncthreads();
     const uint32_t q = f.m[8];
-    const bool ok = q + 4 * (uint32_t)nw <= sha::kFsPending;
-    if (ok)
-        for (int i = threadIdx.x; i < nw; i += blockDim.x) f.m[9 + (q >> 2) + i] = w[i];
+    const bool ok = fs_append(f, q, w, nw, threadIdx.x, blockDim.x);
     __syncthreads();
     if (ok && threadIdx.x == 0) f.m[8] = q + 4 * (uint32_t)nw;
     __syncthreads();
     return ok;
 }
 
-// Sixteen rounds on the working variables, kw read as four vectors.
-__device__ __forceinline__ void fs_rounds16(uint32_t (&v)[8], const uint4 *kw)
-{
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const uint4 x = kw[q];
-        const uint32_t k4[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const uint32_t e = v[4], a = v[0];
-            const uint32_t S1 = sha::xor3(sha::rotr(e, 6), sha::rotr(e, 11), sha::rotr(e, 25));
-            const uint32_t T1 = (v[7] + k4[u]) + S1 + sha::choose(e, v[5], v[6]);
-            const uint32_t S0 = sha::xor3(sha::rotr(a, 2), sha::rotr(a, 13), sha::rotr(a, 22));
-            const uint32_t T2 = S0 + sha::majority(a, v[1], v[2]);
-            v[7] = v[6];
-            v[6] = v[5];
-            v[5] = e;
-            v[4] = v[3] + T1;
-            v[3] = v[2];
-            v[2] = v[1];
-            v[1] = a;
-            v[0] = T1 + T2;
-        }
+// The rounds of one hash over the lanes of a wave.  In each group of eight
+// lanes the first four hold a, b, c, d and the others e, f, g, h, so that one
+// instruction forms both big sigmas (the rotations differ by lane), and one
+// pair of them both majority and choice: with x = a ^ b the majority is
+// x ? c : b, with x = ~e the choice is x ? g : f.  The halves meet in adds
+// whose operand is the other half's lane (DPP row_half_mirror: lane i reads
+// 7 - i): 10 instructions per round where one lane alone needs 14.
+struct ShaLanes {
+    uint32_t v[4];         // a, b, c, d or e, f, g, h
+    uint32_t q;            // h + schedule word + constant of the round to come (e's half), 0 (a's half)
+    uint32_t s1, s2, s3;   // the rotations of the half's sigma
+    uint32_t m;            // all ones in e's half
+    __device__ __forceinline__ void init(int lane)
+    {
+        const bool e = lane & 4;
+        s1 = vgpr(e ? 6 : 2);
+        s2 = vgpr(e ? 11 : 13);
+        s3 = vgpr(e ? 25 : 22);
+        m = vgpr(e ? ~0u : 0u);
     }
-}
+    __device__ __forceinline__ void start(const uint32_t (&st)[4], uint32_t kw0)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = st[i];
+        q = (v[3] + kw0) & m;
+        // a DPP operand may not be written in the two instructions before it is read
+        asm volatile("s_nop 1" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(q));
+    }
+    // four rounds; k: schedule words + constants of the second to the fourth
+    // and of the round after them.  A round: sigma in s; x = m ? ~v0 : v0 ^ v1
+    // and the choice by it; s = T1 in e's half, T2 in a's; e' = T1 + d, a' = T2
+    // + T1 in the place of h and d.  Two instructions lie between the write of
+    // s and its DPP read.  (In one block, since the compiler puts a wait
+    // between two blocks that pass a register on.)
+    __device__ __forceinline__ void rounds4(uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3)
+    {
+#define RA_SHA_ROUND(A, B, C, D, K)                                                   \
+    "v_alignbit_b32 %[s], " A ", " A ", %[s1]\n\t"                                    \
+    "v_alignbit_b32 %[x], " A ", " A ", %[s2]\n\t"                                    \
+    "v_alignbit_b32 %[y], " A ", " A ", %[s3]\n\t"                                    \
+    "v_bitop3_b32 %[s], %[s], %[x], %[y] bitop3:0x96\n\t"                             \
+    "v_bitop3_b32 %[x], " A ", " B ", %[m] bitop3:0x1e\n\t"                           \
+    "v_bitop3_b32 %[x], %[x], " C ", " B " bitop3:0xca\n\t"                           \
+    "v_add3_u32 %[s], %[q], %[s], %[x]\n\t"                                           \
+    "v_add_u32_dpp " D ", " D ", %[s] row_half_mirror row_mask:0xf bank_mask:0xf\n\t"  \
+    "v_add_u32_dpp %[q], " C ", " K " quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0xa\n\t" \
+    "v_add_u32_dpp " D ", %[s], %[s] row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        uint32_t s, x, y;
+        asm(RA_SHA_ROUND("%[a]", "%[b]", "%[c]", "%[d]", "%[k0]")
+            RA_SHA_ROUND("%[d]", "%[a]", "%[b]", "%[c]", "%[k1]")
+            RA_SHA_ROUND("%[c]", "%[d]", "%[a]", "%[b]", "%[k2]")
+            RA_SHA_ROUND("%[b]", "%[c]", "%[d]", "%[a]", "%[k3]")
+            : [s] "=&v"(s), [x] "=&v"(x), [y] "=&v"(y), [q] "+&v"(q), [a] "+&v"(v[0]), [b] "+&v"(v[1]),
+              [c] "+&v"(v[2]), [d] "+&v"(v[3])
+            : [k0] "v"(k0), [k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3), [s1] "v"(s1), [s2] "v"(s2), [s3] "v"(s3),
+              [m] "v"(m));
+#undef RA_SHA_ROUND
+    }
+    // sixteen rounds; k: the words of the rounds, next: of the one after them
+    __device__ __forceinline__ void rounds16(const uint4 (&k)[4], uint32_t next)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; i++) rounds4(k[i].y, k[i].z, k[i].w, i < 3 ? k[i < 3 ? i + 1 : 0].x : next);
+    }
+};
 
 // Words 16 (p + 1) .. 16 (p + 1) + 15 of the schedule from the sixteen before
 // them (w, replaced), stored with their round constants.
@@ -114,68 +183,96 @@ __device__ __forceinline__ void fs_schedule16(uint32_t (&w)[16], uint4 *kw)
 // The draw proper, by waves 0 and 1 between two barriers of the block (the
 // message complete before the first; the other waves may do other work):
 // S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two words to f.out.
-// Wave 0 waits in LDS for each quarter of the first block's schedule; wave 1
-// stores every quarter without waiting for anything.
+// Wave 0 waits in LDS for each later quarter of the first block's schedule;
+// wave 1 stores every quarter without waiting for anything.
 __device__ inline void fs_hash(FsLds &f)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int words = 9 + (int)(f.m[8] >> 2), nblk = (4 * words + 9 + 63) / 64;
+    const int nblk = fs_blocks(9 + (int)(f.m[8] >> 2));
     auto publish = [&](uint32_t p) {  // LDS operations of a wave stay in order
         __hip_atomic_store(&f.ready, p, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
-    auto await = [&](uint32_t p) {
-        while (__hip_atomic_load(&f.ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < p) {
-        }
-    };
+    auto word = [&](int g) { return __builtin_bswap32(f.m[g]); };  // of the padded message
     if (wave == 1 && lane < nblk) {  // the lanes without a block take no part: they would publish ahead of the others
         uint32_t w[16];
         uint4 *kw = f.kw + 16 * lane;
-        // the padded message: 0x80 after its last word, its bit length at the end
 #pragma unroll
-        for (int t = 0; t < 16; t++) w[t] = f.m[16 * lane + t];  // m has room for the last block
+        for (int t = 0; t < 16; t++) w[t] = word(16 * lane + t);
+        if (lane > 0)  // wave 0 forms the first block's
 #pragma unroll
-        for (int t = 0; t < 16; t++) {
-            const int g = 16 * lane + t;
-            w[t] = g < words ? __builtin_bswap32(w[t]) : (g == words ? 0x80000000u : 0u);
-        }
-        if (lane == nblk - 1) w[15] = 32u * (uint32_t)words;
-#pragma unroll
-        for (int q = 0; q < 4; q++)
-            kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
-                               w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
-        publish(1);
+            for (int q = 0; q < 4; q++)
+                kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
+                                   w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
         fs_schedule16<1>(w, kw);
-        publish(2);
+        publish(1);
         fs_schedule16<2>(w, kw);
-        publish(3);
+        publish(2);
         fs_schedule16<3>(w, kw);
-        publish(4);
+        publish(3);
     } else if (wave == 0) {
-        uint32_t v[8], st[8];
+        ShaLanes l;
+        l.init(lane);
+        uint32_t st[4];
 #pragma unroll
-        for (int i = 0; i < 8; i++) st[i] = vgpr(sha::kConsts.h[i]);
+        for (int i = 0; i < 4; i++) st[i] = f.h0[(lane & 4) + i];
+        if (lane < 16) ((uint32_t *)f.kw)[lane] = word(lane) + f.k16[lane];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        auto load = [&](uint4 (&x)[4], int q) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) x[i] = f.kw[4 * q + i];
+        };
+        auto add = [&]() {
+#pragma unroll
+            for (int i = 0; i < 4; i++) st[i] += l.v[i];
+        };
+        uint4 x[4];
+        load(x, 0);
+        l.start(st, x[0].x);
 #pragma unroll 1
-        for (int b = 0; b < nblk; b++) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[i] = st[i];
-#pragma unroll 1
-            for (int p = 0; p < 4; p++) {
-                if (b == 0) await(p + 1);
-                fs_rounds16(v, f.kw + 16 * b + 4 * p);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; i++) st[i] += v[i];
+        for (int p = 1; p < 4; p++) {  // the first block: each quarter as it comes
+            // the round before a quarter's first needs its first word: it is
+            // run with 0 in its place, which is added once the quarter is there
+            l.rounds16(x, 0);
+            uint32_t got;
+            do {  // a wave's LDS operations stay in order: the words are those of a quarter stored before `got`
+                got = __hip_atomic_load(&f.ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                asm volatile("" ::: "memory");
+                load(x, p);
+                asm volatile("" ::: "memory");
+            } while (got < (uint32_t)p);
+            l.q += x[0].x & l.m;
         }
-        if (lane == 0) {
+        l.rounds16(x, 0);
+        add();
+        if (nblk > 1) {
+            load(x, 4);
+#pragma unroll 1
+            for (int b = 1; b < nblk; b++) {
+                l.start(st, x[0].x);
 #pragma unroll
-            for (int i = 0; i < 8; i++) f.m[i] = st[i] = __builtin_bswap32(st[i]);  // S as its bytes in order
-            f.m[8] = 0;
+                for (int p = 0; p < 4; p++) {
+                    uint4 y[4];
+                    load(y, b + 1 < nblk || p < 3 ? 4 * b + p + 1 : 0);
+                    l.rounds16(x, y[0].x);
+#pragma unroll
+                    for (int i = 0; i < 4; i++) x[i] = y[i];
+                }
+                add();
+            }
+        }
+        if ((lane & ~4) == 0) {  // lanes 0 and 4: S as its bytes in order
+#pragma unroll
+            for (int i = 0; i < 4; i++) f.m[lane + i] = st[i] = __builtin_bswap32(st[i]);
+        }
+        if (lane >= 8 && lane < 16)  // nothing pending: |Q| = 0 and the padding of nine words
+            f.m[lane] = lane == 9 ? 0x80u : (lane == 15 ? __builtin_bswap32(32u * 9u) : 0u);
+        if (lane == 0) {
             f.ready = 0;
             constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
 #pragma unroll
             for (int q = 0; q < 2; q++) {
-                const uint64_t x = (uint64_t)st[2 * q] | ((uint64_t)st[2 * q + 1] << 32);  // LE64 of S[8q .. 8q + 8]
-                const uint64_t r = (x & p) + (x >> 61);                                     // x mod p (x < 2^64)
+                const uint64_t x2 = (uint64_t)st[2 * q] | ((uint64_t)st[2 * q + 1] << 32);  // LE64 of S[8q .. 8q + 8]
+                const uint64_t r = (x2 & p) + (x2 >> 61);                                    // x mod p (x < 2^64)
                 f.out[q] = r >= p ? r - p : r;
             }
         }
