@@ -217,54 +217,84 @@ void launch_fs_claims(const uint64_t *part, int nb, uint64_t *out8, sha::Transcr
 // transcript after it.  K: K_j in LDS.
 struct FsFinLds {
     FsLds f;
-    f2 g[4], K;
+    f2 g[4], K, k[2];
+    f2 co[4][2];  // by X: the factors of the round's quadratic and linear sums in its value
     uint64_t tot[10];
 };
 
-// The values of a round from its sums in l.tot (after a barrier): to l.g, and
-// by the writer to ev; absorbed, the challenge drawn; K advanced.
-template <int KIND>
-__device__ __forceinline__ f2 fs_finish_round(FsFinLds &l, f2 r, const uint64_t *cst, uint64_t *ev, bool writer,
-                                              uint32_t *err)
-{
-    constexpr int D1 = KIND == F2_MATMUL ? 3 : 4;
-    const int tid = threadIdx.x;
-    if (tid < D1) {
-        const f2 g = f2_round_value(KIND, l.tot, tid, l.K, r, cst);
-        l.g[tid] = g;
-        if (writer) stp(ev + 2 * tid, g);
-    }
-    if (!fs_absorb(l.f, (const uint32_t *)l.g, 4 * D1) && tid == 0 && writer) *err = 1;
-    fs_draw(l.f);
-    return f2{l.f.out[0], l.f.out[1]};
-}
-
-// As above, with the sums taken from the blocks' partials first and the
-// transcript pulled; K_j-1 read from K_in (null: 1).
+// The transcript pulled; round j - 1's sums added up from the blocks'
+// partials, its values formed and absorbed, its challenge drawn, K_j-1 (K_in;
+// null: 1) advanced.  What does not depend on the sums (the factors K eq(r, X)
+// of the values, K's next value as a line in rho) is formed beside them by
+// the last wave, and nothing is stored to memory before the last barrier (it
+// would be waited for there).
 template <int KIND>
 __device__ __forceinline__ f2 fs_finish_prev(FsFinLds &l, const FsFinArgs &a, bool writer)
 {
-    constexpr int NW = f2_sum_words(KIND);
-    const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    constexpr int NW = f2_sum_words(KIND), D1 = KIND == F2_MATMUL ? 3 : 4;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
     fs_pull(l.f, a.fs_in);
-    for (int q = tid >> 6; q < NW; q += nw) {
-        uint64_t v = 0;
-        for (int b = lane; b < a.nb; b += 64) v = m61::fold(v + a.part[(size_t)q * kF2MaxBlocks + b]);
+    uint64_t v[3] = {0, 0, 0};  // at least four waves: at most three words each
+#pragma unroll 4
+    for (int b = lane; b < a.nb; b += 64)
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) v = m61::fold(v + __shfl_xor(v, off, 64));
-        if (lane == 0) l.tot[q] = m61::canon(v);
-    }
-    const f2 r = KIND == F2_MATMUL ? f2of(0) : ldp(a.r);
-    if (tid == 0) l.K = KIND != F2_MATMUL && a.K_in ? ldp(a.K_in) : f2of(1);
-    __syncthreads();
-    const f2 rho = fs_finish_round<KIND>(l, r, a.cst, a.ev, writer, a.err);
-    if (KIND != F2_MATMUL) {
-        if (tid == 64) {
-            const f2 K = f2mul(l.K, eq1z(r, rho));
-            l.K = K;
-            if (writer && a.K_out) stp(a.K_out, K);
+        for (int u = 0; u < 3; u++)
+            if (wave + u * nw < NW) v[u] = m61::fold(v[u] + a.part[(size_t)(wave + u * nw) * kF2MaxBlocks + b]);
+    if (KIND != F2_MATMUL && wave == nw - 1) {
+        const f2 K = a.K_in ? ldp(a.K_in) : f2of(1), r = ldp(a.r);
+        f2 w = l2mul(K, l2eq1x(r, lane & 3));
+        if (KIND == F2_RANGE) {
+            const f2 ceq = ldp(a.cst), cd = f2sub(ldp(a.cst + 2), ceq);
+            w = l2mul(w, lane & 4 ? cd : ceq);
         }
-        __syncthreads();
+        if (lane < 8) l.co[lane & 3][lane >> 2] = w;
+        const f2 k = l2mul(K, lane & 1 ? f2sub(f2add(r, r), f2of(1)) : f2sub(f2of(1), r));
+        if (lane < 2) l.k[lane] = k;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int u = 0; u < 3; u++) v[u] = m61::fold(v[u] + __shfl_xor(v[u], off, 64));
+#pragma unroll
+    for (int u = 0; u < 3; u++)
+        if (lane == 0 && wave + u * nw < NW) l.tot[wave + u * nw] = m61::canon(v[u]);
+    __syncthreads();
+    if (wave == 0) {
+        const int X = lane & 3, j = (lane >> 2) & 1;
+        auto at = [&](int q) { return f2{l.tot[2 * q], l.tot[2 * q + 1]}; };
+        f2 lo, hi, inf;  // the sum (linear: j = 1) at 0 and 1, its leading coefficient
+        if (KIND == F2_RANGE) {
+            lo = at(j ? 0 : 2);
+            hi = at(j ? 1 : 4);
+            const f2 m = at(3);
+            inf = j ? f2of(0) : l2sub(l2add(lo, hi), l2add(m, m));
+        } else {
+            lo = at(0);
+            hi = at(1);
+            const f2 t = l2add(lo, hi);
+            inf = l2sub(l2add(t, t), at(2));
+        }
+        f2 g = l2add(l2add(lo, l2small(l2sub(hi, lo), X)), l2small(inf, X * (X - 1)));
+        if (KIND != F2_MATMUL) g = l2mul(l.co[X][j], g);
+        if (KIND == F2_RANGE) g = l2add(g, f2{__shfl_xor(g.re, 4, 64), __shfl_xor(g.im, 4, 64)});
+        g = l2canon(g);
+        if (lane < D1) l.g[lane] = g;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t q = l.f.m[8];
+        const bool ok = fs_append(l.f, q, (const uint32_t *)l.g, 4 * D1, lane, 64);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane == 0) {
+            if (ok) l.f.m[8] = q + 16 * D1;
+            else if (writer) *a.err = 1;
+        }
+    }
+    fs_draw(l.f);
+    const f2 rho{l.f.out[0], l.f.out[1]};
+    if (writer && tid < D1) stp(a.ev + 2 * tid, l.g[tid]);
+    if (KIND != F2_MATMUL && writer && tid == 64) {  // K (1 - r) + rho K (2 r - 1)
+        const f2 K = l2canon(l2add(l.k[0], l2mul(rho, l.k[1])));
+        l.K = K;
+        if (a.K_out) stp(a.K_out, K);
     }
     return rho;
 }
@@ -366,16 +396,21 @@ void launch_fs_pass(const FsPassArgs &a, hipStream_t st)
 // pass's round is finished and folded), the instance's final values, and
 // their absorption, in one workgroup.
 //
-// A round's hash takes 3.5 us on two waves, so the rest of a round runs
+// A round's hash takes 3.5 us on two waves, so all the rest of a round runs
 // beside it on the others: with T_c the tables bound at rho_{<c}, the sums of
 // round c + 1 are quadratic in rho_c, its pairs being lo = x0 + rho (x2 - x0),
 // hi = x1 + rho (x3 - x1) over T_c's quads, and are taken at rho = 0 (x0, x1),
-// 1 (x2, x3) and infinity (the differences) while rho_c is being hashed.  Once
-// it is there, wave 0 alone interpolates them, forms the round's values and
-// goes on hashing while the other waves fold.  Eleven rounds in sequence (sums
-// over the block, values, hash, fold) took 111 us; so they take 88 (range).
+// 1 (x2, x3) and infinity (the differences) while rho_c is being hashed; the
+// last of the waves turns them into the values g_{c+1}(X), X = 0 .. 3, as
+// cubics in rho_c (their eq factor is linear in it).  Once rho_c is there,
+// wave 0 evaluates these and goes on hashing, and the other waves fold.
+// Per round, sums over the block, values, hash and fold one after the other
+// took 10 us; with the sums beside the hash 7.5; with the cubics 4.2 to 4.6 from
+// 64 quads down (11 range rounds 86 -> 70 us with their start, MI355X).
 // ---------------------------------------------------------------------------
 constexpr int kTailWorkers = kFsTailThreads / 64 - 2;  // waves 2 ..
+constexpr int kTailSplit = 512;                        // short rounds: the other place of a table
+static_assert(kFsTailThreads == 512, "six waves beside the chain's two");
 
 // Sums over pairs weighted by w: ll = lo lo', hh = hi hi', and lo hi' (range)
 // or (lo + hi)(lo' + hi') (else).
@@ -395,7 +430,8 @@ constexpr int tail_values(int kind) { return kind == F2_RANGE ? 13 : 9; }
 struct FsTailLds {
     uint64_t part[kTailWorkers][2 * 13];  // a wave's sums, canonical
     uint64_t tr[kTailWorkers][8 * 64];    // its transposes
-    f2 co[5][2];                          // K_{c+1} eq(r_{c+1}, Y), Y = 0 .. 3, and K_{c+1}, linear in rho_c
+    f2 co[4][4];                          // by X: the factors of tail_cubics
+    f2 val[16];                           // the waves' sums added up
 };
 
 // Sums of NV values per lane of the wave, to out (2 NV words); tr: 512 words.
@@ -426,6 +462,68 @@ __device__ __forceinline__ void wave_totals(const f2 (&x)[NV], uint64_t *tr, uin
 
 __device__ __forceinline__ f2 lane_of(f2 v, int i) { return f2{__shfl(v.re, i, 64), __shfl(v.im, i, 64)}; }
 
+// Lanes 0 .. 15 (X = lane & 3, j = lane >> 2): the factors of the values of a
+// round at X, with K = k0 + rho k1, r the round's coordinate: of the quadratic
+// and the linear sums (c_eq, c_d = c_w - c_eq; ReLU: 1, none) times rho^0, rho^1.
+template <int KIND>
+__device__ __forceinline__ void tail_factors(FsTailLds &t, f2 k0, f2 k1, f2 r, f2 ceq, f2 cd)
+{
+    const int lane = threadIdx.x & 63, X = lane & 3, j = (lane >> 2) & 3;
+    f2 v = l2mul(j < 2 ? k0 : k1, l2eq1x(r, X));
+    if (KIND == F2_RANGE) v = l2mul(v, j & 1 ? cd : ceq);
+    else if (j & 1) v = f2of(0);
+    if (lane < 16) t.co[X][j] = v;
+}
+
+// One wave: the values of round c + 1 at X = 0 .. 3 as cubics in rho_c from
+// nw waves' sums (split: from three waves' sums, those of wave e at rho = 0, 1,
+// infinity): cub[X][d], the coefficient of rho_c^d.  Lane (j, d, X) forms the
+// product with factor j, the four products of a (d, X) are added over lanes.
+template <int KIND>
+__device__ __forceinline__ void tail_cubics(FsTailLds &t, int nw, bool split, f2 (*cub)[4])
+{
+    constexpr int NV = tail_values(KIND);
+    const int lane = threadIdx.x & 63, X = lane & 3, d = (lane >> 2) & 3, j = lane >> 4;
+    if (lane < NV) {
+        f2 v = f2of(0);
+        if (split) {
+            const int e = lane < 9 ? lane / 3 : (lane - 9) >> 1, q = lane < 9 ? lane % 3 : 3 + ((lane - 9) & 1);
+            v = f2{t.part[e][2 * q], t.part[e][2 * q + 1]};
+        } else {
+            for (int w = 0; w < nw; w++) v = l2add(v, f2{t.part[w][2 * lane], t.part[w][2 * lane + 1]});
+        }
+        t.val[lane] = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int at = KIND == F2_MATMUL || j < 2 ? d : d - 1;  // of rho in the sum
+    auto coef = [&](int q) {  // of rho^at in the sum q, from its values at 0, 1 and infinity
+        const f2 p0 = t.val[q], pi = t.val[6 + q];
+        const f2 b = l2sub(l2sub(t.val[3 + q], p0), pi);
+        return at == 0 ? p0 : (at == 1 ? b : (at == 2 ? pi : f2of(0)));
+    };
+    f2 lo = coef(0), hi = coef(2), inf = coef(1);
+    const f2 t2 = l2add(lo, hi);
+    inf = KIND == F2_RANGE ? l2sub(t2, l2add(inf, inf)) : l2sub(l2add(t2, t2), inf);
+    if (KIND == F2_RANGE && (j & 1)) {  // the linear sums
+        lo = t.val[9];
+        hi = t.val[10];
+        if (at == 1) {
+            lo = l2sub(t.val[11], lo);
+            hi = l2sub(t.val[12], hi);
+        } else if (at != 0) {
+            lo = hi = f2of(0);
+        }
+        inf = f2of(0);
+    }
+    f2 s = l2add(l2add(lo, l2small(l2sub(hi, lo), X)), l2small(inf, X * (X - 1)));
+    if (KIND != F2_MATMUL) {
+        s = l2mul(t.co[X][j], s);
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) s = l2add(s, f2{__shfl_xor(s.re, off, 64), __shfl_xor(s.im, off, 64)});
+    }
+    if (lane < 16) cub[X][d] = s;
+}
+
 template <int KIND>
 __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
 {
@@ -440,6 +538,9 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
     } u;
     __shared__ FsFinLds l;
     __shared__ f2 sig[KIND == F2_RANGE ? 64 : 1], fin[3];
+    __shared__ f2 cub[2][4][4];  // the values of round c as cubics in rho_{c-1}, by c's parity
+    __shared__ uint32_t arrived;
+    __shared__ uint64_t drawn[2][2];  // rho_c, by c's parity: rho_{c-1} may still be read while rho_c is drawn
     __shared__ f2 ev[D1 * kFsTailLog], rs[kFsTailLog];  // the rounds' values, written out at the end; r_j0 ..
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n0 = 1 << a.v;
     f2 rho{0, 0};
@@ -508,62 +609,43 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
         uint64_t v[NW];
         acc.words(v, false, f2of(1));
         f2_totals<NW>(v, u.red, l.tot, h < 64 ? 64 : (h < kFsTailThreads ? h : kFsTailThreads));
-        // the factors of the first round's values (no rho before it)
-        if (KIND != F2_MATMUL && tid < 5)
-            u.t.co[tid][0] = tid < 4 ? f2mul(l.K, eq1x(rs[0], tid)) : l.K;
-        if (tid < 5) u.t.co[tid][1] = f2of(0);
+        // the first round's values as cubics (no rho before it: constants)
+        if (wave == 0) {
+            if (KIND != F2_MATMUL) tail_factors<KIND>(u.t, l.K, f2of(0), rs[0], ceq, cd);
+            constexpr int omap[3] = {0, 2, 1};  // of F2Sums' words: ll, lh, hh
+            if (lane < 13) {
+                int at = KIND == F2_RANGE ? (lane >= 9 ? (lane - 9) & 1 : 2 + lane % 3) : omap[lane % 3];
+                const bool inf = lane >= 6 && lane < 9;
+                u.t.part[0][2 * lane] = inf ? 0 : l.tot[2 * at];
+                u.t.part[0][2 * lane + 1] = inf ? 0 : l.tot[2 * at + 1];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            tail_cubics<KIND>(u.t, 1, false, cub[0]);
+            if (lane == 0) {
+                l.f.go = 0;
+                arrived = 0;
+            }
+        }
         __syncthreads();
     }
+    // the other waves in the order they take a long round's work: those that
+    // share a SIMD with the chain's two (waves w and w + 4) last
+    const int w = wave < 4 ? wave - 2 : (wave < 6 ? wave : wave - 4), wt = 64 * w + lane;
+    f2 kk0 = l.K, kk1 = f2of(0);  // wave 7's: K_c, linear in rho_{c-1}
+    int base = 0;                    // T_{c-1}'s place
+    if (wave < 2) __builtin_amdgcn_s_setprio(3);  // the chain's waves before the one they share a SIMD with
     for (int c = 0; c < a.v; c++) {
         const int lg = a.v - c;                         // T_c holds 2^lg entries
         const int n = lg >= 2 ? 1 << (lg - 2) : 0;      // its quads
-        const f2 z = c ? f2{l.f.out[0], l.f.out[1]} : f2of(0);  // rho_{c-1}
+        const f2 z = c ? f2{drawn[(c - 1) & 1][0], drawn[(c - 1) & 1][1]} : f2of(0);  // rho_{c-1}
         if (wave == 0) {
-            // the round's sums at rho_{c-1}, in lanes 0 .. 4: ll, lh, hh, l, h; in lanes 5 .. 9 the factors
-            f2 p0 = f2of(0), p1 = f2of(0), pi = f2of(0);
-            const int q = lane < 3 ? lane : (KIND == F2_RANGE && lane < 5 ? lane : 0);
-            if (c == 0) {
-                constexpr int rmap[5] = {2, 3, 4, 0, 1}, omap[3] = {0, 2, 1};  // of F2Sums' words
-                const int at = KIND == F2_RANGE ? (q == 0 ? rmap[0] : q == 1 ? rmap[1] : q == 2 ? rmap[2] : q == 3 ? rmap[3] : rmap[4])
-                                                : (q == 0 ? omap[0] : q == 1 ? omap[1] : omap[2]);
-                p0 = p1 = f2{l.tot[2 * at], l.tot[2 * at + 1]};
-            } else {
-                const int nq = 1 << (lg - 1), nw = nq < 64 * kTailWorkers ? (nq + 63) >> 6 : kTailWorkers;  // of T_{c-1}
-                const int i0 = q < 3 ? q : 6 + q, i1 = q < 3 ? 3 + q : 8 + q, ii = q < 3 ? 6 + q : i0;
-                for (int w = 0; w < nw; w++) {
-                    const uint64_t *t = u.t.part[w];
-                    p0 = l2add(p0, f2{t[2 * i0], t[2 * i0 + 1]});
-                    p1 = l2add(p1, f2{t[2 * i1], t[2 * i1 + 1]});
-                    if (q < 3) pi = l2add(pi, f2{t[2 * ii], t[2 * ii + 1]});
-                }
-            }
-            f2 b = l2sub(p1, p0);
-            if (KIND != F2_MATMUL && lane >= 5 && lane < 10) {
-                p0 = u.t.co[lane - 5][0];
-                b = u.t.co[lane - 5][1];
-                pi = f2of(0);
-            }
-            const f2 v = l2add(p0, l2mul(z, l2add(b, l2mul(l2sub(z, f2of(1)), pi))));
-            // s(0), s(1), s(infinity) (the leading coefficient) in lanes 0, 1, 2
-            const f2 ll = lane_of(v, 0), lh = lane_of(v, 1), hh = lane_of(v, 2), t2 = l2add(ll, hh);
-            f2 sv;
-            if (KIND == F2_RANGE) {
-                const f2 inf = l2sub(t2, l2add(lh, lh)), l0 = lane_of(v, 3), h0 = lane_of(v, 4);
-                const f2 lin = l2mul(cd, lane == 0 ? l0 : h0), qd = l2mul(ceq, lane == 0 ? ll : (lane == 1 ? hh : inf));
-                sv = lane == 2 ? qd : l2add(qd, lin);
-            } else {
-                sv = lane == 0 ? ll : (lane == 1 ? hh : l2sub(l2add(t2, t2), lh));
-            }
-            const f2 s0 = lane_of(sv, 0), s1 = lane_of(sv, 1), si = lane_of(sv, 2);
+            // the round's values: lanes 0 .. 3 form z^2, 4 .. 7 z D1, 8 .. 11 z D3
             const int X = lane & 3;
-            f2 g = l2add(l2add(s0, l2small(l2sub(s1, s0), X)), l2small(si, X * (X - 1)));
-            if (KIND != F2_MATMUL) {
-                const f2 ke = lane_of(v, 5 + X);
-                g = l2mul(ke, g);
-                if (lane == 9) l.K = v;  // K_c
-            }
-            g = l2canon(g);
-            // the values: to the transcript, behind what is pending
+            const f2(*D)[4] = cub[c & 1];
+            const f2 pr = l2mul(z, lane < 4 ? z : D[X][lane < 8 ? 1 : 3]);
+            const f2 hi = l2add(D[X][2], lane_of(pr, 8 + X)), lo = l2add(D[X][0], lane_of(pr, 4 + X));
+            const f2 g = l2canon(l2add(lo, l2mul(lane_of(pr, X), hi)));
+            // to the transcript, behind what is pending
             const uint32_t qlen = l.f.m[8];
             if (lane < D1) {
                 ev[D1 * c + lane] = g;
@@ -575,65 +657,128 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
             if (lane == 0) {
                 if (ok) l.f.m[8] = qlen + 16 * D1;
                 else *a.err = 1;
+                __hip_atomic_store(&l.f.go, (uint32_t)(c + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
-        } else if (wave >= 2 && c > 0) {  // T_c from T_{c-1}: an entry's two sources are read by its own thread only
-            for (int i = tid - 128; i < (n ? n : 1); i += 64 * kTailWorkers)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            fs_hash_rounds(l.f, drawn[c & 1]);
+        } else if (wave == 1) {
+            while (__hip_atomic_load(&l.f.go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < (uint32_t)(c + 1)) {
+            }
+            fs_hash_schedules(l.f);
+        } else {
+            const int hs = 1 << lg;
+            const bool split = n <= 64;
+            int of = 0, nw = 3;  // the waves whose results the round's cubics take
+            if (KIND != F2_MATMUL && n && wave == 7) {
+                // K_{c+1} = K_c eq(r_c, rho_c) = K_c (1 - r_c) + rho_c K_c (2 r_c - 1)
+                const f2 K = l2add(kk0, l2mul(z, kk1)), r = rs[c];
+                kk0 = l2mul(K, f2sub(f2of(1), r));
+                kk1 = l2mul(K, f2sub(f2add(r, r), f2of(1)));
+                tail_factors<KIND>(u.t, kk0, kk1, rs[c + 1], ceq, cd);
+            }
+            if (split) {
+                // short rounds: waves 2, 3, 6 take the sums at rho = 0, 1,
+                // infinity (folding what they need themselves), waves 5 and 7 fold
+                const int e = wave == 6 ? 2 : wave - 2;
+                if (n && (wave < 4 || wave == 6)) {
+                    const int i = lane & (n - 1);
+                    f2 x[2], y[2];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int p = n ? i + e * n : e, hs = 1 << lg;
-                    if (p < hs)
+                    for (int q = 0; q < NT; q++)
 #pragma unroll
-                        for (int q = 0; q < NT; q++) T[q][p] = l2fold(T[q][p], T[q][p + hs], z);
-                }
-        }
-        __syncthreads();
-        if (wave < 2) {
-            fs_hash(l.f);
-        } else if (n) {
-            if (tid - 128 < (n > 64 ? n : 64) || wave == 2) {
-                PairSums at[3];
-                f2 lin[2][2] = {{f2of(0), f2of(0)}, {f2of(0), f2of(0)}};
-                for (int i = tid - 128; i < n; i += 64 * kTailWorkers) {
-                    f2 x[4], y[4];
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        y[e] = T[NT - 1][i + e * n];
-                        x[e] = T[0][i + e * n];
-                        if (KIND != F2_MATMUL) x[e] = l2mul(LS[n + i], x[e]);
+                        for (int b = 0; b < 2; b++) {
+                            const f2 *src = &T[q][base + i + b * n];
+                            f2 v = src[e ? 2 * n : 0], o = c ? src[(e ? 2 * n : 0) + hs] : f2of(0);
+                            if (e == 2) {
+                                v = l2sub(v, src[0]);
+                                if (c) o = l2sub(o, src[hs]);
+                            }
+                            if (c) v = l2fold(v, o, z);
+                            (q == NT - 1 ? y : x)[b] = v;
+                            if (NT == 1) x[b] = v;
+                        }
+                    if (KIND != F2_MATMUL) {
+                        const f2 wt1 = LS[n + i];
+                        x[0] = l2mul(wt1, x[0]);
+                        x[1] = l2mul(wt1, x[1]);
                     }
-                    at[0].template add<KIND>(x[0], x[1], y[0], y[1]);
-                    at[1].template add<KIND>(x[2], x[3], y[2], y[3]);
-                    at[2].template add<KIND>(l2sub(x[2], x[0]), l2sub(x[3], x[1]), l2sub(y[2], y[0]), l2sub(y[3], y[1]));
-                    if (KIND == F2_RANGE)
+                    PairSums at;
+                    at.template add<KIND>(x[0], x[1], y[0], y[1]);
+                    f2 val[KIND == F2_RANGE ? 5 : 3] = {at.ll.value(), at.lh.value(), at.hh.value()};
+                    if constexpr (KIND == F2_RANGE) {
+                        val[3] = x[0];
+                        val[4] = x[1];
+                    }
+                    if (lane >= n)
 #pragma unroll
-                        for (int e = 0; e < 4; e++) lin[e >> 1][e & 1] = l2add(lin[e >> 1][e & 1], x[e]);
+                        for (auto &v : val) v = f2of(0);
+                    wave_totals<KIND == F2_RANGE ? 5 : 3>(val, u.t.tr[w], u.t.part[e]);
                 }
-                f2 val[NV];
-#pragma unroll
-                for (int e = 0; e < 3; e++) {
-                    val[3 * e] = at[e].ll.value();
-                    val[3 * e + 1] = at[e].lh.value();
-                    val[3 * e + 2] = at[e].hh.value();
+                if ((wave == 5 || wave == 7) && c > 0) {
+                    const int db = base ^ kTailSplit;
+                    for (int i = 32 * (wave - 5) + lane; i < NT << lg; i += 128) {
+                        const int q = i >> lg, p = i & (hs - 1);
+                        T[q][db + p] = l2fold(T[q][base + p], T[q][base + p + hs], z);
+                    }
                 }
-                if constexpr (KIND == F2_RANGE)
+                if (n && (wave < 4 || wave == 6 || wave == 7)) of = 4;
+            } else {
+                nw = n < 64 * kTailWorkers ? (n + 63) >> 6 : kTailWorkers;
+                if (c > 0)  // T_c from T_{c-1}: an entry's two sources are read by its own thread only
+                    for (int i = wt; i < n; i += 64 * kTailWorkers)
 #pragma unroll
-                    for (int e = 0; e < 4; e++) val[9 + e] = lin[e >> 1][e & 1];
-                wave_totals<NV>(val, u.t.tr[wave - 2], u.t.part[wave - 2]);
+                        for (int e = 0; e < 4; e++) {
+                            const int p = i + e * n;
+#pragma unroll
+                            for (int q = 0; q < NT; q++) T[q][p] = l2fold(T[q][p], T[q][p + hs], z);
+                        }
+                if (w < nw) {
+                    PairSums at[3];
+                    f2 lin[2][2] = {{f2of(0), f2of(0)}, {f2of(0), f2of(0)}};
+                    for (int i = wt; i < n; i += 64 * kTailWorkers) {
+                        f2 x[4], y[4];
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            y[e] = T[NT - 1][i + e * n];
+                            x[e] = T[0][i + e * n];
+                            if (KIND != F2_MATMUL) x[e] = l2mul(LS[n + i], x[e]);
+                        }
+                        at[0].template add<KIND>(x[0], x[1], y[0], y[1]);
+                        at[1].template add<KIND>(x[2], x[3], y[2], y[3]);
+                        at[2].template add<KIND>(l2sub(x[2], x[0]), l2sub(x[3], x[1]), l2sub(y[2], y[0]), l2sub(y[3], y[1]));
+                        if (KIND == F2_RANGE)
+#pragma unroll
+                            for (int e = 0; e < 4; e++) lin[e >> 1][e & 1] = l2add(lin[e >> 1][e & 1], x[e]);
+                    }
+                    f2 val[NV];
+#pragma unroll
+                    for (int e = 0; e < 3; e++) {
+                        val[3 * e] = at[e].ll.value();
+                        val[3 * e + 1] = at[e].lh.value();
+                        val[3 * e + 2] = at[e].hh.value();
+                    }
+                    if constexpr (KIND == F2_RANGE)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) val[9 + e] = lin[e >> 1][e & 1];
+                    wave_totals<NV>(val, u.t.tr[w], u.t.part[w]);
+                }
+                if (w < nw || wave == 7) of = nw + (nw <= 3 ? 1 : 0);  // wave 7 is the fourth to take work
             }
-            if (KIND != F2_MATMUL && wave == kTailWorkers + 1 && lane < 5) {
-                // K_{c+1} = K_c eq(r_c, rho_c) = K_c (1 - r_c) + rho_c K_c (2 r_c - 1), with its factors for round c + 1
-                const f2 K = l.K, r = rs[c];
-                const f2 k0 = l2mul(K, f2sub(f2of(1), r)), k1 = l2mul(K, f2sub(f2add(r, r), f2of(1)));
-                f2 e = f2of(1);
-                if (lane < 4) e = l2eq1x(rs[c + 1], lane);
-                u.t.co[lane][0] = l2mul(k0, e);
-                u.t.co[lane][1] = l2mul(k1, e);
+            if (of) {  // the last of these waves to arrive has all of their results
+                uint32_t before = 0;
+                if (lane == 0) before = __hip_atomic_fetch_add(&arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (__builtin_amdgcn_readfirstlane((int)before) == of - 1) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    tail_cubics<KIND>(u.t, nw, split, cub[(c + 1) & 1]);
+                    if (lane == 0) arrived = 0;
+                }
             }
         }
+        if (c > 0 && n <= 64) base ^= kTailSplit;
         __syncthreads();
     }
     if (a.v > 0) {
-        if (tid < NT) T[tid][0] = l2fold(T[tid][0], T[tid][1], f2{l.f.out[0], l.f.out[1]});
+        if (tid < NT) T[tid][0] = l2fold(T[tid][base], T[tid][base + 1], f2{drawn[(a.v - 1) & 1][0], drawn[(a.v - 1) & 1][1]});
         if (tid >= 64 && tid - 64 < D1 * a.v) stp(a.ev + 2 * (D1 * a.j0 + tid - 64), ev[tid - 64]);
         __syncthreads();
     }

@@ -29,6 +29,7 @@ struct FsLds {
     uint4 kw[kFsMaxBlocks * 16];      // schedule plus round constants, 64 words per block
     uint64_t out[2];                  // the last challenge drawn
     uint32_t h0[8], k16[16];          // the initial state, the first sixteen round constants
+    uint32_t go;                      // fs_tail: rounds whose message is complete
     uint32_t ready;                   // quarters of the schedules after the first that wave 1 has stored (0 between draws)
 };
 
@@ -56,7 +57,10 @@ __device__ inline void fs_pull(FsLds &f, const sha::Transcript *g)
 {
     const uint32_t *s = (const uint32_t *)g;
     const int words = 9 + (int)(s[8] >> 2);
-    for (int i = threadIdx.x; i < words; i += blockDim.x) f.m[i] = s[i];
+    for (int i = threadIdx.x; i < kFsMsgWords; i += blockDim.x) {  // all of it: the loads do not wait for the length
+        const uint32_t x = s[i];
+        if (i < words) f.m[i] = x;
+    }
     fs_pad(f, words, threadIdx.x, blockDim.x);
     if (threadIdx.x < 16) f.k16[threadIdx.x] = sha::kConsts.k[threadIdx.x];
     if (threadIdx.x < 8) f.h0[threadIdx.x] = sha::kConsts.h[threadIdx.x];
@@ -180,103 +184,111 @@ __device__ __forceinline__ void fs_schedule16(uint32_t (&w)[16], uint4 *kw)
     for (int q = 0; q < 4; q++) kw[4 * P + q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
 }
 
-// The draw proper, by waves 0 and 1 between two barriers of the block (the
-// message complete before the first; the other waves may do other work):
-// S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two words to f.out.
-// Wave 0 waits in LDS for each later quarter of the first block's schedule;
-// wave 1 stores every quarter without waiting for anything.
-__device__ inline void fs_hash(FsLds &f)
+// The draw proper: S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two
+// words to out; one wave for each part, both started once the message is
+// complete.  The rounds wait in LDS for each later quarter of the first
+// block's schedule; the schedules are stored without waiting for anything.
+__device__ __forceinline__ void fs_hash_schedules(FsLds &f)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int nblk = fs_blocks(9 + (int)(f.m[8] >> 2));
+    const int lane = threadIdx.x & 63;
+    if (lane >= fs_blocks(9 + (int)(f.m[8] >> 2))) return;  // lanes without a block would publish ahead of the others
     auto publish = [&](uint32_t p) {  // LDS operations of a wave stay in order
         __hip_atomic_store(&f.ready, p, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
-    auto word = [&](int g) { return __builtin_bswap32(f.m[g]); };  // of the padded message
-    if (wave == 1 && lane < nblk) {  // the lanes without a block take no part: they would publish ahead of the others
-        uint32_t w[16];
-        uint4 *kw = f.kw + 16 * lane;
+    uint32_t w[16];
+    uint4 *kw = f.kw + 16 * lane;
 #pragma unroll
-        for (int t = 0; t < 16; t++) w[t] = word(16 * lane + t);
-        if (lane > 0)  // wave 0 forms the first block's
+    for (int t = 0; t < 16; t++) w[t] = __builtin_bswap32(f.m[16 * lane + t]);
+    if (lane > 0)  // wave 0 forms the first block's
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-                kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
-                                   w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
-        fs_schedule16<1>(w, kw);
-        publish(1);
-        fs_schedule16<2>(w, kw);
-        publish(2);
-        fs_schedule16<3>(w, kw);
-        publish(3);
-    } else if (wave == 0) {
-        ShaLanes l;
-        l.init(lane);
-        uint32_t st[4];
+        for (int q = 0; q < 4; q++)
+            kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
+                               w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
+    fs_schedule16<1>(w, kw);
+    publish(1);
+    fs_schedule16<2>(w, kw);
+    publish(2);
+    fs_schedule16<3>(w, kw);
+    publish(3);
+}
+
+__device__ __forceinline__ void fs_hash_rounds(FsLds &f, uint64_t *out)
+{
+    const int lane = threadIdx.x & 63, nblk = fs_blocks(9 + (int)(f.m[8] >> 2));
+    ShaLanes l;
+    l.init(lane);
+    uint32_t st[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) st[i] = f.h0[(lane & 4) + i];
-        if (lane < 16) ((uint32_t *)f.kw)[lane] = word(lane) + f.k16[lane];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        auto load = [&](uint4 (&x)[4], int q) {
+    for (int i = 0; i < 4; i++) st[i] = f.h0[(lane & 4) + i];
+    if (lane < 16) ((uint32_t *)f.kw)[lane] = __builtin_bswap32(f.m[lane]) + f.k16[lane];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    auto load = [&](uint4 (&x)[4], int q) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) x[i] = f.kw[4 * q + i];
-        };
-        auto add = [&]() {
+        for (int i = 0; i < 4; i++) x[i] = f.kw[4 * q + i];
+    };
+    auto add = [&]() {
 #pragma unroll
-            for (int i = 0; i < 4; i++) st[i] += l.v[i];
-        };
-        uint4 x[4];
-        load(x, 0);
-        l.start(st, x[0].x);
+        for (int i = 0; i < 4; i++) st[i] += l.v[i];
+    };
+    uint4 x[4];
+    load(x, 0);
+    l.start(st, x[0].x);
 #pragma unroll 1
-        for (int p = 1; p < 4; p++) {  // the first block: each quarter as it comes
-            // the round before a quarter's first needs its first word: it is
-            // run with 0 in its place, which is added once the quarter is there
-            l.rounds16(x, 0);
-            uint32_t got;
-            do {  // a wave's LDS operations stay in order: the words are those of a quarter stored before `got`
-                got = __hip_atomic_load(&f.ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                asm volatile("" ::: "memory");
-                load(x, p);
-                asm volatile("" ::: "memory");
-            } while (got < (uint32_t)p);
-            l.q += x[0].x & l.m;
-        }
+    for (int p = 1; p < 4; p++) {  // the first block: each quarter as it comes
+        // the round before a quarter's first needs its first word: it is
+        // run with 0 in its place, which is added once the quarter is there
         l.rounds16(x, 0);
-        add();
-        if (nblk > 1) {
-            load(x, 4);
+        uint32_t got;
+        do {  // a wave's LDS operations stay in order: the words are those of a quarter stored before `got`
+            got = __hip_atomic_load(&f.ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            asm volatile("" ::: "memory");
+            load(x, p);
+            asm volatile("" ::: "memory");
+        } while (got < (uint32_t)p);
+        l.q += x[0].x & l.m;
+    }
+    l.rounds16(x, 0);
+    add();
+    if (nblk > 1) {
+        load(x, 4);
 #pragma unroll 1
-            for (int b = 1; b < nblk; b++) {
-                l.start(st, x[0].x);
+        for (int b = 1; b < nblk; b++) {
+            l.start(st, x[0].x);
 #pragma unroll
-                for (int p = 0; p < 4; p++) {
-                    uint4 y[4];
-                    load(y, b + 1 < nblk || p < 3 ? 4 * b + p + 1 : 0);
-                    l.rounds16(x, y[0].x);
+            for (int p = 0; p < 4; p++) {
+                uint4 y[4];
+                load(y, b + 1 < nblk || p < 3 ? 4 * b + p + 1 : 0);
+                l.rounds16(x, y[0].x);
 #pragma unroll
-                    for (int i = 0; i < 4; i++) x[i] = y[i];
-                }
-                add();
+                for (int i = 0; i < 4; i++) x[i] = y[i];
             }
-        }
-        if ((lane & ~4) == 0) {  // lanes 0 and 4: S as its bytes in order
-#pragma unroll
-            for (int i = 0; i < 4; i++) f.m[lane + i] = st[i] = __builtin_bswap32(st[i]);
-        }
-        if (lane >= 8 && lane < 16)  // nothing pending: |Q| = 0 and the padding of nine words
-            f.m[lane] = lane == 9 ? 0x80u : (lane == 15 ? __builtin_bswap32(32u * 9u) : 0u);
-        if (lane == 0) {
-            f.ready = 0;
-            constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
-#pragma unroll
-            for (int q = 0; q < 2; q++) {
-                const uint64_t x2 = (uint64_t)st[2 * q] | ((uint64_t)st[2 * q + 1] << 32);  // LE64 of S[8q .. 8q + 8]
-                const uint64_t r = (x2 & p) + (x2 >> 61);                                    // x mod p (x < 2^64)
-                f.out[q] = r >= p ? r - p : r;
-            }
+            add();
         }
     }
+    if ((lane & ~4) == 0) {  // lanes 0 and 4: S as its bytes in order
+#pragma unroll
+        for (int i = 0; i < 4; i++) f.m[lane + i] = st[i] = __builtin_bswap32(st[i]);
+    }
+    if (lane >= 8 && lane < 16)  // nothing pending: |Q| = 0 and the padding of nine words
+        f.m[lane] = lane == 9 ? 0x80u : (lane == 15 ? __builtin_bswap32(32u * 9u) : 0u);
+    if (lane == 0) {
+        f.ready = 0;
+        constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            const uint64_t x2 = (uint64_t)st[2 * q] | ((uint64_t)st[2 * q + 1] << 32);  // LE64 of S[8q .. 8q + 8]
+            const uint64_t r = (x2 & p) + (x2 >> 61);                                    // x mod p (x < 2^64)
+            out[q] = r >= p ? r - p : r;
+        }
+    }
+}
+
+// Waves 0 and 1, between two barriers of the block (the other waves may do
+// other work).
+__device__ __forceinline__ void fs_hash(FsLds &f)
+{
+    if (threadIdx.x < 64) fs_hash_rounds(f, f.out);
+    else if (threadIdx.x < 128) fs_hash_schedules(f);
 }
 
 // The block: a draw with its barriers.
