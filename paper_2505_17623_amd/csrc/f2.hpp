@@ -180,6 +180,25 @@ __device__ __forceinline__ f2 f2_round_value(int kind, const uint64_t *t, int X,
     return f2mul(f2mul(K, eq1x(r, X)), s);
 }
 
+// Sums over adjacent lanes (all of them active), in each of the lanes; in and
+// out folded.  The partner values come by DPP moves in the adds' own registers
+// (lane ^ 1, ^ 2, then the other quad and the other half by mirrors): a
+// cross-lane read through LDS takes 100 cycles and more per step.
+template <int CTRL> __device__ __forceinline__ uint64_t dpp_plus(uint64_t v)
+{
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xF, 0xF, false);
+    return v + ((uint64_t)hi << 32 | lo);  // two such adds of folded values stay below 2^64
+}
+__device__ __forceinline__ uint64_t sum8(uint64_t v)
+{
+    return m61::fold(dpp_plus<0x141>(m61::fold(dpp_plus<0x4E>(dpp_plus<0xB1>(v)))));
+}
+__device__ __forceinline__ uint64_t sum16(uint64_t v)
+{
+    return m61::fold(dpp_plus<0x140>(dpp_plus<0x141>(m61::fold(dpp_plus<0x4E>(dpp_plus<0xB1>(v))))));
+}
+
 // Totals of NW words per thread over the block's first nt threads (nt a
 // multiple of 64, the others' words are zero): canonical, in tot (LDS) for
 // every thread.  red: NW nt words.  Barriers on both sides.
@@ -199,9 +218,7 @@ __device__ __forceinline__ void f2_totals(const uint64_t (&v)[NW], uint64_t *red
             a0 = m61::fold(a0 + src[16 * e] + src[16 * e + 32]);
             a1 = m61::fold(a1 + src[16 * e + 16] + src[16 * e + 48]);
         }
-        uint64_t x = m61::fold(a0 + a1);
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) x = m61::fold(x + __shfl_xor(x, off, 64));
+        const uint64_t x = sum16(m61::fold(a0 + a1));
         if ((task & 15) == 0) tot[task >> 4] = m61::canon(x);
     }
     __syncthreads();

@@ -498,7 +498,9 @@ void launch_f2_tails(const F2TailArgs &mm, const F2TailArgs &rs, const F2TailArg
 // es, three of W with g), one per group of 32 lanes; then g and W are folded at
 // sigma_j, and G on both sides (its upper triangle, h (h + 1) / 2 entries).
 // Keeping G unfolded and forming c^T G c anew each round took 106 us (118 us
-// with the challenges hashed, MI355X, 64 planes); this takes 37 and 61.
+// with the challenges hashed, MI355X, 64 planes); the evaluation on four
+// threads in canonical arithmetic and sums through LDS lane reads 37 and 61; this
+// takes 28 and 44.
 //
 // Also writes the x rounds' constants c_eq = eq(tau_p, sigma_p), c_w =
 // mu W~(sigma_p), the claimed sum mu (l1 Rm~ + l2 (R~ + 2^(t+1)) + l3 Y~) and,
@@ -506,10 +508,8 @@ void launch_f2_tails(const F2TailArgs &mm, const F2TailArgs &rs, const F2TailArg
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ f2 group32_sum(f2 v)
 {
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1)
-        v = f2{m61::fold(v.re + __shfl_xor(v.re, off, 64)), m61::fold(v.im + __shfl_xor(v.im, off, 64))};
-    return v;
+    v = f2{sum16(v.re), sum16(v.im)};
+    return f2{m61::fold(v.re + __shfl_xor(v.re, 16, 64)), m61::fold(v.im + __shfl_xor(v.im, 16, 64))};
 }
 
 // eq(z, .) of k variables at index i (first variable most significant)
@@ -525,9 +525,11 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
     constexpr int GS = 65;  // row stride of the staged Gram matrix (odd, so rows start in different banks)
     __shared__ uint64_t g_re[64 * GS], g_im[64 * GS];
     __shared__ f2 W[64], dv[64], es[64], tau[8], sig[8], lam[4], pre[8], tot[8], gsh[4];
+    __shared__ f2 ke[2][4];  // K_j eq(tau_j, X), by j's parity
     __shared__ f2 ev[4 * kMaxPlaneLog];  // the rounds' values: stores to memory would be waited for at each barrier
     __shared__ FsLds fsl;  // the transcript (Fiat-Shamir mode)
     const int tid = threadIdx.x, lP = a.lP, P = a.P;
+#pragma unroll 8
     for (int e = tid; e < P * P; e += blockDim.x) {
         const int p = e >> lP, q = e & (P - 1);
         g_re[p * GS + q] = a.G_re[p * 64 + q];
@@ -557,6 +559,8 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
         }
     } else if (tid == 128) {
         pre[0] = f2of(1);  // pre[i] = prod over i' < i of eq(tau_i', sigma_i'), after round i - 1
+    } else if (tid >= 192 && tid < 196 && lP) {
+        ke[0][tid - 192] = l2eq1x(tau[0], tid - 192);
     }
     __syncthreads();
     for (int jj = 0; jj < lP; jj++) {
@@ -589,25 +593,41 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
             if (q == 0) tot[T] = l2canon(v);
         }
         __syncthreads();
-        if (tid < 4) {
-            const int X = tid, u = 1 - X;
-            const f2 cross = f2sub(f2sub(tot[7], tot[5]), tot[6]);
-            f2 A = f2add(f2add(f2small(tot[0], u * u), f2small(tot[1], 2 * X * u)), f2small(tot[2], X * X));
-            A = f2sub(f2sub(A, f2small(tot[3], u)), f2small(tot[4], X));
-            const f2 B = f2add(f2add(f2small(tot[5], u * u), f2small(cross, X * u)), f2small(tot[6], X * X));
-            const f2 g = f2add(f2mul(f2mul(pre[jj], eq1x(tau[jj], X)), A), f2mul(mu, B));
-            ev[4 * jj + tid] = g;
-            gsh[tid] = g;
+        if (tid < 64) {
+            // lanes 0 .. 3: K_j eq(tau_j, X) A(X); 4 .. 7: mu B(X); each from
+            // its values at 0 and 1 and its leading coefficient
+            const int X = tid & 3;
+            const bool second = tid & 4;
+            const f2 t0 = tot[second ? 5 : 0], t1 = tot[second ? 6 : 2], tm = tot[second ? 7 : 1], t = l2add(t0, t1);
+            const f2 lo = second ? t0 : l2sub(t0, tot[3]), hi = second ? t1 : l2sub(t1, tot[4]);
+            const f2 inf = second ? l2sub(l2add(t, t), tm) : l2sub(t, l2add(tm, tm));
+            f2 g = l2add(l2add(lo, l2small(l2sub(hi, lo), X)), l2small(inf, X * (X - 1)));
+            g = l2mul(second ? mu : ke[jj & 1][X], g);
+            g = l2canon(l2add(g, f2{__shfl_xor(g.re, 4, 64), __shfl_xor(g.im, 4, 64)}));
+            if (tid < 4) ev[4 * jj + tid] = g;
+            if (a.fs) {
+                if (tid < 4) gsh[tid] = g;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t ql = fsl.m[8];
+                const bool ok = fs_append(fsl, ql, (const uint32_t *)gsh, 16, tid, 64);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (tid == 0) {
+                    if (ok) fsl.m[8] = ql + 64;
+                    else *a.err = 1;
+                }
+            }
         }
-        __syncthreads();
         if (a.fs) {  // the round's values absorbed, sigma_jj drawn
-            if (!fs_absorb(fsl, (const uint32_t *)gsh, 16) && tid == 0) *a.err = 1;
             fs_draw(fsl);
             if (tid == 0) sig[jj] = f2{fsl.out[0], fsl.out[1]};
-            __syncthreads();
         }
-        const f2 sg = sig[jj];
-        if (tid == 255) pre[jj + 1] = f2mul(pre[jj], eq1z(tau[jj], sg));
+        const f2 sg = a.fs ? f2{fsl.out[0], fsl.out[1]} : sig[jj];
+        if (tid >= 192 && tid < 196) {  // K_{j+1} and the factors of the next round's values
+            const f2 ab = l2mul(tau[jj], sg);
+            const f2 K = l2mul(pre[jj], l2add(l2sub(l2sub(f2of(1), tau[jj]), sg), l2add(ab, ab)));
+            if (tid == 192) pre[jj + 1] = l2canon(K);
+            if (jj + 1 < lP) ke[(jj + 1) & 1][tid - 192] = l2mul(K, l2eq1x(tau[jj + 1], tid - 192));
+        }
         // the folds; an entry's four sources are read by its own thread only
         if (tid < h) dv[tid] = l2fold(dv[tid], dv[tid + h], sg);
         else if (tid >= 64 && tid < 64 + h) W[tid - 64] = l2fold(W[tid - 64], W[tid - 64 + h], sg);
