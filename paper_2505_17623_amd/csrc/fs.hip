@@ -16,30 +16,125 @@ namespace ra {
 // Merkle root: 1 KiB chunks, leaf H(0x00 || chunk), nodes H(0x01 || 4
 // digests), root H(0x02 || LE64(leaves) || top).  A 4-ary node is 129 bytes
 // (three compressions), which keeps the sequential levels short.
+//
+// Even the largest tables leave the chip less than one wave of leaves per
+// SIMD, so the 17 compressions of a leaf and the three of every level are
+// chains of latency.  A leaf's schedule is expanded by a second wave one block
+// ahead of the rounds; a workgroup goes on from its 64 leaves to the node
+// above them (three levels), and one workgroup takes the rest of the tree and
+// the root, with the schedules of a level's blocks all at once and eight nodes
+// per wave (ShaLanes).  One thread per hash and a launch per level: 113 us for
+// 352 leaves, 155 us for 45056; so 65 and 131 (MI355X).
 // ---------------------------------------------------------------------------
-// SHA-256 of prefix || NB bytes at src (NB a multiple of 64; bytes at or
-// beyond `avail` read as zero), src 16-byte aligned; digest stored as its 32
-// bytes in order.
-template <int NB>
-__device__ void hash_chunk(uint8_t prefix, const uint8_t *__restrict__ src, uint32_t avail, uint32_t *__restrict__ out)
+constexpr int kLeafThreads = 128, kLeafGroup = 64, kLeafLevels = 3;
+constexpr int kTopThreads = 128, kTopNodes = 64;  // digests the last workgroup starts from, at most: its levels take two waves
+constexpr int kNodeRow = 3 * 16 + 1;  // a node's three schedules, rows one bank group apart
+
+// Message word from stored words (digests and data as their bytes in order):
+// the last byte of `prev`, then the first three of `cur`, big-endian.
+__device__ __forceinline__ uint32_t shifted_word(uint32_t prev, uint32_t cur)
 {
-    static_assert(NB % 64 == 0, "whole blocks of data");
-    uint32_t st[8];
+    return (prev & 0xFF000000u) | ((cur & 0xFFu) << 16) | (cur & 0xFF00u) | ((cur >> 16) & 0xFFu);
+}
+
+// The schedule of block b of a node over `kids` digests (8 words each) at d.
+__device__ __forceinline__ void node_schedule(const uint32_t *d, int kids, int b, uint4 *kw)
+{
+    uint32_t w[16];
+    const int n = 8 * kids, g0 = 16 * b;
+    uint32_t prev = b ? (g0 - 1 < n ? d[g0 - 1] : 0u) : 0x01000000u;
+    if (b < 2) {
 #pragma unroll
-    for (int i = 0; i < 8; i++) st[i] = sha::kConsts.h[i];
-    const uint32_t *s32 = (const uint32_t *)src;
-    auto word = [&](int i) -> uint32_t {  // little-endian word i of the chunk, zero past avail
-        if (4u * i + 4u <= avail) return s32[i];
-        uint32_t v = 0;
-        for (int b = 0; b < 4; b++)
-            if (4u * i + b < avail) v |= (uint32_t)src[4 * i + b] << (8 * b);
-        return v;
-    };
-    uint32_t prev = (uint32_t)prefix << 24;  // the byte before chunk word 0 sits in the top byte
-    for (int blk = 0; blk <= NB / 64; blk++) {
-        uint32_t w[16];
-        if (blk < NB / 64) {
-            uint32_t c[16];
+        for (int t = 0; t < 16; t++) {
+            const uint32_t cur = g0 + t < n ? d[g0 + t] : 0u;
+            w[t] = shifted_word(prev, cur);
+            prev = cur;
+        }
+    } else {  // the last byte, the 0x80 marker, the length
+        w[0] = (prev & 0xFF000000u) | 0x00800000u;
+#pragma unroll
+        for (int t = 1; t < 15; t++) w[t] = 0;
+        w[15] = 129u * 8u;
+    }
+    sha_schedule(w, kw);
+}
+
+// A level of nodes in place: digests dig[0 .. count) to dig[0 .. (count + 3) /
+// 4), at most 8 per wave at a time, whose schedules kw holds.  A chunk's nodes
+// are written below every digest that a later chunk reads.  Barriers on both
+// sides; the block.
+__device__ __forceinline__ void node_level(uint32_t *dig, int count, uint4 *kw)
+{
+    const int tid = threadIdx.x, lane = tid & 63, per = (blockDim.x >> 6) * 8, nodes = (count + 3) / 4;
+    for (int first = 0; first < nodes; first += per) {
+        __syncthreads();
+        for (int i = tid; i < 3 * per; i += blockDim.x) {
+            const int j = i / 3, g = first + j;
+            if (g < nodes) node_schedule(dig + 32 * g, count - 4 * g < 4 ? count - 4 * g : 4, i % 3, kw + kNodeRow * j + 16 * (i % 3));
+        }
+        __syncthreads();
+        const int j0 = (tid >> 6) * 8;  // this wave's nodes
+        if (first + j0 < nodes) {
+            const int j = j0 + (lane >> 3);
+            uint32_t st[4];
+            sha_lanes_hash(kw + kNodeRow * (first + j < nodes ? j : j0), 3, st);
+            if ((lane & 3) == 0 && first + j < nodes)
+#pragma unroll
+                for (int i = 0; i < 4; i++) dig[8 * (first + j) + (lane & 4) + i] = __builtin_bswap32(st[i]);
+        }
+    }
+    __syncthreads();
+}
+
+// Sixteen rounds of one hash per lane, kw read at a stride of 64 vectors.
+__device__ __forceinline__ void sha_rounds16(uint32_t (&v)[8], const uint4 *kw)
+{
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const uint4 x = kw[64 * q];
+        const uint32_t k4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const uint32_t e = v[4], a = v[0];
+            const uint32_t S1 = sha::xor3(sha::rotr(e, 6), sha::rotr(e, 11), sha::rotr(e, 25));
+            const uint32_t T1 = (v[7] + k4[u]) + S1 + sha::choose(e, v[5], v[6]);
+            const uint32_t S0 = sha::xor3(sha::rotr(a, 2), sha::rotr(a, 13), sha::rotr(a, 22));
+            const uint32_t T2 = S0 + sha::majority(a, v[1], v[2]);
+            v[7] = v[6];
+            v[6] = v[5];
+            v[5] = e;
+            v[4] = v[3] + T1;
+            v[3] = v[2];
+            v[2] = v[1];
+            v[1] = a;
+            v[0] = T1 + T2;
+        }
+    }
+}
+
+// 64 leaves (src: from their tables; else 64 digests of `in`) and the levels
+// above them, at most `levels`, to out[blockIdx.x].  count: leaves, or digests.
+template <bool LEAVES>
+__global__ __launch_bounds__(kLeafThreads) void k_merkle_group(MerkleArgs a, const uint32_t *__restrict__ in,
+                                                               uint64_t count, int levels, uint32_t *__restrict__ out)
+{
+    __shared__ uint4 buf[2][16][64];   // the schedules of a block of 64 leaves, twice
+    __shared__ uint32_t dig[kLeafGroup * 8];
+    static_assert(sizeof(buf) >= sizeof(uint4) * 16 * kNodeRow, "the first level's 16 nodes");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t first = (uint64_t)blockIdx.x * kLeafGroup;
+    const int here = (int)(count - first < kLeafGroup ? count - first : kLeafGroup);
+    if (!LEAVES) {
+        for (int i = tid; i < 8 * here; i += kLeafThreads) dig[i] = in[8 * first + i];
+    } else {
+        const uint64_t leaf = first + (lane < here ? lane : 0);
+        int sg = 0;
+        while (sg < 4 && leaf >= a.seg[sg + 1].first_leaf) sg++;
+        const uint64_t off = (leaf - a.seg[sg].first_leaf) * 1024, left = a.seg[sg].bytes - off;
+        const uint8_t *src = a.seg[sg].p + off;  // 16-byte aligned
+        const uint32_t avail = left < 1024 ? (uint32_t)left : 1024u;
+        // the 16 words of data block blk, zero past avail
+        auto data = [&](int blk, uint32_t (&c)[16]) {
             if (64u * blk + 64u <= avail) {
                 const uint4 *q = (const uint4 *)(src + 64 * blk);
 #pragma unroll
@@ -52,57 +147,97 @@ __device__ void hash_chunk(uint8_t prefix, const uint8_t *__restrict__ src, uint
                 }
             } else {
 #pragma unroll
-                for (int t = 0; t < 16; t++) c[t] = word(16 * blk + t);
+                for (int t = 0; t < 16; t++) {
+                    uint32_t v = 0;
+                    for (uint32_t at = 64u * blk + 4u * t, b = 0; b < 4 && at + b < avail; b++)
+                        v |= (uint32_t)src[at + b] << (8 * b);
+                    c[t] = v;
+                }
             }
-            // message word g = 16 blk + t holds bytes chunk[4g - 1], chunk[4g .. 4g + 2]
+        };
+        uint32_t v[8], st[8], c[16], prev = 0;  // prefix 0x00
 #pragma unroll
-            for (int t = 0; t < 16; t++) {
-                const uint32_t cw = c[t];
-                w[t] = (prev & 0xFF000000u) | ((cw & 0xFFu) << 16) | (cw & 0xFF00u) | ((cw >> 16) & 0xFFu);
-                prev = cw;
+        for (int i = 0; i < 8; i++) st[i] = sha::kConsts.h[i];
+        if (wave == 1) data(0, c);
+#pragma unroll 1
+        for (int it = 0; it <= 17; it++) {  // wave 1: block it; wave 0: block it - 1
+            if (wave == 1 && it < 17) {
+                uint32_t w[16];
+                if (it < 16) {
+#pragma unroll
+                    for (int t = 0; t < 16; t++) {
+                        w[t] = shifted_word(prev, c[t]);
+                        prev = c[t];
+                    }
+                    if (it < 15) data(it + 1, c);  // the next block's loads beside this one's schedule
+                } else {  // the last data byte, the 0x80 marker, the length
+                    w[0] = (prev & 0xFF000000u) | 0x00800000u;
+#pragma unroll
+                    for (int t = 1; t < 15; t++) w[t] = 0;
+                    w[15] = 1025u * 8u;
+                }
+                uint4(*kw)[64] = buf[it & 1];
+                uint4 row[16];
+                sha_schedule(w, row);
+#pragma unroll
+                for (int q = 0; q < 16; q++) kw[q][lane] = row[q];
+            } else if (wave == 0 && it > 0) {
+                const uint4 *kw = &buf[(it - 1) & 1][0][lane];
+#pragma unroll
+                for (int i = 0; i < 8; i++) v[i] = st[i];
+#pragma unroll 1
+                for (int p = 0; p < 4; p++) sha_rounds16(v, kw + 256 * p);
+#pragma unroll
+                for (int i = 0; i < 8; i++) st[i] += v[i];
             }
-        } else {
-            // the last data byte, the 0x80 marker, zeros, the length (1 + NB) * 8 bits
-            w[0] = (prev & 0xFF000000u) | 0x00800000u;
-#pragma unroll
-            for (int t = 1; t < 15; t++) w[t] = 0;
-            w[15] = (1u + NB) * 8u;
+            __syncthreads();
         }
-        sha::compress(st, w);
-    }
+        if (wave == 0 && lane < here)
 #pragma unroll
-    for (int i = 0; i < 8; i++) out[i] = __builtin_bswap32(st[i]);
+            for (int i = 0; i < 8; i++) dig[8 * lane + i] = __builtin_bswap32(st[i]);
+    }
+    int n = here;
+    for (int l = 0; l < levels; l++) {
+        node_level(dig, n, &buf[0][0][0]);
+        n = (n + 3) / 4;
+    }
+    __syncthreads();
+    if (tid < 8) out[8 * (size_t)blockIdx.x + tid] = dig[tid];
 }
 
-__global__ __launch_bounds__(256) void k_merkle_leaves(MerkleArgs a, uint32_t *__restrict__ dig)
+// The levels above `count` digests (at most kTopNodes) and the root.
+__global__ __launch_bounds__(kTopThreads) void k_merkle_top(const uint32_t *__restrict__ in, int count, uint64_t leaves,
+                                                            uint32_t *__restrict__ root)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.leaves) return;
-    int sg = 0;
-    while (sg < 4 && i >= a.seg[sg + 1].first_leaf) sg++;
-    const uint64_t off = (i - a.seg[sg].first_leaf) * 1024;
-    const uint64_t left = a.seg[sg].bytes - off;
-    hash_chunk<1024>(0x00, a.seg[sg].p + off, (uint32_t)(left < 1024 ? left : 1024), dig + 8 * i);
-}
-
-__global__ __launch_bounds__(256) void k_merkle_nodes(const uint32_t *__restrict__ in, uint64_t count,
-                                                      uint32_t *__restrict__ out)
-{
-    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (count + 3) / 4) return;
-    const uint64_t kids = std::min<uint64_t>(4, count - 4 * g);
-    hash_chunk<128>(0x01, (const uint8_t *)(in + 8 * 4 * g), (uint32_t)(32 * kids), out + 8 * g);
-}
-
-__global__ void k_merkle_root(const uint32_t *__restrict__ top, uint64_t leaves, uint8_t *__restrict__ root)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    sha::Hasher h;
-    h.init();
-    h.byte(0x02);
-    h.le(leaves, 8);
-    h.update((const uint8_t *)top, 32);
-    h.final(root);
+    __shared__ uint32_t dig[8 * kTopNodes];
+    __shared__ uint4 kw[kTopThreads / 64 * 8 * kNodeRow];
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < 8 * count; i += kTopThreads) dig[i] = in[i];
+    __syncthreads();
+    for (; count > 1; count = (count + 3) / 4) node_level(dig, count, kw);
+    if (tid == 0) {  // 0x02, the leaves, the digest: 41 bytes
+        uint32_t w[16], prev = (uint32_t)(leaves >> 32);
+        w[0] = 0x02000000u | __builtin_bswap32((uint32_t)leaves) >> 8;
+        w[1] = (uint32_t)(leaves >> 24 & 0xFF) << 24 | __builtin_bswap32(prev) >> 8;
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            w[2 + t] = shifted_word(prev, dig[t]);
+            prev = dig[t];
+        }
+        w[10] = (prev & 0xFF000000u) | 0x00800000u;
+#pragma unroll
+        for (int t = 11; t < 15; t++) w[t] = 0;
+        w[15] = 41u * 8u;
+        sha_schedule(w, kw);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        uint32_t st[4];
+        sha_lanes_hash(kw, 1, st);
+        if (lane < 8 && (lane & 3) == 0)
+#pragma unroll
+            for (int i = 0; i < 4; i++) root[lane + i] = __builtin_bswap32(st[i]);
+    }
 }
 
 uint64_t merkle_leaves(const MerkleArgs &a)
@@ -112,7 +247,7 @@ uint64_t merkle_leaves(const MerkleArgs &a)
     return n;
 }
 
-// digests: two areas of merkle_leaves() x 8 words each
+// digests: two areas, of merkle_leaves() and a quarter as many of 8 words
 void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *root, hipStream_t st)
 {
     uint64_t first = 0;
@@ -121,16 +256,24 @@ void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *r
         first += (a.seg[s].bytes + 1023) / 1024;
     }
     a.leaves = first;
-    hipLaunchKernelGGL(k_merkle_leaves, dim3((unsigned)((first + 255) / 256)), dim3(256), 0, st, a, dig0);
-    uint64_t count = first;
+    // a group's levels: those of the tree where it is one group, which ends at the top
+    auto levels = [](uint64_t n) {
+        int l = 0;
+        for (; l < kLeafLevels && n > 1; l++) n = (n + 3) / 4;
+        return l;
+    };
+    uint64_t count = (first + kLeafGroup - 1) / kLeafGroup;
+    hipLaunchKernelGGL((k_merkle_group<true>), dim3((unsigned)count), dim3(kLeafThreads), 0, st, a, nullptr, first,
+                       levels(first), dig0);
     uint32_t *in = dig0, *out = dig1;
-    while (count > 1) {
-        const uint64_t next = (count + 3) / 4;
-        hipLaunchKernelGGL(k_merkle_nodes, dim3((unsigned)((next + 255) / 256)), dim3(256), 0, st, in, count, out);
+    while (count > kTopNodes) {
+        const uint64_t next = (count + kLeafGroup - 1) / kLeafGroup;
+        hipLaunchKernelGGL((k_merkle_group<false>), dim3((unsigned)next), dim3(kLeafThreads), 0, st, a, in, count,
+                           kLeafLevels, out);
         std::swap(in, out);
         count = next;
     }
-    hipLaunchKernelGGL(k_merkle_root, dim3(1), dim3(64), 0, st, in, first, root);
+    hipLaunchKernelGGL(k_merkle_top, dim3(1), dim3(kTopThreads), 0, st, in, (int)count, first, (uint32_t *)root);
 }
 
 // ---------------------------------------------------------------------------
@@ -252,7 +395,9 @@ __device__ __forceinline__ f2 fs_finish_prev(FsFinLds &l, const FsFinArgs &a, bo
         if (lane < 2) l.k[lane] = k;
     }
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1)
+    for (int u = 0; u < 3; u++) v[u] = sum16(v[u]);
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1)
 #pragma unroll
         for (int u = 0; u < 3; u++) v[u] = m61::fold(v[u] + __shfl_xor(v[u], off, 64));
 #pragma unroll
@@ -452,8 +597,7 @@ __device__ __forceinline__ void wave_totals(const f2 (&x)[NV], uint64_t *tr, uin
         uint64_t v = 0;
 #pragma unroll
         for (int e = 0; e < 8; e += 2) v = m61::fold(v + src[8 * e] + src[8 * e + 8]);
-#pragma unroll
-        for (int off = 1; off < 8; off <<= 1) v = m61::fold(v + __shfl_xor(v, off, 64));
+        v = sum8(v);
         const int w = 2 * q0 + (lane >> 3);
         if ((lane & 7) == 0 && w < 2 * NV) out[w] = m61::canon(v);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

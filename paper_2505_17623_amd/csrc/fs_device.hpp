@@ -184,6 +184,49 @@ __device__ __forceinline__ void fs_schedule16(uint32_t (&w)[16], uint4 *kw)
     for (int q = 0; q < 4; q++) kw[4 * P + q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
 }
 
+// A block's schedule with its round constants, 64 words, from its message
+// words (replaced).
+__device__ __forceinline__ void sha_schedule(uint32_t (&w)[16], uint4 *kw)
+{
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+        kw[q] = make_uint4(w[4 * q] + sha::kConsts.k[4 * q], w[4 * q + 1] + sha::kConsts.k[4 * q + 1],
+                           w[4 * q + 2] + sha::kConsts.k[4 * q + 2], w[4 * q + 3] + sha::kConsts.k[4 * q + 3]);
+    fs_schedule16<1>(w, kw);
+    fs_schedule16<2>(w, kw);
+    fs_schedule16<3>(w, kw);
+}
+
+// Eight hashes per wave, one per group of eight lanes: nblk blocks whose
+// schedules lie at kw (16 vectors each).  Lane 8 g: words 0 .. 3 of hash g's
+// state, lane 8 g + 4: words 4 .. 7.
+__device__ __forceinline__ void sha_lanes_hash(const uint4 *kw, int nblk, uint32_t (&st)[4])
+{
+    ShaLanes l;
+    l.init(threadIdx.x & 63);
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        st[i] = vgpr(sha::kConsts.h[i]) ^ (l.m & vgpr(sha::kConsts.h[i] ^ sha::kConsts.h[4 + i]));
+    uint4 x[4], y[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) x[i] = kw[i];
+#pragma unroll 1
+    for (int b = 0; b < nblk; b++) {
+        l.start(st, x[0].x);
+#pragma unroll
+        for (int p = 0; p < 4; p++) {
+            const int next = b + 1 < nblk || p < 3 ? 4 * (4 * b + p + 1) : 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) y[i] = kw[next + i];
+            l.rounds16(x, y[0].x);
+#pragma unroll
+            for (int i = 0; i < 4; i++) x[i] = y[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) st[i] += l.v[i];
+    }
+}
+
 // The draw proper: S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two
 // words to out; one wave for each part, both started once the message is
 // complete.  The rounds wait in LDS for each later quarter of the first

@@ -135,6 +135,32 @@ def abi_layers(ra, wl, got):
                  transcript=g["transcript"], chained=li > 0 and wl.links[li] is None) for li, g in enumerate(got)]
 
 
+# rounds that all run in one workgroup, long (more than 64 quads) and short:
+# 2^7 .. 2^11 outputs, 2^7 .. 2^11 matrix entries
+@pytest.mark.parametrize("n,m,k,relu", [(8, 128, 16, True), (16, 256, 16, False), (16, 512, 32, True),
+                                        (32, 1024, 32, True), (1, 2048, 2048, False)])
+def test_fs_tail_rounds(ra, n, m, k, relu):
+    check_layer(ra, n, m, k, relu, "tail")
+
+
+# Merkle trees over 5 .. 11264 leaves: one group, whole and ragged groups, three
+# levels in the last workgroup, one and two levels of groups
+@pytest.mark.parametrize("n,k", [(1, 2), (32, 64), (64, 64), (64, 1024), (128, 512), (64, 4096), (512, 1024)])
+def test_fs_merkle_sizes(ra, n, k):
+    check_layer(ra, n, 1, k, False, "merkle")
+
+
+def check_layer(ra, n, m, k, relu, what):
+    rng = np.random.default_rng(n + 3 * m + 5 * k)
+    A = rng.integers(-300, 300, size=(n, m)).astype(np.int16)
+    B = rng.integers(-300, 300, size=(m, k)).astype(np.int16)
+    domain, pub = hashlib.sha256(f"{what} {n} {m} {k}".encode()).digest(), bytes(range(32))
+    o = orc.prove_layer_fs(A, B, 7, relu, 0, orc.fs_init(domain), pub)
+    g = ra.prove_layer_fp2(ra.Context(fs_domain=domain), torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(),
+                           7, relu, 0, pub=pub)
+    compare(ra, g, o, f"{what} {n}x{m}x{k}")
+
+
 @pytest.mark.parametrize("cfg", [2, 4, 5])
 def test_fs_proofs_verify(ra, cfg):
     """The GPU's non-interactive proofs pass the library's and the oracle's
