@@ -281,18 +281,18 @@ void launch_merkle_root(MerkleArgs a, uint32_t *dig0, uint32_t *dig1, uint8_t *r
 // ---------------------------------------------------------------------------
 constexpr int kFsThreads = 128;  // one wave runs the rounds, one the message schedules
 
-// ndraw challenges (at most kFsDraws) in a row to out.  They are kept in LDS
-// until the last: a store to memory before a barrier is waited for there.
+// ndraw challenges (at most kFsDraws) in a row to out, the first with what is
+// pending.
 constexpr int kFsDraws = 64;
 __device__ __forceinline__ void fs_draws(FsLds &f, uint64_t *out, int ndraw)
 {
-    __shared__ uint64_t drawn[2 * kFsDraws];
-    for (int i = 0; i < ndraw; i++) {
-        fs_draw(f);
-        if (threadIdx.x < 2) drawn[2 * i + threadIdx.x] = f.out[threadIdx.x];
-    }
+    __shared__ uint32_t raw[4 * kFsDraws];
+    if (ndraw == 0) return;
+    fs_draw(f);
+    fs_hash_more(f, ndraw - 1, raw);
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * ndraw; i += blockDim.x) out[i] = drawn[i];
+    for (int i = threadIdx.x; i < 2 * ndraw; i += blockDim.x)
+        out[i] = i < 2 ? f.out[i] : fs_challenge_word(raw + 2 * (i - 2));
 }
 
 __global__ __launch_bounds__(kFsThreads) void k_fs_header(sha::Transcript *fs, FsHeader h,

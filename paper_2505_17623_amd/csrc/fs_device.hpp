@@ -29,7 +29,7 @@ struct FsLds {
     uint4 kw[kFsMaxBlocks * 16];      // schedule plus round constants, 64 words per block
     uint64_t out[2];                  // the last challenge drawn
     uint32_t h0[8], k16[16];          // the initial state, the first sixteen round constants
-    uint32_t go;                      // fs_tail: rounds whose message is complete
+    uint32_t go;                      // messages complete, where no barrier says so (0 before and after)
     uint32_t ready;                   // quarters of the schedules after the first that wave 1 has stored (0 between draws)
 };
 
@@ -64,7 +64,7 @@ __device__ inline void fs_pull(FsLds &f, const sha::Transcript *g)
     fs_pad(f, words, threadIdx.x, blockDim.x);
     if (threadIdx.x < 16) f.k16[threadIdx.x] = sha::kConsts.k[threadIdx.x];
     if (threadIdx.x < 8) f.h0[threadIdx.x] = sha::kConsts.h[threadIdx.x];
-    if (threadIdx.x == 0) f.ready = 0;
+    if (threadIdx.x == 0) f.ready = f.go = 0;
 }
 
 // The block: f back into the transcript (after a barrier).
@@ -227,6 +227,15 @@ __device__ __forceinline__ void sha_lanes_hash(const uint4 *kw, int nblk, uint32
     }
 }
 
+// Word q of the challenge from S's bytes in order: LE64(S[8q .. 8q + 8]) mod p.
+__device__ __forceinline__ uint64_t fs_challenge_word(const uint32_t *s)
+{
+    constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
+    const uint64_t x = (uint64_t)s[0] | ((uint64_t)s[1] << 32);
+    const uint64_t r = (x & p) + (x >> 61);
+    return r >= p ? r - p : r;
+}
+
 // The draw proper: S = H(S || LE32(|Q|) || Q), Q emptied, the challenge's two
 // words to out; one wave for each part, both started once the message is
 // complete.  The rounds wait in LDS for each later quarter of the first
@@ -316,13 +325,8 @@ __device__ __forceinline__ void fs_hash_rounds(FsLds &f, uint64_t *out)
         f.m[lane] = lane == 9 ? 0x80u : (lane == 15 ? __builtin_bswap32(32u * 9u) : 0u);
     if (lane == 0) {
         f.ready = 0;
-        constexpr uint64_t p = 0x1FFFFFFFFFFFFFFFull;
-#pragma unroll
-        for (int q = 0; q < 2; q++) {
-            const uint64_t x2 = (uint64_t)st[2 * q] | ((uint64_t)st[2 * q + 1] << 32);  // LE64 of S[8q .. 8q + 8]
-            const uint64_t r = (x2 & p) + (x2 >> 61);                                    // x mod p (x < 2^64)
-            out[q] = r >= p ? r - p : r;
-        }
+        out[0] = fs_challenge_word(st);
+        out[1] = fs_challenge_word(st + 2);
     }
 }
 
@@ -332,6 +336,86 @@ __device__ __forceinline__ void fs_hash(FsLds &f)
 {
     if (threadIdx.x < 64) fs_hash_rounds(f, f.out);
     else if (threadIdx.x < 128) fs_hash_schedules(f);
+}
+
+// n draws in a row with nothing pending (a draw came before), by waves 0 and
+// 1 between two barriers: the first four words of each new S, as its bytes in
+// order, to raw[4 i ..].  A message is then S and constants, so a draw hands
+// the new state straight to the next one's schedule, with no barrier between.
+__device__ __forceinline__ void fs_hash_more(FsLds &f, int n, uint32_t *raw)
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (wave == 1 && lane == 0) {
+        for (int i = 0; i < n; i++) {
+            while (__hip_atomic_load(&f.go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < (uint32_t)(i + 1)) {
+            }
+            auto publish = [&](uint32_t p) {
+                __hip_atomic_store(&f.ready, 3 * (uint32_t)i + p, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            uint32_t w[16];
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const uint4 x = f.kw[q];
+                w[4 * q] = x.x - sha::kConsts.k[4 * q];
+                w[4 * q + 1] = x.y - sha::kConsts.k[4 * q + 1];
+                w[4 * q + 2] = x.z - sha::kConsts.k[4 * q + 2];
+                w[4 * q + 3] = x.w - sha::kConsts.k[4 * q + 3];
+            }
+#pragma unroll
+            for (int t = 8; t < 16; t++) w[t] = t == 9 ? 0x80000000u : (t == 15 ? 32u * 9u : 0u);
+            fs_schedule16<1>(w, f.kw);
+            publish(1);
+            fs_schedule16<2>(w, f.kw);
+            publish(2);
+            fs_schedule16<3>(w, f.kw);
+            publish(3);
+        }
+    } else if (wave == 0) {
+        ShaLanes l;
+        l.init(lane);
+        uint32_t st[4], h[4], k[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            h[i] = f.h0[(lane & 4) + i];
+            k[i] = f.k16[(lane & 4) + i];
+            st[i] = __builtin_bswap32(f.m[(lane & 4) + i]);
+        }
+        if (lane >= 8 && lane < 16)
+            ((uint32_t *)f.kw)[lane] = (lane == 9 ? 0x80000000u : (lane == 15 ? 32u * 9u : 0u)) + f.k16[lane];
+#pragma unroll 1
+        for (int i = 0; i < n; i++) {
+            if ((lane & ~4) == 0) f.kw[lane >> 2] = make_uint4(st[0] + k[0], st[1] + k[1], st[2] + k[2], st[3] + k[3]);
+            if (lane == 0) __hip_atomic_store(&f.go, (uint32_t)(i + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint4 x[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) x[q] = f.kw[q];
+            l.start(h, x[0].x);
+#pragma unroll 1
+            for (int p = 1; p < 4; p++) {
+                l.rounds16(x, 0);
+                uint32_t got;
+                do {  // as in fs_hash_rounds
+                    got = __hip_atomic_load(&f.ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int q = 0; q < 4; q++) x[q] = f.kw[4 * p + q];
+                    asm volatile("" ::: "memory");
+                } while (got < 3 * (uint32_t)i + (uint32_t)p);
+                l.q += x[0].x & l.m;
+            }
+            l.rounds16(x, 0);
+#pragma unroll
+            for (int q = 0; q < 4; q++) st[q] = h[q] + l.v[q];
+            if (lane == 0)
+#pragma unroll
+                for (int q = 0; q < 4; q++) raw[4 * i + q] = __builtin_bswap32(st[q]);
+        }
+        if (n > 0 && (lane & ~4) == 0)
+#pragma unroll
+            for (int q = 0; q < 4; q++) f.m[lane + q] = __builtin_bswap32(st[q]);
+        if (lane == 0) f.ready = f.go = 0;
+    }
 }
 
 // The block: a draw with its barriers.
