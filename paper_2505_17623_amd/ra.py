@@ -416,8 +416,17 @@ def prove_layer(ctx: Context, A: torch.Tensor, B: torch.Tensor, s: int, relu: bo
         if wit is None:
             wit = witness_outputs(n, k, A.device)
         ra_witness_plan(ctx, s, relu, mode, t, wit)
-    C, mm = ra_sumcheck_matmul_prove(ctx, A, B, None if bufs is None else bufs["C"], ws)
-    (R, Rm, Y, Z, bits), info = ra_rescale_relu_witness(ctx, C, s, relu, mode, t, wit, ws)
+    # a witness call without t waits for the stream by itself, so the matrix
+    # call before it need not (one wait and its idle gap less per layer)
+    join = t < 0 and not ctx.deferred
+    if join:
+        ctx.set_deferred(True)
+    try:
+        C, mm = ra_sumcheck_matmul_prove(ctx, A, B, None if bufs is None else bufs["C"], ws)
+        (R, Rm, Y, Z, bits), info = ra_rescale_relu_witness(ctx, C, s, relu, mode, t, wit, ws)
+    finally:
+        if join:
+            ctx.set_deferred(False)
     rs = ra_range_prove(ctx, bits, R, Y, info, ws)
     tr = {}
 
