@@ -1180,10 +1180,10 @@ ra_status ra_prove_layer_fp2(ra_ctx *c, const void *d_A, ra_dtype a_dtype, const
                            nullptr, s, io->t >= 0 ? &hp : nullptr, (uint32_t *)(c->d_wit + kWitFlags), &wit);
 
     // matrix instance: a = the rows of A bound at r1, b = the columns of B at r2
-    launch_f2_bind(d_A, a_dtype, d_B, n, m, k, E1, E2, scr, Ta, Tb, s);
+    // (and EQ, and the claims at (r1, r2) as partials)
+    launch_f2_sides(F2Sides{d_B, n, m, k, lk, E1, E2, Tb, EQ, d_R, d_Rm, d_Y, relu, N, cpart, 0, 0, 0, 0, nullptr}, d_A,
+                    a_dtype, scr, Ta, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
-    // the claims at (r1, r2), as partials
-    launch_f2_claims(E1, E2, lk, EQ, d_R, d_Rm, d_Y, relu, N, cpart, s);
     // plane rounds: the Gram matrix's two parts from EQ's two parts (the F_p
     // Gram pass with EQ as its row table and a column table of one entry, 1,
     // which the suffix tables hold), and the plane-bound table Bx with the two
@@ -1472,11 +1472,12 @@ extern "C" ra_status ra_prove_layer_fs(ra_ctx *c, const void *d_A, ra_dtype a_dt
     };
 
     // matrix instance: A's rows bound at r1, B's columns at r2; a*, b* absorbed at its end
-    launch_f2_bind(d_A, a_dtype, d_B, n, m, k, E1, E2, scr, Ta, Tb, s);
+    // (and EQ, and the claims at (r1, r2) as partials)
+    launch_f2_sides(F2Sides{d_B, n, m, k, lk, E1, E2, Tb, EQ, d_R, d_Rm, d_Y, relu, N, cpart, 0, 0, 0, 0, nullptr}, d_A,
+                    a_dtype, scr, Ta, s);
     uint64_t *ev_mm = tr + kF2TrFixed, *ev_rs = ev_mm + 6 * (size_t)lm, *ev_zc = ev_rs + 8 * (size_t)(lP + lN);
     instance(F2_MATMUL, lm, Ta, Tb, Ta, Tb, ev_mm, tr);
     // the claims at (r1, r2) absorbed; lambda, mu, tau_p drawn
-    launch_f2_claims(E1, E2, lk, EQ, d_R, d_Rm, d_Y, relu, N, cpart, s);
     launch_fs_claims(cpart, f2_blocks(N), tr + 6, c->d_fs, lam, 4 + lP, err, s);
     // plane rounds: the Gram matrix's two parts in one launch (no plane-bound
     // table: sigma_p does not exist yet), then the rounds, which draw sigma_p as

@@ -346,12 +346,25 @@ struct F2PlaneArgs {
     uint32_t *err = nullptr;
 };
 // The row binding of A (n x m, int16 / int32) at E1 and the column binding of
-// B (m x k) at E2 into Ta, Tb (contiguous re, im); scr: 2 m bind_rows_chunks words.
-void launch_f2_bind(const void *A, int a_dtype, const int16_t *B, uint32_t n, uint32_t m, uint32_t k, F2Tab E1,
-                    F2Tab E2, uint64_t *scr, F2Tab Ta, F2Tab Tb, hipStream_t st);
-// EQ = E1 (x) E2 and the claims R~, Rm~, Y~, Z~ as partials, eight words per block (f2_blocks(N)).
-void launch_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y,
-                      int relu, uint64_t N, uint64_t *part, hipStream_t st);
+// B (m x k) at E2 into Ta, Tb (Ta: contiguous re, im; scr: 2 m bind_rows_chunks
+// words), and EQ = E1 (x) E2 with the claims R~, Rm~, Y~, Z~ as partials, eight
+// words per block (f2_blocks(N)).
+struct F2Sides {
+    const int16_t *B;
+    uint32_t n, m, k;
+    int lk;
+    F2Tab E1, E2, Tb, EQ;
+    const int32_t *R;
+    const uint16_t *Rm;
+    const int32_t *Y;
+    int relu;
+    uint64_t N;
+    uint64_t *cpart;
+    // set by the launcher
+    uint32_t per, groups, ncols, nclaims;
+    uint64_t *chunks;
+};
+void launch_f2_sides(F2Sides a, const void *A, int a_dtype, uint64_t *scr, F2Tab Ta, hipStream_t st);
 // The Gram matrix's two parts from the partial tiles, and (claims given) the claims' totals.
 void launch_f2_gram_sum(const uint64_t *gp_re, const uint64_t *gp_im, int nblk, int tiles, uint64_t *G_re,
                         uint64_t *G_im, const uint64_t *cpart, int cblocks, uint64_t *claims, hipStream_t st);

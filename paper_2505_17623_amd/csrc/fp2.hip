@@ -90,19 +90,18 @@ void launch_f2_eqs(const uint64_t *r, int ln, int lk, F2Tab E1, F2Tab E2, f2 *HS
 // The bound sides of the product.  Binding an integer table at a point of
 // F_{p^2} is linear in the eq table, so one pass over the table sums both
 // parts, by limbs of the eq values (limbs.hpp).  Two F_p
-// bindings per side read each table twice and took six launches; the two
-// sides of a 512 x 4096 by 4096 x 4096 layer went from 46 to 32 us.
+// bindings per side read each table twice and took six launches.
 // ---------------------------------------------------------------------------
 // part[chunk][2 cols]: the sums over a chunk's rows, real parts then imaginary
 template <typename T>
-__global__ __launch_bounds__(256) void k_f2_bind_rows(const T *__restrict__ A, uint32_t rows, uint32_t cols, F2Tab E,
-                                                      uint32_t per_chunk, uint64_t *__restrict__ part)
+__device__ __forceinline__ void f2_bind_rows(const T *__restrict__ A, uint32_t rows, uint32_t cols, F2Tab E,
+                                             uint32_t per_chunk, uint64_t *__restrict__ part, uint32_t group,
+                                             uint32_t chunk, uint64_t (*red)[2][64])
 {
     using L = BindLimbs<T>;
-    __shared__ uint64_t red[4][2][64];
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t c = blockIdx.x * 64 + lane;
-    const uint32_t r0 = blockIdx.y * per_chunk;
+    const uint32_t c = group * 64 + lane;
+    const uint32_t r0 = chunk * per_chunk;
     const uint32_t r1 = r0 + per_chunk < rows ? r0 + per_chunk : rows;
     uint64_t re = 0, im = 0;
     for (uint32_t b = r0 + wid; b < r1; b += 4 * L::kRun) {  // a wave's run: rows b, b + 4, ..
@@ -126,31 +125,18 @@ __global__ __launch_bounds__(256) void k_f2_bind_rows(const T *__restrict__ A, u
     red[wid][1][lane] = im;
     __syncthreads();
     if (wid < 2 && c < cols)
-        part[((size_t)blockIdx.y * 2 + wid) * cols + c] =
+        part[((size_t)chunk * 2 + wid) * cols + c] =
             m61::add(m61::add(red[0][wid][lane], red[1][wid][lane]), m61::add(red[2][wid][lane], red[3][wid][lane]));
 }
 
 // B's columns, a wave per four rows: lanes take eight consecutive columns (one
 // 16-byte load per row) and read each eq value once for the four rows.
-// Workgroups from nmain on sum the chunks of the row binding (256 of its
-// 2 cols entries each).
-__global__ __launch_bounds__(256) void k_f2_bind_cols(const int16_t *__restrict__ B, uint32_t rows, uint32_t cols,
-                                                      F2Tab E, F2Tab out, uint32_t nmain,
-                                                      const uint64_t *__restrict__ part, int nch, uint32_t acols,
-                                                      uint64_t *__restrict__ aout)
+__device__ __forceinline__ void f2_bind_cols(const int16_t *__restrict__ B, uint32_t rows, uint32_t cols, F2Tab E,
+                                             F2Tab out, uint32_t block)
 {
-    if (blockIdx.x >= nmain) {
-        const uint32_t c = (blockIdx.x - nmain) * 256 + threadIdx.x;
-        if (c >= acols) return;
-        uint64_t v = 0;
-#pragma unroll 8
-        for (int q = 0; q < nch; q++) v = m61::fold(v + part[(size_t)q * acols + c]);
-        aout[c] = m61::canon(v);
-        return;
-    }
     using L = BindLimbs<int16_t>;
     constexpr int RW = 4;
-    const uint32_t r0 = ((blockIdx.x * blockDim.x + threadIdx.x) >> 6) * RW;  // wave-uniform
+    const uint32_t r0 = ((block * blockDim.x + threadIdx.x) >> 6) * RW;  // wave-uniform
     const int lane = threadIdx.x & 63;
     if (r0 >= rows) return;
     typedef int v4i __attribute__((ext_vector_type(4)));
@@ -197,39 +183,18 @@ __global__ __launch_bounds__(256) void k_f2_bind_cols(const int16_t *__restrict_
     }
 }
 
-void launch_f2_bind(const void *A, int a_dtype, const int16_t *B, uint32_t n, uint32_t m, uint32_t k, F2Tab E1,
-                    F2Tab E2, uint64_t *scr, F2Tab Ta, F2Tab Tb, hipStream_t st)
-{
-    const int nch = bind_rows_chunks(n, m);
-    const uint32_t per = (n + nch - 1) / nch;
-    const dim3 grid((m + 63) / 64, nch);
-    if (a_dtype == RA_I16)
-        hipLaunchKernelGGL(k_f2_bind_rows<int16_t>, grid, dim3(256), 0, st, (const int16_t *)A, n, m, E1, per, scr);
-    else
-        hipLaunchKernelGGL(k_f2_bind_rows<int32_t>, grid, dim3(256), 0, st, (const int32_t *)A, n, m, E1, per, scr);
-    // 16-byte loads of eight columns where B's rows allow them, else the two parts one after the other
-    const bool vec = k >= 8 && ((uintptr_t)B & 15) == 0;
-    const uint32_t nmain = vec ? ((m + 3) / 4 + 3) / 4 : 0, extra = (2 * m + 255) / 256;
-    hipLaunchKernelGGL(k_f2_bind_cols, dim3(nmain + extra), dim3(256), 0, st, B, m, k, E2, Tb, nmain,
-                       (const uint64_t *)scr, nch, 2 * m, Ta.re);
-    if (!vec) {
-        launch_bind_cols(B, RA_I16, m, k, E2.re, Tb.re, st);
-        launch_bind_cols(B, RA_I16, m, k, E2.im, Tb.im, st);
-    }
-}
-
 // EQ(x) = E1[x >> lk] E2[x mod 2^lk] for x < N (the eq table of (r1, r2),
 // folded parts) and, on the way, the claims R~, Rm~, Y~ and Z~ = (R~ + Y~) / 2
 // (ReLU, else R~) at (r1, r2): sum_x EQ(x) v(x) in 21-bit limbs of EQ, exact in
 // int64 over runs of 1024 entries.  Per-block partials, eight words per block.
-__global__ __launch_bounds__(256) void k_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *__restrict__ R,
-                                                   const uint16_t *__restrict__ Rm, const int32_t *__restrict__ Y,
-                                                   int relu, uint64_t N, uint64_t *part)
+__device__ __forceinline__ void f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *__restrict__ R,
+                                          const uint16_t *__restrict__ Rm, const int32_t *__restrict__ Y, int relu,
+                                          uint64_t N, uint64_t *part, uint32_t block, uint32_t blocks, uint64_t *red,
+                                          uint64_t *tot)
 {
-    __shared__ uint64_t red[6 * 256], tot[6];
-    const uint64_t mask = (1ull << lk) - 1, stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t mask = (1ull << lk) - 1, stride = (uint64_t)blocks * blockDim.x;
     uint64_t acc[6] = {0, 0, 0, 0, 0, 0};
-    for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; b < N; b += 1024 * stride) {
+    for (uint64_t b = (uint64_t)block * blockDim.x + threadIdx.x; b < N; b += 1024 * stride) {
         int64_t s[6][3] = {};
         const uint64_t e1 = b + 1024 * stride, end = e1 < N ? e1 : N;
         for (uint64_t x = b; x < end; x += stride) {
@@ -255,14 +220,71 @@ __global__ __launch_bounds__(256) void k_f2_claims(F2Tab E1, F2Tab E2, int lk, F
         const int p = threadIdx.x & 1;
         uint64_t v = threadIdx.x < 6 ? tot[threadIdx.x] : tot[p];
         if (threadIdx.x >= 6 && relu) v = m61::rotl(m61::add(v, tot[4 + p]), 60);  // 1 / 2 = 2^60
-        part[8 * (size_t)blockIdx.x + threadIdx.x] = v;
+        part[8 * (size_t)block + threadIdx.x] = v;
     }
 }
 
-void launch_f2_claims(F2Tab E1, F2Tab E2, int lk, F2Tab EQ, const int32_t *R, const uint16_t *Rm, const int32_t *Y,
-                      int relu, uint64_t N, uint64_t *part, hipStream_t st)
+// The column binding, the claims and the row binding in one launch, longest
+// first: each alone leaves the chip waiting on loads (one or two waves per
+// SIMD), and none needs another's results.  Three launches one after the other
+// took 53 us for a 512 x 4096 by 4096 x 4096 layer, this and the launch that
+// sums the row chunks 36 to 40 (MI355X).
+template <typename T>
+__global__ __launch_bounds__(256) void k_f2_sides(F2Sides a, const T *__restrict__ A)
 {
-    hipLaunchKernelGGL(k_f2_claims, dim3(f2_blocks(N)), dim3(kThreads), 0, st, E1, E2, lk, EQ, R, Rm, Y, relu, N, part);
+    __shared__ union {
+        uint64_t red[6 * 256];
+        uint64_t rows[4][2][64];
+    } u;
+    __shared__ uint64_t tot[6];
+    uint32_t b = blockIdx.x;
+    if (b < a.ncols) {
+        f2_bind_cols(a.B, a.m, a.k, a.E2, a.Tb, b);
+        return;
+    }
+    b -= a.ncols;
+    if (b < a.nclaims) {
+        f2_claims(a.E1, a.E2, a.lk, a.EQ, a.R, a.Rm, a.Y, a.relu, a.N, a.cpart, b, a.nclaims, u.red, tot);
+        return;
+    }
+    b -= a.nclaims;
+    f2_bind_rows<T>(A, a.n, a.m, a.E1, a.per, a.chunks, b % a.groups, b / a.groups, u.rows);
+}
+
+// out = the chunk rows of part (cols words each) added up
+__global__ __launch_bounds__(256) void k_f2_sum_chunks(const uint64_t *__restrict__ part, int nch, uint32_t cols,
+                                                       uint64_t *__restrict__ out)
+{
+    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= cols) return;
+    uint64_t v = 0;
+#pragma unroll 8
+    for (int q = 0; q < nch; q++) v = m61::fold(v + part[(size_t)q * cols + c]);
+    out[c] = m61::canon(v);
+}
+
+void launch_f2_sides(F2Sides a, const void *A, int a_dtype, uint64_t *scr, F2Tab Ta, hipStream_t st)
+{
+    const int nch = bind_rows_chunks(a.n, a.m);
+    a.per = (a.n + nch - 1) / nch;
+    a.groups = (a.m + 63) / 64;
+    a.chunks = nch > 1 ? scr : Ta.re;  // one chunk: its sums are canonical and Ta's parts lie one after the other
+    // 16-byte loads of eight columns where B's rows allow them, else the two parts one after the other
+    const bool vec = a.k >= 8 && ((uintptr_t)a.B & 15) == 0;
+    a.ncols = vec ? ((a.m + 3) / 4 + 3) / 4 : 0;
+    a.nclaims = f2_blocks(a.N);
+    const dim3 grid(a.ncols + a.nclaims + a.groups * nch);
+    if (a_dtype == RA_I16)
+        hipLaunchKernelGGL(k_f2_sides<int16_t>, grid, dim3(256), 0, st, a, (const int16_t *)A);
+    else
+        hipLaunchKernelGGL(k_f2_sides<int32_t>, grid, dim3(256), 0, st, a, (const int32_t *)A);
+    if (nch > 1)
+        hipLaunchKernelGGL(k_f2_sum_chunks, dim3((2 * a.m + 255) / 256), dim3(256), 0, st, (const uint64_t *)scr, nch,
+                           2 * a.m, Ta.re);
+    if (!vec) {
+        launch_bind_cols(a.B, RA_I16, a.m, a.k, a.E2.re, a.Tb.re, st);
+        launch_bind_cols(a.B, RA_I16, a.m, a.k, a.E2.im, a.Tb.im, st);
+    }
 }
 
 // ---------------------------------------------------------------------------
