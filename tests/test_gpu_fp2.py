@@ -97,6 +97,15 @@ def test_fp2_round_passes(ra, n, m, k, s, relu, mode, mag):
     test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag)
 
 
+# the bindings and the claims in one launch: one row chunk (n <= 4: its sums are the bound side), two, 128, with the
+# narrowest matrix the wide loads take (k = 8) and below; column groups of one and of many
+@pytest.mark.parametrize("n,m,k,s,relu,mode,mag", [(4, 32, 8, 7, True, 0, 300), (8, 256, 8, 7, False, 0, 300),
+                                                   (512, 16, 16, 7, True, 0, 300), (16, 64, 4, 7, True, 0, 300),
+                                                   (2, 2048, 512, 9, True, 0, 64)])
+def test_fp2_sides(ra, n, m, k, s, relu, mode, mag):
+    test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag)
+
+
 @pytest.mark.parametrize("n,m,k,s,relu,mode,mag", SHAPES)
 def test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag):
     rng = np.random.default_rng(n * 131 + m * 7 + k)
