@@ -11,7 +11,7 @@
 //     Gram pass, EQ(x) = E1 E2;
 //   - the bound sides of the product (an integer table bound at a point of
 //     F_{p^2} is the pair of its F_p bindings with the eq table's two parts,
-//     so the F_p binding kernels serve);
+//     formed in one pass);
 //   - the plane rounds' Gram matrix G = sum_x EQ(x) bit bit^T, whose two
 //     parts the F_p Gram pass computes from EQ's two parts;
 //   - every folded table of the rounds.
