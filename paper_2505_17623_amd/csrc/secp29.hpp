@@ -334,10 +334,13 @@ FE bool add_end(const F &U1, const F &S1, const F &P, const F &R, Pt &o, F &PP, 
     return true;
 }
 
-// p + (x, y), x and y fresh or negated
+// p + (x, y), x and y fresh or negated by limbs; so may p.Y be (a run's first
+// point), where a plain difference for R would have magnitude 2, and R^2 twice
+// the bound: p.Y goes into the product's reduction.  (Making a negated y fresh
+// instead costs a reduction in nearly every step of a wave.)
 FE void add_affine(Pt &p, const F &x, const F &y)
 {
-    const F P = sub(mul(x, p.ZZ), p.X), R = sub(mul(y, p.ZZZ), p.Y);
+    const F P = sub(mul(x, p.ZZ), p.X), R = mul_sub(y, p.ZZZ, 1, p.Y);
     Pt o;
     F PP, PPP;
     if (!add_end(p.X, p.Y, P, R, o, PP, PPP)) {  // equal or opposite

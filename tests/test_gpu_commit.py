@@ -209,3 +209,26 @@ def test_commit_equal_and_opposite_points(ra, ctx, gens_small, n):
     for v in (np.full(n, 5, dtype=np.int32), pairs, mixed):
         got = ra.commit(ctx, torch.from_numpy(v).cuda(), same)
         assert got == ec.encode(ec.commit([int(v.sum())], [gens[0]])), int(v.sum())
+
+
+@pytest.mark.parametrize("n", [2, 1024, 5000])
+def test_commit_edge_points(ra, ctx, n):
+    """Points with y = q - 1 and y = 6 (x a cube root of y^2 - 7), whose limbs
+    are all full or all empty, taken with either sign in every order within a
+    thread's run and a bucket: the extremes of the lazy limbs, which hashed
+    generators do not reach."""
+    pts = []
+    for y in (ec.Q - 1, 6):
+        x = pow((y * y - 7) % ec.Q, (ec.Q + 2) // 9, ec.Q)  # q = 7 mod 9
+        assert ec.on_curve((x, y)) and y % 2 == 0
+        pts.append((x, y))
+    rng = np.random.default_rng(n)
+    which = rng.integers(0, 2, size=n)
+    which[:2] = [0, 1]
+    limbs = ra.point_limbs(pts)[which].view(np.int32)
+    gens = torch.from_numpy(np.ascontiguousarray(limbs)).cuda()
+    signs = rng.choice([-1, 1], size=n).astype(np.int32)
+    for v in (np.full(n, -1, dtype=np.int32), np.full(n, 1, dtype=np.int32), signs):
+        got = ra.commit(ctx, torch.from_numpy(v).cuda(), gens)
+        sums = [int(v[which == g].sum()) for g in (0, 1)]
+        assert got == ec.encode(ec.commit(sums, pts)), sums
