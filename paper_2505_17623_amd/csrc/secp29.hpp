@@ -14,6 +14,10 @@
 // residue's representative below 2^261 or so in size; "magnitude" m below is a
 // bound of m 2^29 on the limbs' size.  A product's operands need m1 m2 < 3.5
 // (9 m1 m2 2^58 < 2^63), a difference of two products m1 m2 + m3 m4 < 3.5.
+//
+// The point formulas are those of the Explicit-Formulas Database (Bernstein,
+// Lange) for y^2 = x^3 + b: in XYZZ coordinates madd-2008-s, add-2008-s and
+// dbl-2008-s-1 (Sutherland), and the plain Jacobian doubling for a = 0.
 #pragma once
 #include "secp256k1.hpp"
 
@@ -394,21 +398,25 @@ FE Jac dbl(const Jac &p)  // the identity (Z = 0) stays one
     return r;
 }
 
-// a^(q - 2): the exponent is 223 ones, a zero, 22 ones, 0000101101
+// a^(q - 2), q - 2 = (2^223 - 1) 2^33 + (2^22 - 1) 2^10 + 45: runs of 223 and 22
+// ones, then 45 = 5 8 + 5 in ten bits.  With ones(n) = a^(2^n - 1), ones(i + j) =
+// ones(i)^(2^j) ones(j); the long run is reached through the short one, 223 =
+// 10 22 + 3, and 22 = 2 (2 5 + 1).
 static __device__ __noinline__ F inverse(F a)
 {
-    auto sq = [](F x, int n) {
+    auto shift = [](F x, int n, const F &low) {  // x^(2^n) low
         for (int i = 0; i < n; i++) x = sqr(x);
-        return x;
+        return mul(x, low);
     };
-    const F x2 = mul(sqr(a), a), x3 = mul(sqr(x2), a), x6 = mul(sq(x3, 3), x3), x9 = mul(sq(x6, 3), x3);
-    const F x11 = mul(sq(x9, 2), x2), x22 = mul(sq(x11, 11), x11), x44 = mul(sq(x22, 22), x22);
-    const F x88 = mul(sq(x44, 44), x44), x176 = mul(sq(x88, 88), x88), x220 = mul(sq(x176, 44), x44);
-    const F x223 = mul(sq(x220, 3), x3);  // a^(2^223 - 1)
-    F r = mul(sq(x223, 23), x22);
-    r = mul(sq(r, 5), a);
-    r = mul(sq(r, 3), x2);
-    return mul(sq(r, 2), a);
+    const F ones2 = shift(a, 1, a);
+    const F ones5 = shift(shift(ones2, 2, ones2), 1, a);
+    const F ones11 = shift(shift(ones5, 5, ones5), 1, a);
+    const F ones22 = shift(ones11, 11, ones11);
+    const F ones44 = shift(ones22, 22, ones22);
+    const F ones110 = shift(shift(ones44, 44, ones44), 22, ones22);
+    const F ones223 = shift(shift(ones110, 110, ones110), 3, shift(ones2, 1, a));
+    const F a5 = shift(a, 2, a);
+    return shift(shift(shift(ones223, 23, ones22), 7, a5), 3, a5);
 }
 
 #undef FE
