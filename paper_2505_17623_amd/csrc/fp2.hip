@@ -631,7 +631,7 @@ __global__ __launch_bounds__(256) void k_f2_planes(F2PlaneArgs a)
                 if (tid < 4) gsh[tid] = g;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 const uint32_t ql = fsl.m[8];
-                const bool ok = fs_append(fsl, ql, (const uint32_t *)gsh, 16, tid, 64);
+                const bool ok = fs_append(fsl, ql, gsh, 16, tid, 64);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 if (tid == 0) {
                     if (ok) fsl.m[8] = ql + 64;

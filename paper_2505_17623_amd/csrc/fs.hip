@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256) void k_fs_claims(const uint64_t *__restrict__ 
         for (int q = 0; q < 8; q++) v[q] = m61::add(v[q], part[8 * (size_t)b + q]);
     const uint64_t *tot = m61::block_sum_lds<8>(v, red);
     if (tid < 8) out8[tid] = tot[tid];
-    if (!fs_absorb(f, (const uint32_t *)tot, 16) && tid == 0) *err = 1;
+    if (!fs_absorb(f, tot, 16) && tid == 0) *err = 1;
     fs_draws(f, out, ndraw);
     __syncthreads();
     fs_push(fs, f);
@@ -426,7 +426,7 @@ __device__ __forceinline__ f2 fs_finish_prev(FsFinLds &l, const FsFinArgs &a, bo
         if (lane < D1) l.g[lane] = g;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const uint32_t q = l.f.m[8];
-        const bool ok = fs_append(l.f, q, (const uint32_t *)l.g, 4 * D1, lane, 64);
+        const bool ok = fs_append(l.f, q, l.g, 4 * D1, lane, 64);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (lane == 0) {
             if (ok) l.f.m[8] = q + 16 * D1;
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
                 l.g[lane] = g;
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const bool ok = fs_append(l.f, qlen, (const uint32_t *)l.g, 4 * D1, lane, 64);
+            const bool ok = fs_append(l.f, qlen, l.g, 4 * D1, lane, 64);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (lane == 0) {
                 if (ok) l.f.m[8] = qlen + 16 * D1;
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(kFsTailThreads) void k_fs_tail(FsTailArgs a)
         }
         for (int q = 0; q < nfin; q++) stp(a.out + (KIND == F2_MATMUL ? 2 : 0) + 2 * q, fin[q]);
     }
-    if (!fs_absorb(l.f, (const uint32_t *)fin, 4 * nfin) && tid == 0) *a.err = 1;
+    if (!fs_absorb(l.f, fin, 4 * nfin) && tid == 0) *a.err = 1;
     fs_push(a.fs_out, l.f);
 }
 

@@ -75,21 +75,26 @@ __device__ inline void fs_push(sha::Transcript *g, const FsLds &f)
     for (int i = threadIdx.x; i < words; i += blockDim.x) d[i] = f.m[i];
 }
 
-// Threads t of nt: words w[0 .. nw) behind the pending ones and the padding
-// behind them, where they fit (false: more than sha::kFsPending bytes
-// pending).  The length is the caller's to set, once f.m[8] has been read.
-__device__ __forceinline__ bool fs_append(FsLds &f, uint32_t q, const uint32_t *w, int nw, int t, int nt)
+// Threads t of nt: the nw 32-bit words at w (of any type) behind the pending
+// ones and the padding behind them, where they fit (false: more than
+// sha::kFsPending bytes pending).  The length is the caller's to set, once
+// f.m[8] has been read.
+__device__ __forceinline__ bool fs_append(FsLds &f, uint32_t q, const void *w, int nw, int t, int nt)
 {
     if (q + 4 * (uint32_t)nw > sha::kFsPending) return false;
     const int at = 9 + (int)(q >> 2);
-    for (int i = t; i < nw; i += nt) f.m[at + i] = w[i];
+    for (int i = t; i < nw; i += nt) {
+        uint32_t x;
+        __builtin_memcpy(&x, (const char *)w + 4 * i, 4);  // the words of 64-bit values: a copy, not a read as another type
+        f.m[at + i] = x;
+    }
     fs_pad(f, at + nw, t, nt);
     return true;
 }
 
-// The block: append nw 32-bit words (readable by every thread).  Barriers on
-// both sides; false: more than sha::kFsPending bytes pending.
-__device__ inline bool fs_absorb(FsLds &f, const uint32_t *w, int nw)
+// The block: append the nw 32-bit words at w (of any type, readable by every
+// thread).  Barriers on both sides; false: more than sha::kFsPending bytes pending.
+__device__ inline bool fs_absorb(FsLds &f, const void *w, int nw)
 {
     __syncthreads();
     const uint32_t q = f.m[8];
