@@ -145,3 +145,27 @@ def test_plan_state_and_arguments(ra):
     with pytest.raises(ra.RAError) as e:
         ra.ra_witness_plan(ctx, 4, True, 0, 3, outs)       # between a layer's calls
     assert e.value.code == -7
+
+
+# whether prove_layer joins the matrix call's wait with the witness call's: it does where both make less than eight
+# launches (the fused front) and where the device works long enough; small layers without the fused front, and
+# unaligned ones, keep their own wait.  The proof is the same either way.
+@pytest.mark.parametrize("n,m,k,offset,joined", [(1, 4, 1, 0, False), (16, 16, 16, 0, False), (64, 64, 4, 0, False),
+                                                 (64, 32, 64, 0, False), (64, 64, 64, 1, False), (64, 64, 64, 0, True),
+                                                 (1, 64, 8, 0, True), (256, 8, 1024, 0, True), (2, 4096, 2, 0, True)])
+def test_waits_joined_where_it_pays(ra, n, m, k, offset, joined):
+    rng = np.random.default_rng(n + m + k)
+    dev = []
+    for r, c in ((n, m), (m, k)):
+        buf = torch.zeros(r * c + 8, dtype=torch.int16, device="cuda")
+        dev.append(buf[offset: offset + r * c].reshape(r, c))
+        dev[-1].copy_(torch.from_numpy(rng.integers(-300, 300, size=(r, c)).astype(np.int16)))
+    chal = inputs.xorshift64_stream(17 + n, 1024)
+    ctx, calls = ra.Context(chal), []
+    plain = ctx.set_deferred
+    ctx.set_deferred = lambda on: (calls.append(on), plain(on))
+    got = ra.prove_layer(ctx, *dev, 7, True, 0)
+    assert calls == ([True, False] if joined else []) and not ctx.deferred
+    want = orc.prove_layer(dev[0].cpu().numpy(), dev[1].cpu().numpy(), 7, True, 0, chal, 0)
+    check_network(ra, [got], [want], f"{n}x{m}x{k}")
+    assert ctx.cursor() == want["cursor"]
