@@ -483,8 +483,9 @@ Fp2Layout fp2_layout(bool a_i32, uint32_t n, uint32_t m, uint32_t k)
     l.o_gp0 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_gp1 = cv.take<uint64_t>((size_t)gb * gt * kGramTileWords);
     l.o_g = cv.take<uint64_t>(2 * 4096);
-    // given challenges: every pass's partials; hashed: two copies of ten words per block
-    l.o_part = cv.take<uint64_t>((size_t)std::max(1, f2_passes(lm) + 2 * f2_passes(lN)) * kF2PassPart);
+    // given challenges: every pass's partials; hashed: two copies of ten words per block, where there is a pass
+    static_assert(kFsTailLog >= kF2TailLog, "a hashed pass only where there is one with given challenges");
+    l.o_part = cv.take<uint64_t>((size_t)(f2_passes(lm) + 2 * f2_passes(lN)) * kF2PassPart);
     l.o_cpart = cv.take<uint64_t>((size_t)kF2MaxBlocks * 8);
     l.o_cst = cv.take<uint64_t>(8);
     l.tr_words = kF2TrFixed + 6 * (size_t)lm + 8 * (size_t)(kMaxPlaneLog + lN) + 8 * (size_t)lN;

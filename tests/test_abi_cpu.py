@@ -40,6 +40,15 @@ def test_exports_every_declared_symbol(ra):
         assert hasattr(L, s), s
 
 
+@pytest.mark.parametrize("n,m,k,most", [(1, 1, 1, 205056), (1, 2, 1, 238080), (2, 2, 2, 369408), (64, 4, 64, 1611776)])
+def test_fp2_workspace_does_not_grow(ra, n, m, k, most):
+    """A workspace that once sufficed for a layer over F_{p^2} still does:
+    `most` is the size of the layout before the rounds took partials per pass."""
+    sz = ctypes.c_size_t()
+    assert ra.lib().ra_workspace_size_fp2(n, m, k, ctypes.byref(sz)) == 0
+    assert sz.value <= most
+
+
 def test_commit_batch_workspace_size(ra):
     """ra_commit_batch_workspace_size: one table's region per table (each as
     ra_commit's, rounded to 256 bytes) plus 64 output bytes per table; no
