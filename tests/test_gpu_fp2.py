@@ -106,6 +106,24 @@ def test_fp2_sides(ra, n, m, k, s, relu, mode, mag):
     test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag)
 
 
+# int32 rows that a wave reduces in one run of 512, in two and in sixteen (a quarter of n / 128 rows each), most entries
+# of the largest size and one sign, so that the limb sums would leave int64 if sixteen runs were one: a* = A~(r1) of a
+# one-column A
+@pytest.mark.parametrize("ln", [18, 19, 22])
+def test_fp2_bind_rows_many_runs(ra, ln):
+    rng = np.random.default_rng(ln)
+    A = np.full((1 << ln, 1), -(2 ** 31), dtype=np.int32)
+    A[:: 7] = 2 ** 31 - 1
+    A[rng.integers(0, 1 << ln, size=1000), 0] = rng.integers(-(2 ** 31), 2 ** 31, size=1000)
+    B = np.array([[3]], dtype=np.int16)
+    chal = inputs.xorshift64_stream(40 + ln, 1024)
+    g = ra.prove_layer_fp2(ra.Context(chal), torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), 16, False, 0)
+    r1 = [(int(chal[2 * j]), int(chal[2 * j + 1])) for j in range(ln)]
+    a = orc.mle_int_fp2(A[:, 0].astype(np.int64), r1)
+    assert g["transcript"]["a_star"] == tuple(a) and g["transcript"]["b_star"] == (3, 0)
+    assert g["transcript"]["c0"] == tuple(3 * x % P61 for x in a)
+
+
 @pytest.mark.parametrize("n,m,k,s,relu,mode,mag", SHAPES)
 def test_fp2_layer_parity_shapes(ra, n, m, k, s, relu, mode, mag):
     rng = np.random.default_rng(n * 131 + m * 7 + k)

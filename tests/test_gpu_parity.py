@@ -63,6 +63,22 @@ def test_mle_bind_int16_columns(ra, rows, cols, offset):
     assert [int(x) for x in got] == want
 
 
+# row bindings whose waves reduce more than once: a wave takes a quarter of a chunk's rows (rows / 128 here) in runs of
+# 512 (int32) or 2^15 (int16): exactly one run, two and sixteen, most entries of the largest size and one sign, so that
+# an int32 column's limb sums would leave int64 (2^13 rows a wave, 2^63 and more) if its sixteen runs were one
+@pytest.mark.parametrize("dt,lrows,cols", [(np.int32, 18, 2), (np.int32, 19, 2), (np.int32, 22, 2), (np.int32, 19, 1),
+                                           (np.int16, 24, 1), (np.int16, 25, 1)])
+def test_mle_bind_rows_many_runs(ra, dt, lrows, cols):
+    rng = np.random.default_rng(lrows + cols)
+    info = np.iinfo(dt)
+    T = np.full((1 << lrows, cols), info.min, dtype=dt)
+    T[:: 7] = info.max
+    T[rng.integers(0, 1 << lrows, size=1000), 0] = rng.integers(info.min, info.max, size=1000)
+    z = [int(x) for x in inputs.xorshift64_stream(70 + lrows, lrows)]
+    got = ra.ra_mle_bind(ra.Context(seed=4), torch.from_numpy(T).cuda(), True, z).cpu().numpy()
+    assert [int(x) for x in got] == [orc.mle_int(T[:, c].astype(np.int64), z) for c in range(cols)]
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (4, 8), (64, 32), (512, 256), (8, 2048), (128, 1)])
 @pytest.mark.parametrize("dt", [np.int16, np.int32, np.int64, "field"])
 def test_mle_bind_parity(ra, shape, dt):
