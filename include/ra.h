@@ -361,9 +361,9 @@ ra_status ra_commit(ra_ctx *ctx, const void *d_values, ra_dtype dtype, uint64_t 
  * the Pedersen vector commitment g^a): table t has d_values[t] (device,
  * caller-owned), dtypes[t] (RA_I16, RA_U16, RA_I32 or RA_U64) and ns[t]
  * values, every table committed with the generators d_gens from generator 0
- * (at least max ns[t] of them).  The tables' bucket passes run one after
- * another; their bucket sums, bit sums and final doubling chains each run in
- * one launch for all tables, so the short serial parts of the tables overlap.
+ * (at least max ns[t] of them).  The bucket passes, the bucket sums, the bit
+ * sums and the final doubling chains each run in one launch for all tables, so
+ * the short serial parts of the tables overlap.
  * out: 64 host bytes per table, table t at out + 64 t, the same bytes
  * ra_commit gives.  count in 1 .. 64 (RA_E_INVAL for 0, a null pointer or an
  * unknown dtype; RA_E_NOT_IMPLEMENTED above 64).  Workspace:

@@ -263,8 +263,4 @@ __device__ __forceinline__ f2 f2_plane_bound(uint64_t w, int tabs, const f2 (*ta
     return l2canon(s);
 }
 
-// ---- suffix eq tables of the point r = (r1, r2) ----
-// LS: the last kF2Low variables, a heap: entry 2^k + y is eq over the last k
-// variables at y.  HS: the variables before them, in the same form.
-
 }  // namespace ra

@@ -27,9 +27,11 @@
 
 namespace ra {
 
-// The eq tables of a layer in one launch: segments E1, E2 (SoA), LS, HS
-// (f2.hpp; heaps, entry 2^k + y), each entry the product of its variables'
-// factors.
+// The eq tables of a layer in one launch, each entry the product of its
+// variables' factors: E1, E2 (SoA) and the suffix eq tables of the point r = (r1,
+// r2), which the rounds take their weights from.  LS: the last kF2Low variables,
+// a heap: entry 2^k + y is eq over the last k variables at y.  HS: the variables
+// before them, in the same form.
 __global__ __launch_bounds__(256) void k_f2_eqs(const uint64_t *__restrict__ r, int ln, int lk, F2Tab E1, F2Tab E2,
                                                 f2 *__restrict__ HS, f2 *__restrict__ LS,
                                                 const uint64_t *__restrict__ sig, int lP, F2Tab SIG)
@@ -296,7 +298,7 @@ void launch_f2_sides(F2Sides a, const void *A, int a_dtype, uint64_t *scr, F2Tab
 // per launch in registers: a thread reads the four entries of a quad, sums
 // both rounds and writes the one entry left, so a table crosses memory 1.25
 // times per two rounds, and the range and the ReLU instance share the launch.
-// Bound by the field products (20 of F_{p^2} per range quad, about 1100 VALU
+// Bound by the field products (19 of F_{p^2} per range quad, about 1100 VALU
 // instructions).  One round per launch over tables that carried EQ took 430 us
 // for the two instances of 2^21 and the one of 2^21 without ReLU; this takes
 // 160 (MI355X).
