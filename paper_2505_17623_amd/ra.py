@@ -407,7 +407,7 @@ def prove_layer(ctx: Context, A: torch.Tensor, B: torch.Tensor, s: int, relu: bo
     written again by later calls with it (a caller proving the same shapes
     repeatedly saves the allocations).  With t given and plan set, the
     witness is announced (ra_witness_plan) and computed inside the product."""
-    (n, m), k = A.shape, B.shape[1]
+    n, k = A.shape[0], B.shape[1]
     if bufs is not None and "C" not in bufs:
         bufs["C"] = torch.empty((n, k), dtype=torch.int64, device=A.device)
         bufs["wit"] = witness_outputs(n, k, A.device)
@@ -425,8 +425,10 @@ def prove_layer(ctx: Context, A: torch.Tensor, B: torch.Tensor, s: int, relu: bo
     # Else they make eight or nine, and the saving outweighs that only where the
     # device works longer than the host takes: 1 x 4 x 1 106 -> 118 us, 64 x 16 x
     # 64 118 -> 123, but 1024 x 16 x 256 143 -> 139 and 8 x 4096 x 4 133 -> 124.
-    join = t < 0 and not ctx.deferred and (m >= 64 and k >= 8 and not (A.data_ptr() | B.data_ptr()) & 15 or
-                                           n * k >= 1 << 18 or m >= 4096)
+    join = False
+    if t < 0 and not ctx.deferred:
+        m = A.shape[1]
+        join = (m >= 64 and k >= 8 and not (A.data_ptr() | B.data_ptr()) & 15) or n * k >= 1 << 18 or m >= 4096
     if join:
         ctx.set_deferred(True)
     try:
