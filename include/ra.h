@@ -127,6 +127,9 @@ const char *ra_status_str(ra_status st);
  *     meaningful (create a new context to continue).
  *   ra_ctx_set_deferred(ctx, 0): completes what is pending and returns to
  *     synchronous calls (a device error found then is kept for ra_ctx_sync).
+ *     A synchronous caller without t can save the matrix call's wait by turning
+ *     deferred mode on before it and off after the witness call, which waits;
+ *     it pays where the device's work outlasts the launches.
  *   ra_ctx_sync: waits for all enqueued work, writes every pending host
  *     output, and returns the first error met since the last ra_ctx_sync
  *     (RA_OK if none).  Harmless in synchronous mode. */
